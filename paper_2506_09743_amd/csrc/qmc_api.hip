@@ -490,12 +490,18 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     }
     const int n_ao = (int)angf.size();
     std::vector<double> mo((size_t)n_ao * nmo_pad, 0.0);
-    std::vector<float> mo_f((size_t)n_ao * nmo_pad, 0.0f);
+    // rows up to the next multiple of 4 and four more (the operands of the
+    // next four rows are loaded ahead) stay zero
+    const size_t a_rows = (size_t)((n_ao + 3) / 4) * 4 + 4;
+    std::vector<double> mo_a(a_rows * nmo_pad, 0.0);
+    std::vector<float> mo_fa(a_rows * nmo_pad, 0.0f);
     for (int mu = 0; mu < n_ao; ++mu)
         for (int m = 0; m < d->n_mo; ++m) {
             const double v = d->mo_coef[(size_t)mu * d->n_mo + old_of_new[m]] * angf[mu];
+            const size_t at = (size_t)mu * nmo_pad + (m % 4) * (nmo_pad / 4) + m / 4;
             mo[(size_t)mu * nmo_pad + m] = v;
-            mo_f[(size_t)mu * nmo_pad + m] = (float)v;
+            mo_a[at] = v;
+            mo_fa[at] = (float)v;
         }
     std::vector<double> atoms;
     double vnn = 0.0;
@@ -516,7 +522,8 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     const size_t o_shells = push_bytes(blob, shells.data(), shells.size());
     const size_t o_prims = push_bytes(blob, prims.data(), prims.size());
     const size_t o_mo = push_bytes(blob, mo.data(), mo.size());
-    const size_t o_mof = push_bytes(blob, mo_f.data(), mo_f.size());
+    const size_t o_moa = push_bytes(blob, mo_a.data(), mo_a.size());
+    const size_t o_mofa = push_bytes(blob, mo_fa.data(), mo_fa.size());
     const size_t o_dets = push_bytes(blob, dets.data(), dets.size());
     const size_t o_ci = push_bytes(blob, ci.data(), ci.size());
     const size_t o_ent = push_bytes(blob, entries.data(), entries.size());
@@ -586,7 +593,8 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     S.shells = (const int4 *)(base + o_shells);
     S.prims = (const double2 *)(base + o_prims);
     S.mo = (const double *)(base + o_mo);
-    S.mo_f = (const float *)(base + o_mof);
+    S.mo_a = (const double *)(base + o_moa);
+    S.mo_fa = (const float *)(base + o_mofa);
     S.dets = (const int *)(base + o_dets);
     S.ci = (const double *)(base + o_ci);
     S.entries = (const int4 *)(base + o_ent);

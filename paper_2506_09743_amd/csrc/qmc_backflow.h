@@ -41,14 +41,6 @@
 namespace qmc {
 namespace walker {
 
-// The system tables never change while a kernel runs: read through the
-// constant address space, a load whose address is the same on every lane
-// becomes a scalar load.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(4))) T *const_tab(const T *p) {
-    return (const __attribute__((address_space(4))) T *)p;
-}
-
 // Walker-local lane of electron j.
 __device__ __forceinline__ int lane_of(const DevSystem &S, int j) {
     return j < S.n_up ? j : S.G + (j - S.n_up);

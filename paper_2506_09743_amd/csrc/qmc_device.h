@@ -38,7 +38,11 @@ struct DevSystem {
     const int4 *shells;     // [n_shells]: atom, l, kn, nprim
     const double2 *prims;   // [n_prim]: exponent, coefficient x radial normalisation
     const double *mo;       // [n_ao][nmo_pad]: permuted columns, angular factors folded in
-    const float *mo_f;      // same, FP32
+    // The same rows in the order of the matrix-core operands, in FP64 and
+    // FP32: entry [mu][c % 4][c / 4] is column c of row mu; at least 4 rows
+    // past the last multiple of 4 are zero.
+    const double *mo_a;
+    const float *mo_fa;
     const int *dets;        // [n_det][kDetInts]
     const double *ci;       // [n_det], canonicalisation signs folded in
     const int4 *entries;    // [n_entries + 1]: spin, slot k, MO v, first contribution

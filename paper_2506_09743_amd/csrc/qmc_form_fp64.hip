@@ -17,8 +17,9 @@ hipError_t launch_form_explicit(QMC_LAUNCH_ARGS) {
 hipError_t launch_eval_fd(const DevSystem &S, const double *X, int64_t W, double h, double *LP, double *EL,
                           hipStream_t st) {
     const int64_t blocks = (W + S.WPW - 1) / S.WPW;
-    QMC_NMO_SWITCH(hipLaunchKernelGGL((k_eval_fd<N>), dim3((unsigned)blocks), dim3(kWave),
-                                      (size_t)S.WPW * (walker_lds<N, false>(S)) * sizeof(double), st, S, X, W, h, LP, EL);
+    QMC_NMO_SWITCH(size_t lds = (size_t)S.WPW * (walker_lds<N, false>(S)) * sizeof(double);
+                   if (lds < walker::orbital_lds_bytes<N>()) lds = walker::orbital_lds_bytes<N>();
+                   hipLaunchKernelGGL((k_eval_fd<N>), dim3((unsigned)blocks), dim3(kWave), lds, st, S, X, W, h, LP, EL);
                    return hipGetLastError())
 }
 

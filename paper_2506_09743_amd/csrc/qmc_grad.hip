@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
 
     // ---- shared stages: MO values, Gauss-Jordan, determinants, a_e ----------
     Core<NMO> c;
-    core_stages<NMO, RT, 0, false, false, false, true>(S, L, wsm, x0, x1, x2, c);
+    core_stages<NMO, RT, 0, false, false, false, true>(S, L, wsm, x0, x1, x2, c, smem);
     const double gJ[3] = {c.gJ0, c.gJ1, c.gJ2};
     const double *Tg = sT + L.grp * ts;
     const double *Cg = sC + L.grp * ts;
@@ -566,8 +566,8 @@ template <int NMO>
 static hipError_t launch_grad_t(const DevSystem &S, const double *X, int64_t W, const GradOut &G, bool mixed,
                                 hipStream_t st) {
     const int64_t blocks = (W + S.WPW - 1) / S.WPW;
-    const size_t lds =
-        (size_t)S.WPW * (walker_lds<NMO>(S) + grad_extra_lds<NMO>(S)) * sizeof(double);
+    size_t lds = (size_t)S.WPW * (walker_lds<NMO>(S) + grad_extra_lds<NMO>(S)) * sizeof(double);
+    if (lds < walker::orbital_lds_bytes<NMO>()) lds = walker::orbital_lds_bytes<NMO>();
     if (mixed)
         hipLaunchKernelGGL((k_grad<NMO, float>), dim3((unsigned)blocks), dim3(kWave), lds, st, S, X, W, G);
     else

@@ -25,14 +25,14 @@ constexpr double kRefineKinetic = 3.0e4;
 
 // Evaluates log|Psi|, sign and E_L of the lane's walker at the electron
 // positions held by its lanes (x0, x1, x2 of the lane's electron).  Every
-// lane of the block must call it (it contains block barriers); results are
+// lane of the wave must call it (it exchanges through LDS); results are
 // identical on all lanes of a walker.  need: a mixed form's result must be
 // refined in FP64 (kinetic energy not finite or above kRefineKinetic).
-template <int NMO, typename RT, int MF, bool EXPL, int BF>
+template <int NMO, typename RT, int MF, bool EXPL, int BF, bool VK = false>
 __device__ __forceinline__ WalkerResult eval_walker(const DevSystem &S, const Lane &L, double *wsm, double x0,
                                                     double x1, double x2, void *stage, bool &need) {
     Core<NMO> c;
-    core_stages<NMO, RT, MF, EXPL, BF>(S, L, wsm, x0, x1, x2, c, stage);
+    core_stages<NMO, RT, MF, EXPL, BF, false, false, VK>(S, L, wsm, x0, x1, x2, c, stage);
 
     // ---- pass 2: grad and Laplacian of Sigma at this electron ---------------
     double gS0, gS1, gS2, lapS;
@@ -44,7 +44,7 @@ __device__ __forceinline__ WalkerResult eval_walker(const DevSystem &S, const La
         gS2 = c.bgS2;
         lapS = c.blap;
     } else {
-        sigma_derivs<NMO, RT>(S, x0, x1, x2, c.av, gS0, gS1, gS2, lapS);
+        sigma_derivs<NMO, RT, VK>(S, L.lane, (double *)stage, x0, x1, x2, c.av, gS0, gS1, gS2, lapS);
     }
 
     // ---- local energy and log|Psi| ------------------------------------------
@@ -68,7 +68,7 @@ __device__ __forceinline__ WalkerResult eval_walker(const DevSystem &S, const La
         res.sign = c.sgn_up * c.sgn_dn * (c.Ssum < 0.0 ? -1.0 : 1.0);
         res.eloc = eloc;
     }
-    __syncthreads();  // LDS is reused by the next evaluation
+    wave_sync();  // LDS is reused by the next evaluation
     return res;
 }
 
@@ -156,51 +156,82 @@ struct StepMarks {
     double in_mark, done_mark, defer_mark;
 };
 
+// A loop over steps reads the system and its lane's place anew in every
+// trip: what the compiler would otherwise hoist (table pointers, rows,
+// a comparison mask per lane predicate) does not fit the scalar registers,
+// and came back from vector lanes one word at a time (540 reads in the H2
+// kernel).  DevSystem is the first kernel argument.
+__device__ __forceinline__ const DevSystem &fresh_system() {
+    auto *p = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const DevSystem *)p;
+}
+
+__device__ __forceinline__ Lane fresh_lane(const Lane &L, int valid) {
+    Lane F = L;
+    asm volatile("" : "+v"(F.lw), "+v"(F.grp), "+v"(F.i), "+v"(F.e), "+v"(F.nsig), "+v"(F.lane), "+v"(valid));
+    F.wvalid = valid != 0;
+    F.active = F.wvalid && F.i < F.nsig;
+    return F;
+}
+
 // n_steps Metropolis steps of the valid walkers of a wave (w: this lane's
 // walker).  Mixed forms read a caller's sign entry as its sign.  INL (mixed
 // forms): a walker whose proposal needs FP64 orbitals is evaluated again
 // with them right away (the wave runs the FP64 evaluation when any of its
 // walkers needs it), so any number of steps can be taken; otherwise mixed
-// forms take one step per call and defer such walkers.
-template <int NMO, typename RT, int MF, bool EXPL, int BF, bool INL = false>
-__device__ __forceinline__ void metropolis_wave(const DevSystem &S, const Lane &L, int64_t w, double *__restrict__ X,
+// forms take one step per call and defer such walkers.  ONE: a single step;
+// the walker's state is then read after the evaluation (only the proposal
+// stays in registers across it) and the positions of a rejected move are
+// left as they are.
+template <int NMO, typename RT, int MF, bool EXPL, int BF, bool INL = false, bool ONE = !INL>
+__device__ __forceinline__ void metropolis_wave(const DevSystem &S0, const Lane &L0, int64_t w, double *__restrict__ X,
                                                 double *__restrict__ LP, double *__restrict__ SG,
                                                 double *__restrict__ EL, int n_steps, double sigma, uint64_t seed,
                                                 uint64_t step0, uint32_t walker_offset, double *__restrict__ ACC,
                                                 double *smem, StepMarks mk) {
     constexpr bool kMixed = sizeof(RT) != sizeof(double);
-    double *wsm = smem + L.wloc * lds_per_walker<NMO, RT, EXPL, BF>(S);
+    double *wsm = smem + L0.wloc * lds_per_walker<NMO, RT, EXPL, BF>(S0);
     double x0 = 0.0, x1 = 0.0, x2 = 0.0;
-    if (L.active) {
-        const double *p = X + (w * S.ne + L.e) * 3;
+    if (L0.active) {
+        const double *p = X + (w * S0.ne + L0.e) * 3;
         x0 = p[0];
         x1 = p[1];
         x2 = p[2];
     }
     double lp = 0.0, sg = 0.0, el = 0.0;
-    if (L.wvalid) {
-        lp = LP[w];
-        sg = SG[w] - mk.in_mark;
-        el = EL[w];
-        if constexpr (kMixed) sg = sg > 0.0 ? 1.0 : (sg < 0.0 ? -1.0 : 0.0);
-    }
     // running accumulators start from the caller's values, so a block split
     // at any step gives the same sums as one block
     // (the two counts are integer-valued doubles below 2^31 in the array)
     double s_e = 0.0, s_e2 = 0.0;
     int n_acc = 0, n_bad = 0;
-    if (L.wvalid) {
-        s_e = ACC[4 * w + 0];
-        s_e2 = ACC[4 * w + 1];
-        n_acc = (int)ACC[4 * w + 2];
-        n_bad = (int)ACC[4 * w + 3];
-    }
+    auto load_state = [&]() {
+        if (L0.wvalid) {
+            lp = LP[w];
+            sg = SG[w] - mk.in_mark;
+            el = EL[w];
+            if constexpr (kMixed) sg = sg > 0.0 ? 1.0 : (sg < 0.0 ? -1.0 : 0.0);
+            s_e = ACC[4 * w + 0];
+            s_e2 = ACC[4 * w + 1];
+            n_acc = (int)ACC[4 * w + 2];
+            n_bad = (int)ACC[4 * w + 3];
+        }
+    };
+    if constexpr (!ONE) load_state();
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     const uint32_t wid = walker_offset + (uint32_t)w;
     const double s32 = 1.0 / 4294967296.0;
     const double two_pi = 6.283185307179586;
-    bool defer = false;
-    for (int t = 0; t < n_steps; ++t) {
+    auto uniform = [&](uint64_t step) {
+        uint32_t ca[4] = {wid, (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)S0.ne};
+        philox4x32_10(ca, k0, k1);
+        const uint64_t bits = ((((uint64_t)ca[0]) << 32) | (uint64_t)ca[1]) >> 11;
+        return (double)bits * (1.0 / 9007199254740992.0);
+    };
+    bool defer = false, moved = false;
+    for (int t = 0; t < (ONE ? 1 : n_steps); ++t) {
+        const DevSystem &S = ONE ? S0 : fresh_system();
+        const Lane L = ONE ? L0 : fresh_lane(L0, L0.wvalid ? 1 : 0);
         const uint64_t step = step0 + (uint64_t)t;
         uint32_t c[4] = {wid, (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)L.e};
         philox4x32_10(c, k0, k1);
@@ -215,24 +246,28 @@ __device__ __forceinline__ void metropolis_wave(const DevSystem &S, const Lane &
         const double y0 = __dadd_rn(x0, __dmul_rn(sigma, z0));
         const double y1 = __dadd_rn(x1, __dmul_rn(sigma, z1));
         const double y2 = __dadd_rn(x2, __dmul_rn(sigma, z2));
-        uint32_t ca[4] = {wid, (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)S.ne};
-        philox4x32_10(ca, k0, k1);
-        const uint64_t bits = ((((uint64_t)ca[0]) << 32) | (uint64_t)ca[1]) >> 11;
-        const double u = (double)bits * (1.0 / 9007199254740992.0);
+
+        // the acceptance uniform: beside the proposal in a loop over steps (the
+        // two generators' rounds overlap), after the evaluation otherwise
+        double u = 0.0;
+        if constexpr (!ONE) u = uniform(step);
 
         bool need;
-        WalkerResult r = eval_walker<NMO, RT, MF, EXPL, BF>(S, L, wsm, y0, y1, y2, smem, need);
+        WalkerResult r = eval_walker<NMO, RT, MF, EXPL, BF, !ONE>(S, L, wsm, y0, y1, y2, smem, need);
         if constexpr (kMixed && INL) {
             if (__any(need ? 1 : 0)) {
                 bool unused;
                 const WalkerResult r64 =
-                    eval_walker<NMO, double, 0, false, false>(S, L, wsm, y0, y1, y2, smem, unused);
+                    eval_walker<NMO, double, 0, false, false, true>(S, L, wsm, y0, y1, y2, smem, unused);
                 if (need) r = r64;
             }
-        } else {
-            defer = kMixed && need;
+        }
+        if constexpr (ONE) load_state();
+        if constexpr (kMixed && !INL) {
+            defer = need;
             if (defer) continue;  // one step per call
         }
+        if constexpr (ONE) u = uniform(step);
         const bool acc = isfinite(r.logpsi) && (u < exp(2.0 * (r.logpsi - lp)));
         if (acc) {
             x0 = y0;
@@ -241,6 +276,7 @@ __device__ __forceinline__ void metropolis_wave(const DevSystem &S, const Lane &
             lp = r.logpsi;
             sg = r.sign;
             el = r.eloc;
+            moved = true;
         }
         // a state without a finite log|Psi| and E_L is counted, not summed
         if (isfinite(el) && isfinite(lp)) {
@@ -252,16 +288,16 @@ __device__ __forceinline__ void metropolis_wave(const DevSystem &S, const Lane &
         n_acc += acc ? 1 : 0;
     }
     if (defer) {  // state unchanged, sign marked
-        if (L.wvalid && L.lw == 0) SG[w] = sg + mk.defer_mark;
+        if (L0.wvalid && L0.lw == 0) SG[w] = sg + mk.defer_mark;
         return;
     }
-    if (L.active) {
-        double *p = X + (w * S.ne + L.e) * 3;
+    if (L0.active && moved) {
+        double *p = X + (w * S0.ne + L0.e) * 3;
         p[0] = x0;
         p[1] = x1;
         p[2] = x2;
     }
-    if (L.wvalid && L.lw == 0) {
+    if (L0.wvalid && L0.lw == 0) {
         LP[w] = lp;
         SG[w] = sg + mk.done_mark;
         EL[w] = el;
@@ -301,10 +337,9 @@ __global__ __launch_bounds__(kWave, (metro_waves<RT, MF, EXPL, BF>())) void k_me
         L.wvalid = false;
         L.active = false;
     }
-    const int steps = metro_one_step<RT, MF, EXPL, BF>() ? 1 : n_steps;
     const StepMarks mk{0.0, 0.0, kMixed ? mark_of(0, step0) : 0.0};
-    metropolis_wave<NMO, RT, MF, EXPL, BF>(S, L, w, X, LP, SG, EL, steps, sigma, seed, step0, walker_offset, ACC,
-                                            smem, mk);
+    metropolis_wave<NMO, RT, MF, EXPL, BF, false, metro_one_step<RT, MF, EXPL, BF>()>(
+        S, L, w, X, LP, SG, EL, n_steps, sigma, seed, step0, walker_offset, ACC, smem, mk);
 }
 
 // Metropolis block in one launch (step loop) for blocks of at most
@@ -433,7 +468,7 @@ __global__ __launch_bounds__(kWave, 1) void k_eval_fd(DevSystem S, const double 
     {
         Core<NMO> c;
         double y0 = x0, y1 = x1, y2 = x2;
-        core_stages<NMO, double, 0, false, false, true>(S, L, wsm, y0, y1, y2, c);
+        core_stages<NMO, double, 0, false, false, true>(S, L, wsm, y0, y1, y2, c, smem);
         vpot = walker_sum(L.active ? c.vpot : 0.0, S.LW) + S.vnn;
         lp0 = walker_sum(c.J, S.LW) + c.logD_up + c.logD_dn + log(fabs(c.Ssum));
         sg0 = c.sgn_up * c.sgn_dn * (c.Ssum < 0.0 ? -1.0 : 1.0);
@@ -450,7 +485,7 @@ __global__ __launch_bounds__(kWave, 1) void k_eval_fd(DevSystem S, const double 
             else y2 = x2 + step;
         }
         Core<NMO> c;
-        core_stages<NMO, double, 0, false, false, true>(S, L, wsm, y0, y1, y2, c);
+        core_stages<NMO, double, 0, false, false, true>(S, L, wsm, y0, y1, y2, c, smem);
         const double lp = walker_sum(c.J, S.LW) + c.logD_up + c.logD_dn + log(fabs(c.Ssum));
         const double sg = c.sgn_up * c.sgn_dn * (c.Ssum < 0.0 ? -1.0 : 1.0);
         lap += sg * sg0 * exp(lp - lp0) - 1.0;
@@ -508,6 +543,7 @@ static hipError_t launch_t(bool mc, const DevSystem &S, double *X, double *LP, d
     constexpr bool kMixed = sizeof(RT) != sizeof(double);
     const int64_t blocks = (W + S.WPW - 1) / S.WPW;
     size_t lds = (size_t)S.WPW * lds_per_walker<NMO, RT, EXPL, BF>(S) * sizeof(double);
+    if (!BF && lds < orbital_lds_bytes<NMO>()) lds = orbital_lds_bytes<NMO>();
     if (MF > 0 && lds < (size_t)kStageBytes) lds = kStageBytes;
     const hipStream_t st = cs.st;
     hipError_t e = hipSuccess;

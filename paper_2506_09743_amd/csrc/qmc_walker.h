@@ -29,12 +29,40 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace qmc {
 namespace walker {
 
 // Determinant and cofactor records fetched per batch.
 constexpr int kRecBatch = 4;
 
+// The system tables never change while a kernel runs: read through the
+// constant address space, a load whose address is the same on every lane
+// becomes a scalar load, and no load is held back by the LDS exchanges
+// between it and its use.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *const_tab(const T *p) {
+    return (const __attribute__((address_space(4))) T *)p;
+}
+typedef double double2v __attribute__((ext_vector_type(2)));
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int4v shell_info(const DevSystem &S, int sh) {  // atom, l, kn, nprim
+    return const_tab((const int4v *)S.shells)[sh];
+}
+__device__ __forceinline__ double2v prim_info(const DevSystem &S, int p) {  // exponent, coefficient
+    return const_tab((const double2v *)S.prims)[p];
+}
+
+// Orders a wave's LDS accesses across its lanes: the work-group is one wave,
+// whose LDS instructions execute in order, so only the compiler has to keep
+// them so.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // Cross-lane exchange within a row of 16 lanes by DPP moves (no LDS round
 // trip).  Walkers (LW <= 16 lanes) and spin groups (G <= 8 lanes) are
@@ -71,6 +99,14 @@ __device__ __forceinline__ int span_sum_i(int v, int n) {
     if (n > 2) v += dpp_i<kSwap2>(v);
     if (n > 4) v += dpp_i<kHalfMirror>(v);
     if (n > 8) v += dpp_i<kMirror>(v);
+    return v;
+}
+
+__device__ __forceinline__ uint32_t span_max_u(uint32_t v, int n) {
+    if (n > 1) v = max(v, (uint32_t)dpp_i<kSwap1>((int)v));
+    if (n > 2) v = max(v, (uint32_t)dpp_i<kSwap2>((int)v));
+    if (n > 4) v = max(v, (uint32_t)dpp_i<kHalfMirror>((int)v));
+    if (n > 8) v = max(v, (uint32_t)dpp_i<kMirror>((int)v));
     return v;
 }
 
@@ -178,22 +214,27 @@ __device__ __forceinline__ double ratio_code(const double *T, uint32_t c, int ts
     return a * T[h2 * ts + p2] - T[h1 * ts + p2] * T[h2 * ts + p1];
 }
 
-// d = a * b + c as one three-address FMA: the constant c stays in the
-// register that holds it for the whole kernel instead of being copied into
-// the accumulator of a two-address FMA before every use.
+// d = a * b + c as one three-address FMA: the constant c is not copied into
+// the accumulator of a two-address FMA before every use.  VK: c in vector
+// registers (the kernels that loop over steps at one wave per SIMD have
+// those to spare, and hoist more scalars out of the loop than fit), else in
+// scalar ones.
+template <bool VK>
 __device__ __forceinline__ double fma_c(double a, double b, double c) {
     double d;
-    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    if constexpr (VK) asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    else asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
     return d;
 }
 
 // exp(x) in FP64 (qmc_exp.h), its polynomial's multiply-adds as
 // three-address FMAs.
-__device__ __forceinline__ double exp_f64(double x) { return exp_cody_waite(x, fma_c); }
+template <bool VK = false>
+__device__ __forceinline__ double exp_f64(double x) { return exp_cody_waite(x, fma_c<VK>); }
 
-// 1 / x for x >= 1 (the Pade-type denominators 1 + b r): the hardware
-// reciprocal estimate refined by two Newton steps, within an ulp or so of
-// the quotient.
+// 1 / x for x well inside the exponent range (the Pade-type denominators
+// 1 + b r >= 1, elimination pivots): the hardware reciprocal estimate refined
+// by two Newton steps, within an ulp or so of the quotient.
 __device__ __forceinline__ double rcp_ge1(double x) {
     double y = __builtin_amdgcn_rcp(x);
     double e = __builtin_fma(-x, y, 1.0);
@@ -202,23 +243,27 @@ __device__ __forceinline__ double rcp_ge1(double x) {
     return __builtin_fma(y, e, y);
 }
 
-template <typename RT> __device__ __forceinline__ RT rt_exp(RT x);
-template <> __device__ __forceinline__ double rt_exp<double>(double x) { return exp_f64(x); }
-// FP32: the hardware base-2 exponential of x log2(e)
-template <> __device__ __forceinline__ float rt_exp<float>(float x) {
-    return __builtin_amdgcn_exp2f(x * 1.44269504088896341f);
+// a / b given y, 1 / b within an ulp or so: one residual step gives the
+// rounded quotient (a == b gives exactly 1).  b well inside the exponent
+// range.
+__device__ __forceinline__ double div_by_rcp(double a, double b, double y) {
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-q, b, a), y, q);
 }
 
-template <typename RT> __device__ __forceinline__ const RT *mo_table(const DevSystem &S);
-template <> __device__ __forceinline__ const double *mo_table<double>(const DevSystem &S) { return S.mo; }
-template <> __device__ __forceinline__ const float *mo_table<float>(const DevSystem &S) { return S.mo_f; }
+template <typename RT, bool VK>
+__device__ __forceinline__ RT rt_exp(RT x) {
+    if constexpr (sizeof(RT) == sizeof(double)) return exp_f64<VK>(x);
+    // FP32: the hardware base-2 exponential of x log2(e)
+    else return __builtin_amdgcn_exp2f(x * 1.44269504088896341f);
+}
 
 // Radial part of one shell at distance r: R, and with DERIV also R'/r and
 // R'' + (2l+2) R'/r.  Slater R = sum_p c_p r^kn exp(-zeta_p r), so R'/R =
 // kn/r - zeta; Gaussian R = sum_p c_p exp(-alpha_p r^2), so R'/r = -2 alpha R
 // and R'' + (2l+2) R'/r = (4 alpha^2 r^2 - (4l+6) alpha) R.  The primitive
 // coefficients carry the radial normalisation.
-template <typename RT, bool DERIV>
+template <typename RT, bool DERIV, bool VK = false>
 __device__ __forceinline__ void shell_radial(const DevSystem &S, int p, int np, int l, int kn, RT r,
                                              RT r2, RT rinv, RT &Rv, RT &Rd, RT &Rl) {
     Rv = RT(0);
@@ -229,9 +274,9 @@ __device__ __forceinline__ void shell_radial(const DevSystem &S, int p, int np, 
         RT rk = RT(1);
         for (int t = 0; t < kn; ++t) rk *= r;
         for (int q = 0; q < np; ++q) {
-            const double2 pe = S.prims[p + q];
+            const double2v pe = prim_info(S, p + q);
             const RT ex = RT(pe.x);
-            const RT f = RT(pe.y) * rk * rt_exp<RT>(-ex * r);
+            const RT f = RT(pe.y) * rk * rt_exp<RT, VK>(-ex * r);
             Rv += f;
             if (DERIV) {
                 const RT g = RT(kn) * rinv - ex;
@@ -241,136 +286,28 @@ __device__ __forceinline__ void shell_radial(const DevSystem &S, int p, int np, 
         }
     } else {
         const RT fl = RT(4 * l + 6);
-        for (int q = 0; q < np; ++q) {
-            const double2 pe = S.prims[p + q];
+        auto add = [&](double2v pe, RT e) {
             const RT ex = RT(pe.x);
-            const RT f = RT(pe.y) * rt_exp<RT>(-ex * r2);
+            const RT f = RT(pe.y) * e;
             Rv += f;
             if (DERIV) {
                 Rd -= RT(2) * ex * f;
                 Rl += f * (RT(4) * ex * ex * r2 - fl * ex);
             }
+        };
+        // two at a time: one scalar load and two independent exponentials
+        int q = 0;
+        for (; q + 1 < np; q += 2) {
+            const double2v pa = prim_info(S, p + q), pb = prim_info(S, p + q + 1);
+            const RT ea = rt_exp<RT, VK>(-RT(pa.x) * r2), eb = rt_exp<RT, VK>(-RT(pb.x) * r2);
+            add(pa, ea);
+            add(pb, eb);
+        }
+        if (q < np) {
+            const double2v pa = prim_info(S, p + q);
+            add(pa, rt_exp<RT, VK>(-RT(pa.x) * r2));
         }
     }
-}
-
-// Pass 1: MO values phi_m(r_e) = sum_mu C[mu][m] chi_mu(r_e) of the lane's
-// electron (Methods, AO and MO layers).  AO = P(x,y,z) R(r) with P a
-// Cartesian monomial; angular normalisations are folded into the rows of C.
-template <int NMO, typename RT>
-__device__ __forceinline__ void mo_values(const DevSystem &S, double x0, double x1, double x2,
-                                          RT (&phi)[NMO]) {
-#pragma unroll
-    for (int m = 0; m < NMO; ++m) phi[m] = RT(0);
-    const RT *C = mo_table<RT>(S);
-    int p = 0;
-    const RT *crow = C;
-    int atom = -1;
-    RT dx = RT(0), dy = RT(0), dz = RT(0), r2 = RT(0), r = RT(0);
-    for (int sh = 0; sh < S.n_shells; ++sh) {
-        const int4 si = S.shells[sh];
-        if (si.x != atom) {  // shells of one atom share the geometry
-            atom = si.x;
-            const double *A = S.atoms + 4 * atom;
-            // displacement in FP64, cast afterwards
-            dx = RT(x0 - A[0]);
-            dy = RT(x1 - A[1]);
-            dz = RT(x2 - A[2]);
-            r2 = dx * dx + dy * dy + dz * dz;
-            r = sqrt(r2);
-        }
-        RT Rv, Rd, Rl;
-        shell_radial<RT, false>(S, p, si.w, si.y, si.z, r, r2, RT(0), Rv, Rd, Rl);
-        p += si.w;
-        const int nc = (si.y + 1) * (si.y + 2) / 2;
-        for (int c = 0; c < nc; ++c) {
-            RT P;
-            if (si.y == 0) P = RT(1);
-            else if (si.y == 1) P = c == 0 ? dx : (c == 1 ? dy : dz);
-            else {
-                const RT u = (c < 3) ? dx : (c < 5 ? dy : dz);
-                const RT v = (c == 0) ? dx : (c == 1 || c == 3) ? dy : dz;
-                P = u * v;
-            }
-            const RT val = P * Rv;
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) phi[m] += val * crow[m];
-            crow += S.nmo_pad;
-        }
-    }
-}
-
-// Pass 2: grad_e Sigma / Sigma and lap_e Sigma / Sigma.  With a_e[m] =
-// d log Sigma / d phi_m(r_e) and t_mu = sum_m C[mu][m] a_e[m], both are
-// sum_mu t_mu (grad, lap) chi_mu(r_e); for chi = P R:
-//   grad chi = R grad P + P (R'/r) d,   lap chi = R lap P + P (R'' + (2l+2) R'/r).
-// This contraction is the Jacobi trace: the weights t and the products
-// t (grad, lap) chi are FP64 in every form; RT is the arithmetic of the AO
-// derivative factors (FP32 in the mixed forms).
-template <int NMO, typename RT>
-__device__ __forceinline__ void sigma_derivs(const DevSystem &S, double x0, double x1, double x2,
-                                             const double (&av)[NMO], double &g0, double &g1,
-                                             double &g2, double &lap) {
-    const double *C = S.mo;
-    int p = 0;
-    const double *crow = C;
-    double G0 = 0.0, G1 = 0.0, G2 = 0.0, L = 0.0;
-    int atom = -1;
-    RT dx = RT(0), dy = RT(0), dz = RT(0), r2 = RT(0), r = RT(0), rinv = RT(0);
-    for (int sh = 0; sh < S.n_shells; ++sh) {
-        const int4 si = S.shells[sh];
-        if (si.x != atom) {  // shells of one atom share the geometry
-            atom = si.x;
-            const double *A = S.atoms + 4 * atom;
-            dx = RT(x0 - A[0]);
-            dy = RT(x1 - A[1]);
-            dz = RT(x2 - A[2]);
-            r2 = dx * dx + dy * dy + dz * dz;
-            r = sqrt(r2);
-            rinv = RT(1) / r;
-        }
-        RT Rv, Rd, Rl;
-        shell_radial<RT, true>(S, p, si.w, si.y, si.z, r, r2, rinv, Rv, Rd, Rl);
-        p += si.w;
-        const int nc = (si.y + 1) * (si.y + 2) / 2;
-        for (int c = 0; c < nc; ++c) {
-            double t = 0.0;
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) t += crow[m] * av[m];
-            crow += S.nmo_pad;
-            // monomial, its gradient and Laplacian
-            RT P, Px, Py, Pz, PL;
-            if (si.y == 0) {
-                P = RT(1); Px = Py = Pz = PL = RT(0);
-            } else if (si.y == 1) {
-                P = c == 0 ? dx : (c == 1 ? dy : dz);
-                Px = c == 0 ? RT(1) : RT(0);
-                Py = c == 1 ? RT(1) : RT(0);
-                Pz = c == 2 ? RT(1) : RT(0);
-                PL = RT(0);
-            } else {
-                // xx, xy, xz, yy, yz, zz
-                const int iu = (c < 3) ? 0 : (c < 5 ? 1 : 2);
-                const int iv = (c == 0) ? 0 : (c == 1 || c == 3) ? 1 : 2;
-                const RT u = iu == 0 ? dx : (iu == 1 ? dy : dz);
-                const RT v = iv == 0 ? dx : (iv == 1 ? dy : dz);
-                P = u * v;
-                Px = (iu == 0 ? v : RT(0)) + (iv == 0 ? u : RT(0));
-                Py = (iu == 1 ? v : RT(0)) + (iv == 1 ? u : RT(0));
-                Pz = (iu == 2 ? v : RT(0)) + (iv == 2 ? u : RT(0));
-                PL = iu == iv ? RT(2) : RT(0);
-            }
-            const RT PRd = P * Rd;
-            G0 += t * double(Rv * Px + PRd * dx);
-            G1 += t * double(Rv * Py + PRd * dy);
-            G2 += t * double(Rv * Pz + PRd * dz);
-            L += t * double(Rv * PL + P * Rl);
-        }
-    }
-    g0 = G0;
-    g1 = G1;
-    g2 = G2;
-    lap = L;
 }
 
 // ---- BF16 matrix-core contractions (mixed form) ------------------------------
@@ -450,10 +387,10 @@ __device__ __forceinline__ void mo_values_mfma(const DevSystem &S, int lane, voi
     int atom = -1;
     float dx = 0.f, dy = 0.f, dz = 0.f, r2 = 0.f, r = 0.f;
     for (int sh = 0; sh < S.n_shells; ++sh) {
-        const int4 si = S.shells[sh];
+        const int4v si = shell_info(S, sh);
         if (si.x != atom) {  // shells of one atom share the geometry
             atom = si.x;
-            const double *A = S.atoms + 4 * atom;
+            const auto *A = const_tab(S.atoms) + 4 * atom;
             dx = float(x0 - A[0]);
             dy = float(x1 - A[1]);
             dz = float(x2 - A[2]);
@@ -477,20 +414,29 @@ __device__ __forceinline__ void mo_values_mfma(const DevSystem &S, int lane, voi
         }
     }
     for (int k = mu; k < kStageK; ++k) stage_put(st, lane, k, 0.f);
-    __syncthreads();
+    wave_sync();
     mfma_apply<(NMO + 15) / 16, SPLIT>(S, 0, st, lane);
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int m = 0; m < NMO; ++m) phi[m] = st.out[lane * kRowF + m];
-    __syncthreads();
+    wave_sync();
 }
+
+}  // namespace walker
+}  // namespace qmc
+
+#include "qmc_orbitals.h"
+
+namespace qmc {
+namespace walker {
 
 // LDS of one walker (doubles): T tables [2][nmax][cols] at 0 (nmax =
 // max(n_up, n_dn)) and the cofactor tables [2][nmax][cregion] after them,
 // both written from the determinant stage on.  FULL layout (the adjoint's):
 // cols = NMO, the T rows holding A0^-1 in their reference columns.  Compact
 // layout (the evaluation and Metropolis kernels'): only the columns from
-// c0 = min(n_up, n_dn) on, the ones the ratios and cofactors read; A0^-1
+// c0 = min(n_up, n_dn), rounded down to even so that rows are read and
+// written two columns at a time, the ones the ratios and cofactors read; A0^-1
 // passes through the cofactor region (cregion = max(cols, nmax) per row)
 // before the cofactors accumulate there.  Before the determinant stage the
 // same space holds the e-e-n factor table (een_table doubles at 0, when
@@ -506,7 +452,7 @@ __host__ __device__ inline int een_table(const DevSystem &S) {
 
 template <int NMO, bool FULL = true>
 __host__ __device__ inline int tab_c0(const DevSystem &S) {
-    return FULL ? 0 : (S.n_up < S.n_dn ? S.n_up : S.n_dn);
+    return FULL ? 0 : (S.n_up < S.n_dn ? S.n_up : S.n_dn) & ~1;
 }
 
 template <int NMO, bool FULL = true>
@@ -517,14 +463,14 @@ __host__ __device__ inline int tab_cols(const DevSystem &S) {
 template <int NMO, bool FULL = true>
 __host__ __device__ inline int tab_cregion(const DevSystem &S) {
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn, cols = tab_cols<NMO, FULL>(S);
-    return FULL ? cols : (cols > nmax ? cols : nmax);
+    return FULL ? cols : (cols > nmax ? cols : (nmax + 1) & ~1);
 }
 
 template <int NMO, bool FULL = true>
 __host__ __device__ inline int pos_offset(const DevSystem &S) {
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const int t = 2 * nmax * tab_cols<NMO, FULL>(S), f = een_table(S);
-    return f > t ? f : t;
+    return ((f > t ? f : t) + 3 * S.LW + 1) / 2 * 2 - 3 * S.LW;  // the pivot rows are 16-byte aligned
 }
 
 template <int NMO, bool FULL = true>
@@ -532,7 +478,7 @@ __host__ __device__ inline int walker_lds(const DevSystem &S) {
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const int tc = 2 * nmax * (tab_cols<NMO, FULL>(S) + tab_cregion<NMO, FULL>(S));
     const int pp = pos_offset<NMO, FULL>(S) + 3 * S.LW + 2 * NMO;
-    return tc > pp ? tc : pp;
+    return ((tc > pp ? tc : pp) + 1) & ~1;  // 16-byte aligned rows
 }
 
 // ---- Jastrow stage, generic in its scalar type ------------------------------
@@ -588,9 +534,9 @@ struct PlainPrm {
     __device__ bool use_een_term(int) const { return true; }
     __device__ bool use_een(int, int) const { return true; }  // term m, nucleus a
     __device__ double b() const { return S.b; }
-    __device__ double R(int a, int k) const { return S.atoms[4 * a + k]; }
-    __device__ double en(int a, int k) const { return S.jas_en[3 * a + k]; }
-    __device__ double een(int m, int k) const { return S.jas_een[7 * m + k]; }
+    __device__ double R(int a, int k) const { return const_tab(S.atoms)[4 * a + k]; }
+    __device__ double en(int a, int k) const { return const_tab(S.jas_en)[3 * a + k]; }
+    __device__ double een(int m, int k) const { return const_tab(S.jas_een)[7 * m + k]; }
 };
 
 // Seeded entry: kind 0 the Pade b, 1 the e-n parameter (i, k), 2 the e-e-n
@@ -683,7 +629,7 @@ __device__ __forceinline__ JasTerms<T> jastrow_terms(const DevSystem &S, const L
     }
     for (int a = 0; a < S.n_atoms; ++a) {
         const T d0 = x0 - prm.R(a, 0), d1 = x1 - prm.R(a, 1), d2 = x2 - prm.R(a, 2);
-        if constexpr (kPlain) o.vpot -= S.atoms[4 * a + 3] / sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+        if constexpr (kPlain) o.vpot -= const_tab(S.atoms)[4 * a + 3] / sqrt(d0 * d0 + d1 * d1 + d2 * d2);
         if (S.jas_en && prm.use_en(a)) {
             // e-n kernel K = N / D, N = w0 r + w1 r^2, D = 1 + w2 r:
             // K' = (N' - K D') / D and K'' = (N'' - 2 K' D') / D
@@ -752,8 +698,8 @@ struct Core {
 
 // Jastrow and Coulomb terms, pass 1 (MO values), in-place Gauss-Jordan of
 // the reference matrices, determinant ratios, S, cofactor tables and the
-// adjoint vector a_e.  Every lane of the block must call it (it contains
-// block barriers).  On return the walker's LDS holds the T tables
+// adjoint vector a_e.  Every lane of the wave must call it (it exchanges
+// through LDS).  On return the walker's LDS holds the T tables
 // [2][nmax][NMO] at wsm and the cofactor tables right after them.
 template <int NMO>
 __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L, double *wsm,
@@ -773,9 +719,9 @@ __host__ __device__ inline int bf_pos_offset(const DevSystem &S);
 // the values a finite-difference kinetic energy needs.  RT is the arithmetic
 // of the AO evaluation and MF the MO contraction of pass 1 (FP64 when RT is
 // double).  FULLT: the full table layout (walker_lds<NMO, true>), which the
-// adjoint reads; otherwise the compact one.
+// adjoint reads; otherwise the compact one.  VK: see fma_c.
 template <int NMO, typename RT, int MF = 0, bool EXPL = false, int BF = 0, bool PSI = false,
-          bool FULLT = false>
+          bool FULLT = false, bool VK = false>
 __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, double *wsm, double &x0,
                                             double &x1, double &x2, Core<NMO> &c, void *stage = nullptr) {
     // the compact layout serves the low-rank Metropolis and evaluation
@@ -809,7 +755,7 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     sPos[3 * L.lw + 2] = x2;
     const PlainPrm prm{S};
     een_table_fill<double>(S, L, x0, x1, x2, sF, sG, prm);
-    __syncthreads();
+    wave_sync();
 
     // ---- Jastrow and Coulomb terms of this electron (FP64) ----------------
     const JasTerms<double> jt = jastrow_terms<double>(S, L, x0, x1, x2, sPos, sF, sG, prm);
@@ -828,23 +774,26 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     }
 
     // ---- pass 1: MO values of this electron ------------------------------
+    // (the LDS stage of the contractions overlays the walkers' tables, whose
+    // positions the pair loop has read)
     double a[NMO];
     if constexpr (sizeof(RT) == sizeof(double)) {
+        wave_sync();
         double phi[NMO];
-        mo_values<NMO, double>(S, x0, x1, x2, phi);
+        mo_values_f64<NMO, VK>(S, L.lane, (double *)stage, x0, x1, x2, phi);
 #pragma unroll
         for (int m = 0; m < NMO; ++m) a[m] = phi[m];
     } else if constexpr (MF > 0) {
         // the staging area overlays the walkers' tables: wait for the
         // position reads of the pair loop first
-        __syncthreads();
+        wave_sync();
         float phi[NMO];
         mo_values_mfma<NMO, MF>(S, L.lane, stage, x0, x1, x2, phi);
 #pragma unroll
         for (int m = 0; m < NMO; ++m) a[m] = double(phi[m]);
     } else {
-        RT phi[NMO];
-        mo_values<NMO, RT>(S, x0, x1, x2, phi);
+        float phi[NMO];
+        mo_values_f32<NMO>(S, L.lane, x0, x1, x2, phi);
 #pragma unroll
         for (int m = 0; m < NMO; ++m) a[m] = double(phi[m]);
     }
@@ -858,77 +807,95 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     // after the create-time column permutation) is overwritten by the
     // inverse, so at the end the row of slot s holds A0^-1[s][slot(e)] in
     // the columns < n and T[s][v] = (A0^-1 Phi)[s][v] in the virtual columns.
+    // A step's chain is: largest |a[j]| of the rows left, that row through
+    // LDS, one reciprocal, one multiply-add per column.  The largest is taken
+    // on one word per lane (the upper bits of |a[j]|, then the lower lane),
+    // three cross-lane maxima.
     constexpr int JMAX = kMaxSpin < NMO ? kMaxSpin : NMO;
     bool done = !L.active;
-    int slot = -1;
+    int slot = -1, inv_cnt = 0;
     double dprod = 1.0;
     bool singular = false;
 #pragma unroll
     for (int j = 0; j < JMAX; ++j) {
         if (j >= nmax) break;
         const bool work = j < L.nsig;
-        double cand = (work && !done) ? fabs(a[j]) : -1.0;
-        int cl = L.i;
-        span_argmax(cand, cl, S.G);
-        const bool ok = work && cand > 0.0;
-        if (work && !ok) singular = true;
-        const bool is_piv = ok && L.active && L.i == cl;
+        uint32_t key = 0;  // 8 or more for a non-zero candidate
+        if (work && !done && a[j] != 0.0) {
+            const uint32_t hi = (uint32_t)__double2hiint(a[j]) & 0x7FFFFFF8u;
+            key = (hi > 8u ? hi : 8u) | (uint32_t)(7 - L.i);
+        }
+        key = span_max_u(key, S.G);
+        const int cl = 7 - (int)(key & 7u);
+        const bool is_piv = key >= 8u && L.i == cl;
         if (is_piv) {
-            // publish the unscaled pivot row, then scale this row in place
 #pragma unroll
-            for (int m = 0; m < NMO; ++m) piv_row[m] = a[m];
-            const double inv = 1.0 / a[j];
+            for (int m = 0; m < NMO; m += 2) *(double2 *)(piv_row + m) = make_double2(a[m], a[m + 1]);
+        }
+        // rows left above the pivot's: its row permutation's inversions
+        if (key >= 8u && !done && L.i < cl) ++inv_cnt;
+        wave_sync();
+        // the pivot from the published row (none: the column is zero, or NaN)
+        const double piv = key >= 8u ? piv_row[j] : 0.0;
+        const bool ok = fabs(piv) > 0.0;
+        if (work && !ok) singular = true;
+        if (work) dprod *= piv;
+        // multiplier as in Doolittle elimination: equal rows cancel exactly
+        const double y = rcp_ge1(piv);
+        double inv = div_by_rcp(1.0, piv, y), f = div_by_rcp(a[j], piv, y);
+        // (a pivot at the ends of the exponent range takes the full division)
+        const uint32_t top = (uint32_t)__double2hiint(piv) & 0x7FFFFFFFu;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(ok && top - 0x03C00000u > 0x78400000u) != 0, 0)) {
+            inv = 1.0 / piv;
+            f = a[j] / piv;
+        }
+        if (is_piv) {  // this row is scaled in place
 #pragma unroll
             for (int m = 0; m < NMO; ++m) a[m] *= inv;
             a[j] = inv;
             done = true;
             slot = j;
-        }
-        __syncthreads();
-        // the pivot from the published row (a column without one is zero)
-        const double piv = ok ? piv_row[j] : 0.0;
-        if (work) dprod *= piv;
-        if (ok && L.active && !is_piv) {
-            // multiplier as in Doolittle elimination: equal rows cancel exactly
-            const double f = a[j] / piv;
+        } else if (ok) {
 #pragma unroll
-            for (int m = 0; m < NMO; ++m) a[m] -= f * piv_row[m];
+            for (int m = 0; m < NMO; m += 2) {
+                const double2 pr = *(const double2 *)(piv_row + m);
+                a[m] -= f * pr.x;
+                a[m + 1] -= f * pr.y;
+            }
             a[j] = -f;
         }
-        __syncthreads();
+        wave_sync();
     }
     // compact layout: the reference part of each slot's row (A0^-1) goes
     // to the cofactor region for a moment, and each lane keeps its column
     double ainv[JMAX];
     if (L.active && slot >= 0) {
 #pragma unroll
-        for (int m = 0; m < NMO; ++m)
-            if (m >= c0) Tg[slot * ts + m - c0] = a[m];
+        for (int m = 0; m < NMO; m += 2)
+            if (m >= c0) *(double2 *)(Tg + slot * ts + m - c0) = make_double2(a[m], a[m + 1]);
         if constexpr (!kFull) {
 #pragma unroll
             for (int k = 0; k < JMAX; ++k)
-                if (k < L.nsig) Cg[slot * nmax + k] = a[k];
+                if (k < nmax) Cg[slot * nmax + k] = a[k];
         }
     }
     if constexpr (!kFull) {
-        __syncthreads();
+        wave_sync();
         const int sl = slot < 0 ? 0 : slot;
 #pragma unroll
-        for (int k = 0; k < JMAX; ++k) ainv[k] = (k < nmax && k < L.nsig && L.active) ? Cg[k * nmax + sl] : 0.0;
-        __syncthreads();
+        for (int k = 0; k < JMAX; ++k) {
+            const double t = Cg[(k < nmax ? k : 0) * nmax + sl];
+            ainv[k] = (k < L.nsig && L.active) ? t : 0.0;
+        }
+        wave_sync();
     }
     // Permutation parity (slot s <- electron row): inversions within the group.
-    int inv_cnt = 0;
-    for (int ip = 0; ip < S.G; ++ip) {
-        const int so = __shfl(slot, L.gbase + ip);
-        if (L.active && ip > L.i && so >= 0 && so < slot) ++inv_cnt;
-    }
     inv_cnt = span_sum_i(inv_cnt, S.G);
     const double det_sign = ((inv_cnt & 1) ? -1.0 : 1.0) * (dprod < 0.0 ? -1.0 : 1.0);
     const double det_log = log(fabs(dprod));
     // the shared region now becomes the cofactor tables: zero them
-    for (int q = L.lw; q < 2 * cstride; q += S.LW) sC[q] = 0.0;
-    __syncthreads();
+    for (int q = 2 * L.lw; q < 2 * cstride; q += 2 * S.LW) *(double2 *)(sC + q) = make_double2(0.0, 0.0);
+    wave_sync();
 
     const int wb = L.lane - L.lw;
     const double logD_up = __shfl(det_log, wb), logD_dn = __shfl(det_log, wb + S.G);
@@ -940,13 +907,13 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     const double *Tup = sT, *Tdn = sT + tstride;
     double Sp = 0.0;
     for (int i0 = 0; i0 < S.det_rows; i0 += kRecBatch) {
-        uint4 rb[kRecBatch];
+        uint4v rb[kRecBatch];
 #pragma unroll
         for (int u = 0; u < kRecBatch; ++u)
-            rb[u] = i0 + u < S.det_rows ? S.det_recs[(i0 + u) * S.LW + L.lw] : make_uint4(0, 0, 0, 0);
+            rb[u] = i0 + u < S.det_rows ? const_tab((const uint4v *)S.det_recs)[(i0 + u) * S.LW + L.lw] : uint4v{0, 0, 0, 0};
 #pragma unroll
         for (int u = 0; u < kRecBatch; ++u) {
-            const uint4 r = rb[u];
+            const uint4v r = rb[u];
             Sp += __hiloint2double((int)r.y, (int)r.x) * ratio_code(Tup, r.z, ts, c0) * ratio_code(Tdn, r.w, ts, c0);
         }
     }
@@ -959,7 +926,7 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
         c.sgn_up = sgn_up;
         c.sgn_dn = sgn_dn;
         c.sing_walker = sing_walker;
-        __syncthreads();  // the tables are reused by the next evaluation
+        wave_sync();  // the tables are reused by the next evaluation
         return;
     }
 
@@ -969,13 +936,13 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     {
         double acc = 0.0;
         for (int i0 = 0; i0 < S.cof_rows; i0 += kRecBatch) {
-            uint4 rb[kRecBatch];
+            uint4v rb[kRecBatch];
 #pragma unroll
             for (int u = 0; u < kRecBatch; ++u)
-                rb[u] = i0 + u < S.cof_rows ? S.cof_recs[(i0 + u) * S.LW + L.lw] : make_uint4(0, 0, 0, 0);
+                rb[u] = i0 + u < S.cof_rows ? const_tab((const uint4v *)S.cof_recs)[(i0 + u) * S.LW + L.lw] : uint4v{0, 0, 0, 0};
 #pragma unroll
             for (int u = 0; u < kRecBatch; ++u) {
-                const uint4 r = rb[u];  // an all-zero padding record adds 0 and never flushes
+                const uint4v r = rb[u];  // an all-zero padding record adds 0 and never flushes
                 const int spin = (r.w >> 1) & 1;
                 const double *Ts = spin ? Tdn : Tup, *To = spin ? Tup : Tdn;
                 const uint32_t cc = r.z >> 18;
@@ -989,7 +956,7 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
             }
         }
     }
-    __syncthreads();
+    wave_sync();
 
     // ---- a_e = d log Sigma / d phi(r_e) ------------------------------------
     // virtual orbitals: a_e[v] = (A0^-T C)[e][v] / S (C vanishes on the
@@ -1009,29 +976,51 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
             }
         }
         const double Sinv = 1.0 / Ssum;
+        // two columns at a time with every row's reads in one batch; KR, the
+        // rows read, is G (rows past nmax repeat the last one, their a_e
+        // column is zero)
+        auto adjoint = [&](auto rows) {
+            constexpr int KR = decltype(rows)::value < JMAX ? decltype(rows)::value : JMAX;
+            const double *row[KR];
 #pragma unroll
-        for (int v = 0; v < NMO; ++v) av[v] = 0.0;
+            for (int k = 0; k < KR; ++k) row[k] = Cg + (k < nmax ? k : nmax - 1) * ts - c0;
 #pragma unroll
-        for (int k = 0; k < JMAX; ++k) {
-            if (k >= nmax) break;
+            for (int v = 0; v < NMO; v += 2) {
+                double a0 = 0.0, a1 = 0.0;
+                if (v >= c0) {
 #pragma unroll
-            for (int v = 0; v < NMO; ++v)
-                if (v >= c0) av[v] += ainv[k] * Cg[k * ts + v - c0];
-        }
-#pragma unroll
-        for (int v = 0; v < NMO; ++v) av[v] *= Sinv;
-        double h[JMAX];
-#pragma unroll
-        for (int k = 0; k < JMAX; ++k) {
-            h[k] = 0.0;
-            if (k < nmax) {
-#pragma unroll
-                for (int v = 0; v < NMO; ++v)
-                    if (v >= c0) h[k] += Tg[k * ts + v - c0] * av[v];
+                    for (int k = 0; k < KR; ++k) {
+                        const double2 cv = *(const double2 *)(row[k] + v);
+                        a0 += ainv[k] * cv.x;
+                        a1 += ainv[k] * cv.y;
+                    }
+                }
+                av[v] = a0 * Sinv;
+                av[v + 1] = a1 * Sinv;
             }
-        }
+            double h[KR];
 #pragma unroll
-        for (int k = 0; k < JMAX; ++k) av[k] = (k < L.nsig) ? ainv[k] - h[k] : av[k];
+            for (int k = 0; k < KR; ++k) {
+                row[k] += Tg - Cg;
+                h[k] = 0.0;
+            }
+#pragma unroll
+            for (int v = 0; v < NMO; v += 2) {
+                if (v >= c0) {
+#pragma unroll
+                    for (int k = 0; k < KR; ++k) {
+                        const double2 tv = *(const double2 *)(row[k] + v);
+                        h[k] += tv.x * av[v];
+                        h[k] += tv.y * av[v + 1];
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < KR; ++k) av[k] = (k < L.nsig) ? ainv[k] - h[k] : av[k];
+        };
+        if (S.G <= 2) adjoint(std::integral_constant<int, 2>());
+        else if (S.G == 4) adjoint(std::integral_constant<int, 4>());
+        else adjoint(std::integral_constant<int, 8>());
     }
 
     c.slot = slot;
@@ -1100,7 +1089,7 @@ __device__ __forceinline__ void group_gauss_jordan(const DevSystem &S, const Lan
             done = true;
             slot = j;
         }
-        __syncthreads();
+        wave_sync();
         const double piv = ok ? piv_row[j] : 0.0;
         if (work) dprod *= piv;
         if (ok && L.active && !is_piv) {
@@ -1109,7 +1098,7 @@ __device__ __forceinline__ void group_gauss_jordan(const DevSystem &S, const Lan
             for (int m = 0; m < kMaxSpin; ++m) a[m] -= f * piv_row[m];
             a[j] = -f;
         }
-        __syncthreads();
+        wave_sync();
     }
 }
 
@@ -1140,13 +1129,13 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
     const int ncfg_g = L.grp == 0 ? S.n_cfg_up : S.n_cfg_dn;
     const int ncmax = S.n_cfg_up > S.n_cfg_dn ? S.n_cfg_up : S.n_cfg_dn;
 
-    __syncthreads();  // the Jastrow stage's tables are no longer read
+    wave_sync();  // the Jastrow stage's tables are no longer read
 #pragma unroll
     for (int m = 0; m < NMO; ++m) {
         sPhi[L.lw * NMO + m] = phi[m];
         sA[L.lw * NMO + m] = 0.0;
     }
-    __syncthreads();
+    wave_sync();
 
     // pass A: log|D_c| and sign of every configuration of this spin
     for (int q = 0; q < ncmax; ++q) {
@@ -1166,7 +1155,7 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
             cfg_g[3 * q + 1] = singular ? 0.0 : par * (dprod < 0.0 ? -1.0 : 1.0);
         }
     }
-    __syncthreads();
+    wave_sync();
 
     // common shifts, Sigma / (e^mu e^md)
     double mu = -INFINITY, md = -INFINITY;
@@ -1200,7 +1189,7 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
         }
         own[2] = zero ? 0.0 : acc * own[1] * exp(own[0] - m_own) / Ssum;
     }
-    __syncthreads();
+    wave_sync();
 
     // pass B: a_e accumulated from each weighted inverse
     for (int q = 0; q < ncmax; ++q) {
@@ -1220,11 +1209,11 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
 #pragma unroll
             for (int k = 0; k < kMaxSpin; ++k) inv_g[slot * kMaxSpin + k] = a[k];
         }
-        __syncthreads();
+        wave_sync();
         if (live && L.active && slot >= 0) {
             for (int k = 0; k < L.nsig; ++k) sA[L.lw * NMO + occ[k]] += wq * inv_g[k * kMaxSpin + slot];
         }
-        __syncthreads();
+        wave_sync();
     }
 #pragma unroll
     for (int m = 0; m < NMO; ++m) c.av[m] = sA[L.lw * NMO + m];

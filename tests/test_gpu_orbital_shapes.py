@@ -1,0 +1,70 @@
+"""Orbital stages over the shapes of their matrix-core operands: AO counts
+around the multiples of four that a product takes (one AO to more than the
+LDS ring holds), every compiled MO width, shells of each angular momentum in
+orders that straddle the groups of four, and odd and even primitive counts,
+against the FP64 oracle."""
+import numpy as np
+import pytest
+
+from paper_2506_09743_amd import synth
+from parity_helpers import _compare
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(shells, n_mo, n_up, n_dn, basis, seed, n_det=1):
+    """shells: (atom, l, primitives); two atoms, orthonormal MO columns."""
+    rng = np.random.default_rng(seed)
+    nprim = [n for _, _, n in shells]
+    total = sum(nprim)
+    n_ao = sum(synth.n_cart(l) for _, l, _ in shells)
+    occ_up, occ_dn = synth.excitation_dets(n_up, n_dn, n_mo, n_det)
+    d = dict(name="shapes", Z=[3.0, 2.0], R=[[0, 0, -0.8], [0.1, -0.2, 0.9]], n_up=n_up, n_dn=n_dn, basis=basis,
+             shell_atom=[a for a, _, _ in shells], shell_l=[l for _, l, _ in shells],
+             shell_kn=[i % 2 if basis == "sto" else 0 for i in range(len(shells))], shell_nprim=nprim,
+             prim_exp=np.exp(rng.uniform(np.log(0.3), np.log(8.0), total)), prim_coef=rng.uniform(0.3, 1.0, total),
+             mo_coef=synth.orthogonal(n_ao, rng)[:, :n_mo], occ_up=occ_up, occ_dn=occ_dn,
+             ci=np.r_[1.0, rng.normal(0, 0.05, n_det - 1)], jas_b=1.0)
+    return synth._finish(d)
+
+
+S, P, D = 0, 1, 2
+CASES = [
+    # one AO; 4 and 5 AOs; a p shell across the first group of four
+    ("one", [(0, S, 1)], 1, 1, 1, "gto", 1),
+    ("four", [(0, S, 2), (1, P, 3)], 4, 2, 1, "gto", 3),
+    ("five", [(0, S, 1), (0, S, 1), (1, P, 1)], 5, 2, 2, "sto", 4),
+    # d shells first, and 12 MOs on 13 AOs
+    ("d-first", [(0, D, 3), (0, S, 2), (1, D, 1)], 12, 3, 3, "gto", 5),
+    # 16 AOs fill the ring exactly; 17 and 18 wrap it
+    ("ring", [(0, D, 2), (0, P, 5), (1, S, 1), (1, D, 4)], 16, 4, 3, "gto", 6),
+    ("ring+1", [(0, D, 1), (1, D, 1), (1, P, 1), (0, S, 1), (1, S, 1)], 13, 5, 4, "sto", 7),
+    # the atoms in turn, 31 and 41 AOs, the widest MO tables, an empty spin
+    ("turns", [(0, D, 2), (1, D, 3), (0, P, 1), (1, P, 2), (0, D, 1), (1, S, 4), (0, D, 3)], 24, 8, 6, "gto", 8),
+    ("wide", [(0, D, 1), (1, D, 2), (0, D, 3), (1, D, 1), (0, P, 2), (1, P, 1), (0, D, 2), (1, D, 1), (0, S, 6), (1, S, 5)],
+     32, 8, 0, "gto", 9),
+]
+
+
+@pytest.mark.parametrize("W", [67, 1])
+@pytest.mark.parametrize("tag,shells,n_mo,n_up,n_dn,basis,seed", CASES, ids=[c[0] for c in CASES])
+def test_orbital_shapes(torch_cuda, qmc, oracle_mod, tag, shells, n_mo, n_up, n_dn, basis, seed, W):
+    torch = torch_cuda
+    n_det = 6 if n_mo > max(n_up, n_dn) + 1 and min(n_up, n_dn) > 0 else 1
+    sysd = _system(shells, n_mo, n_up, n_dn, basis, seed, n_det)
+    X = synth.init_walkers(sysd, W, 40 + seed)
+    s = qmc.System(sysd, device=0)
+    print(f"orbital shapes {tag} W={W}", flush=True)
+    tX = torch.from_numpy(X).cuda()
+    # every configuration factorised on its own: E_L keeps the orbitals' accuracy
+    xl, xs, xe = [t.cpu().numpy() for t in s.eval(tX, precision="fp64_explicit")]
+    _compare(oracle_mod.OracleSystem(sysd), sysd, X, xl, xs, xe, f"shapes {tag}")
+    # the low-rank update divides by the reference determinant, so single
+    # walkers near its nodes lose digits of E_L there: the median is held
+    lp, sg, el = [t.cpu().numpy() for t in s.eval(tX)]
+    assert np.array_equal(xs, sg) and np.max(np.abs(xl - lp) / np.maximum(1, np.abs(lp))) < 1e-10
+    assert np.median(np.abs(xe - el)) < 1e-9
+    # the mixed FP32 form runs the same stages on FP32 AOs
+    fl, _, fe = [t.cpu().numpy() for t in s.eval(tX, precision="fp32")]
+    assert np.median(np.abs(fl - lp)) < 1e-4 and np.median(np.abs(fe - el)) < 1e-2
+    s.close()
