@@ -3,8 +3,7 @@
 // parameters (Pade b; the e-n and e-e-n parameters of the many-body
 // appendix when present) (Methods, eq. nabla_loss needs d log|Psi| / d theta),
 // and with respect to the nuclear positions (Methods, eq. force needs
-// d E_L / d R and d ln rho / d R = 2 d log|Psi| / d R).  The Jastrow part is
-// differentiated in forward mode (Dual numbers through the Jastrow stage).
+// d E_L / d R and d ln rho / d R = 2 d log|Psi| / d R).
 //
 // With a_e[m] = d log Sigma / d phi_m(r_e) from the shared stages:
 //   d log|Psi| / d theta = sum_e sum_mu t_mu d chi_mu(r_e) / d theta,
@@ -51,11 +50,10 @@ struct GradOut {
 // the block from 0.  The per-nucleus results [n_atoms][6] live past the end
 // of both.
 // After the MO-coefficient gradient the same block holds the walker's
-// positions [LW][3] and the Dual e-e-n tables of the Jastrow directions
-// (2 doubles per entry): [LW][n_atoms][2 een_n] factors, [LW][n_atoms][kEenGeo]
-// geometry.
-__host__ __device__ inline int grad_dual_size(const DevSystem &S) {
-    return 3 * S.LW + 2 * S.LW * S.n_atoms * (2 * S.een_n + kEenGeo);
+// positions [LW][3] and the e-e-n tables of the Jastrow directions:
+// [LW][n_atoms][2 een_n] factors, [LW][n_atoms][kEenGeo] geometry.
+__host__ __device__ inline int grad_jastrow_size(const DevSystem &S) {
+    return 3 * S.LW + S.LW * S.n_atoms * (2 * S.een_n + kEenGeo);
 }
 
 template <int NMO>
@@ -65,8 +63,8 @@ __host__ __device__ inline int grad_rows_end(const DevSystem &S) {
     const int fwd = base + 6 * nmax * NMO;
     const int rows = S.LW * (2 * S.n_ao + 2 * NMO);
     int e = fwd > rows ? fwd : rows;
-    const int dual = grad_dual_size(S);
-    return e > dual ? e : dual;
+    const int jas = grad_jastrow_size(S);
+    return e > jas ? e : jas;
 }
 
 template <int NMO>
@@ -155,6 +153,234 @@ __device__ __forceinline__ Radial radial_full(const DevSystem &S, int p0, int np
         }
     }
     return R;
+}
+
+// d log|Psi| and d E_L of one direction, from this electron's share of d J
+// and of the functional -1/2 d lap_e J - h . d grad_e J, summed over the
+// walker's electrons.
+__device__ __forceinline__ void put_direction(const GradOut &G, const Lane &L, int LW, int64_t w, int out, double dl,
+                                              double de) {
+    dl = walker_sum(dl, LW);
+    de = walker_sum(de, LW);
+    if (L.wvalid && L.lw == 0) {
+        if (G.dlogpsi) G.dlogpsi[w * G.n_param + out] = dl;
+        if (G.deloc_dth) G.deloc_dth[w * G.n_param + out] = de;
+    }
+}
+
+// A radial function f(|x - c|) added to J: lap f = f'' + 2 f'/r, grad f = f' u.
+// Its share of d E_L is -1/2 (f'' + 2 f'/r) - (h . u) f'.
+__device__ __forceinline__ double radial_energy(double f1, double f2, double ri, double hu) {
+    return -0.5 * f2 - f1 * (ri + hu);
+}
+
+// Derivatives with respect to the Jastrow parameters (Pade b; e-n (w0, w1,
+// w2) per nucleus; e-e-n (c, a1, b1, a2, b2, a3, b3) per term) and the
+// Jastrow's part of the nuclear gradients, added to sAtom.  With
+// h = grad_e log|Psi| a change dJ of the Jastrow factor changes E_L by
+// -1/2 sum_e (lap_e dJ + 2 h_e . grad_e dJ), a functional linear in dJ.
+//
+// e-e-n: for an own factor o(u) (u the distance of this electron from the
+// nucleus, t its unit vector) and a pair factor s(r), w the pair's unit
+// vector, the functional of o s is alpha s + (beta . w) s' + gamma (s'' + 2 s'/r),
+//   alpha = -1/2 (o'' + 2 o'/u) - o' h . t,  beta = -(o' t + o h),  gamma = -o / 2,
+// times the partner's factor p.  So one pass over the partners per term and
+// nucleus gives every direction: the parameters c, a1, a2, a3 scale the
+// term; the partner's b and nuclear derivative replace p by dp (dg/db = -g^2,
+// dp/dR = -p' t_j), b3 replaces s, and the own factor's b and nuclear
+// derivative only need the sums A, B, D of jastrow_terms.  A forward-mode
+// pass per direction ran the pair loop 48 times for CO with 5 terms.
+__device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L, int64_t w, double x0, double x1,
+                                               double x2, const double (&h)[3], const double *sPos, const double *sF,
+                                               const double *sG, const GradOut &G, double *sAtom) {
+    const bool need_R = G.dlogpsi_dR || G.deloc_dR;
+    const int p_b = S.n_prim + S.n_ao * S.n_mo;  // output index of b
+    const int p_en = p_b + 1, p_een = p_en + (S.jas_en ? 3 * S.n_atoms : 0);
+    // ---- Pade b: K = a g, dK/db = -a g^2 ------------------------------------
+    double dl = 0.0, de = 0.0;
+    if (L.active) {
+#pragma unroll 2
+        for (int t = 1; t < S.ne; ++t) {
+            int lj;
+            const int j = partner(S, L.e, t, &lj);
+            const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
+            const Sep s = separation(d0, d1, d2);
+            const double a = (j < S.n_up) == (L.e < S.n_up) ? S.a_par : S.a_anti;
+            const Pade p = pade(S.b, s.r);
+            const double hw = (h[0] * d0 + h[1] * d1 + h[2] * d2) * s.ri;
+            dl -= 0.5 * a * p.g * p.g;
+            de += radial_energy(-2.0 * a * p.g * p.g1, a * p.q * p.g1 * (6.0 * S.b * p.g - 2.0), s.ri, hw);
+        }
+    }
+    put_direction(G, L, S.LW, w, p_b, dl, de);
+    // ---- e-n parameters and nuclear part --------------------------------------
+    if (S.jas_en) {
+        for (int a = 0; a < S.n_atoms; ++a) {
+            double l3[3] = {0.0, 0.0, 0.0}, e3[3] = {0.0, 0.0, 0.0};
+            double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
+            if (L.active) {
+                const auto *R = const_tab(S.atoms) + 4 * a;
+                const auto *wn = const_tab(S.jas_en) + 3 * a;
+                const double d[3] = {x0 - R[0], x1 - R[1], x2 - R[2]};
+                const Sep s = separation(d[0], d[1], d[2]);
+                const double r = s.r, w0 = wn[0], w1 = wn[1], w2 = wn[2];
+                const Pade p = pade(w2, r);
+                const double u[3] = {d[0] * s.ri, d[1] * s.ri, d[2] * s.ri};
+                const double hu = h[0] * u[0] + h[1] * u[1] + h[2] * u[2];
+                // K = (w0 r + w1 r^2) q and its derivatives in r
+                const double K = (w0 + w1 * r) * p.g, K1 = (w0 + 2.0 * w1 * r - K * w2) * p.q;
+                const double K2 = (2.0 * w1 - 2.0 * K1 * w2) * p.q, K3 = -3.0 * w2 * K2 * p.q;
+                // dK/dw0 = g, dK/dw1 = r g, dK/dw2 = -K g
+                l3[0] = p.g;
+                e3[0] = radial_energy(p.g1, p.g2, s.ri, hu);
+                l3[1] = r * p.g;
+                e3[1] = radial_energy(p.g + r * p.g1, 2.0 * p.g1 + r * p.g2, s.ri, hu);
+                l3[2] = -K * p.g;
+                e3[2] = radial_energy(-(K1 * p.g + K * p.g1), -(K2 * p.g + 2.0 * K1 * p.g1 + K * p.g2), s.ri, hu);
+                // d/dR_x: K -> -K' u_x; lap -> -(K''' + 2 K''/r - 2 K'/r^2) u_x;
+                // grad -> -(K'' - K'/r) u_x u - (K'/r) e_x
+                const double kr = K1 * s.ri;
+                const double c = 0.5 * (K3 + 2.0 * s.ri * (K2 - kr)) + (K2 - kr) * hu;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    lr[k] = -K1 * u[k];
+                    er[k] = c * u[k] + kr * h[k];
+                }
+            }
+            for (int k = 0; k < 3; ++k) put_direction(G, L, S.LW, w, p_en + 3 * a + k, l3[k], e3[k]);
+            if (need_R)
+                for (int k = 0; k < 3; ++k) {
+                    const double l = walker_sum(lr[k], S.LW), e = walker_sum(er[k], S.LW);
+                    if (L.wvalid && L.lw == 0) {
+                        sAtom[6 * a + k] += l;
+                        sAtom[6 * a + 3 + k] += e;
+                    }
+                }
+        }
+    }
+    // ---- e-e-n parameters and nuclear part --------------------------------------
+    for (int m = 0; m < S.een_n; ++m) {
+        const auto *tm = const_tab(S.jas_een) + 7 * m;
+        const double c = tm[0], a1 = tm[1], b1 = tm[2], a2 = tm[3], b2 = tm[4], a3 = tm[5], b3 = tm[6];
+        const double kc = c * a1 * a2 * a3;
+        // this term with unit coefficients, and the b1, b2, b3 directions
+        double l0 = 0.0, e0 = 0.0, lb1 = 0.0, eb1 = 0.0, lb2 = 0.0, eb2 = 0.0, lb3 = 0.0, eb3 = 0.0;
+        for (int a = 0; a < S.n_atoms; ++a) {
+            double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
+            if (L.active) {
+                const double *g = sG + (L.lw * S.n_atoms + a) * kEenGeo;
+                const double u = g[0], ui = g[4], tv[3] = {g[1], g[2], g[3]};
+                const double ht = h[0] * tv[0] + h[1] * tv[1] + h[2] * tv[2];
+                // own factor's functional in each role (0: electron i, factor 1)
+                const Pade q[2] = {pade(b1, u), pade(b2, u)};
+                double al[2], be[2][3], ga[2];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    al[r] = radial_energy(q[r].g1, q[r].g2, ui, ht);
+                    ga[r] = -0.5 * q[r].g;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) be[r][k] = -(q[r].g1 * tv[k] + q[r].g * h[k]);
+                }
+                // sums over the partners by role; pl, pe the partner's b
+                double A[2] = {0.0, 0.0}, B[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, D[2] = {0.0, 0.0};
+                double pl = 0.0, pe[2] = {0.0, 0.0};
+                for (int t = 1; t < S.ne; ++t) {
+                    int lj;
+                    const int j = partner(S, L.e, t, &lj);
+                    const bool first = L.e > j;
+                    const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
+                    const Sep s = separation(d0, d1, d2);
+                    const Pade p3 = pade(b3, s.r);
+                    const double w0 = d0 * s.ri, w1 = d1 * s.ri, w2 = d2 * s.ri;
+                    const double lap = p3.g2 + 2.0 * p3.g1 * s.ri;
+                    // partner's factor p, p' = (p / r_aj)^2, dp/db = -p^2
+                    const double *gj = sG + (lj * S.n_atoms + a) * kEenGeo;
+                    const double p = sF[((lj * S.n_atoms + a) * S.een_n + m) * 2 + (first ? 1 : 0)];
+                    const double pq = p * gj[4], pd = pq * pq;
+                    const double o = first ? q[0].g : q[1].g;
+                    const double bw = (first ? be[0][0] : be[1][0]) * w0 + (first ? be[0][1] : be[1][1]) * w1 +
+                                      (first ? be[0][2] : be[1][2]) * w2;
+                    const double alr = first ? al[0] : al[1], gar = first ? ga[0] : ga[1];
+                    // functional of o s, and of o ds/db3 (ds = -s^2, ds' = -2 s s',
+                    // ds'' = q^3 (6 b s - 2))
+                    const double es = alr * p3.g + bw * p3.g1 + gar * lap;
+                    const double s3 = -p3.g * p3.g, s31 = -2.0 * p3.g * p3.g1;
+                    const double s32 = p3.q * p3.g1 * (6.0 * b3 * p3.g - 2.0);
+                    eb3 += p * (alr * s3 + bw * s31 + gar * (s32 + 2.0 * s31 * s.ri));
+                    const double op = first ? o * p : 0.0;  // the pair's value is counted at i
+                    lb3 += op * s3;
+                    const double jv = first ? o * p3.g : 0.0;
+                    pl -= p * p * jv;
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const double pr = first == (r == 0) ? p : 0.0;
+                        A[r] += pr * p3.g;
+                        B[r][0] += pr * p3.g1 * w0;
+                        B[r][1] += pr * p3.g1 * w1;
+                        B[r][2] += pr * p3.g1 * w2;
+                        D[r] += pr * lap;
+                        pe[r] -= pr * p * es;
+                    }
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const double dp = -pd * gj[1 + k];
+                        lr[k] += dp * jv;
+                        er[k] += dp * es;
+                    }
+                }
+                // role 0's partners hold factor 2, role 1's factor 1
+                lb2 += pl;
+                eb2 += pe[0];
+                eb1 += pe[1];
+                l0 += q[0].g * A[0];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const double bB = be[r][0] * B[r][0] + be[r][1] * B[r][1] + be[r][2] * B[r][2];
+                    e0 += al[r] * A[r] + bB + ga[r] * D[r];
+                    // own b: o -> do = -g^2, do' = -2 g g', do'' = q^3 (6 b g - 2)
+                    const double bo = r == 0 ? b1 : b2;
+                    const double og = -q[r].g * q[r].g, og1 = -2.0 * q[r].g * q[r].g1;
+                    const double og2 = q[r].q * q[r].g1 * (6.0 * bo * q[r].g - 2.0);
+                    const double hB = h[0] * B[r][0] + h[1] * B[r][1] + h[2] * B[r][2];
+                    const double tB = tv[0] * B[r][0] + tv[1] * B[r][1] + tv[2] * B[r][2];
+                    const double eo = radial_energy(og1, og2, ui, ht) * A[r] - (og1 * tB + og * hB) - 0.5 * og * D[r];
+                    if (r == 0) {
+                        lb1 += og * A[0];
+                        eb1 += eo;
+                    } else {
+                        eb2 += eo;
+                    }
+                    // own factor's nuclear derivative: du = -t_x, dt = -(e_x - t_x t) / u
+                    const double o1 = q[r].g1, o2 = q[r].g2;
+                    const double o3 = 6.0 * bo * bo * q[r].q * q[r].q * o1;
+                    const double o1u = o1 * ui, c2 = o2 - o1u;
+                    const double ct = (0.5 * (o3 + 2.0 * ui * c2) + c2 * ht) * A[r] + c2 * tB + o1 * hB +
+                                      0.5 * o1 * D[r];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        if (r == 0) lr[k] -= o1 * tv[k] * A[r];
+                        er[k] += ct * tv[k] + o1u * (A[r] * h[k] + B[r][k]);
+                    }
+                }
+            }
+            if (need_R)
+                for (int k = 0; k < 3; ++k) {
+                    const double l = walker_sum(kc * lr[k], S.LW), e = walker_sum(kc * er[k], S.LW);
+                    if (L.wvalid && L.lw == 0) {
+                        sAtom[6 * a + k] += l;
+                        sAtom[6 * a + 3 + k] += e;
+                    }
+                }
+        }
+        const int out = p_een + 7 * m;
+        put_direction(G, L, S.LW, w, out + 0, a1 * a2 * a3 * l0, a1 * a2 * a3 * e0);
+        put_direction(G, L, S.LW, w, out + 1, c * a2 * a3 * l0, c * a2 * a3 * e0);
+        put_direction(G, L, S.LW, w, out + 2, kc * lb1, kc * eb1);
+        put_direction(G, L, S.LW, w, out + 3, c * a1 * a3 * l0, c * a1 * a3 * e0);
+        put_direction(G, L, S.LW, w, out + 4, kc * lb2, kc * eb2);
+        put_direction(G, L, S.LW, w, out + 5, c * a1 * a2 * l0, c * a1 * a2 * e0);
+        put_direction(G, L, S.LW, w, out + 6, kc * lb3, kc * eb3);
+    }
 }
 
 // RT: arithmetic of the forward evaluation's AO values and MO value
@@ -488,57 +714,18 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
     }
 
     // ---- Jastrow parameters and the Jastrow part of the nuclear gradients ---
-    // Forward mode over the Jastrow stage: each direction seeds one Jastrow
-    // parameter (Pade b, e-n (w0, w1, w2) per nucleus, e-e-n (c, a1, b1, a2,
-    // b2, a3, b3) per term) or, when the Jastrow depends on the nuclei, one
-    // nuclear coordinate.  d log|Psi| = d J and
-    // d E_L = -1/2 sum_e (d lap_e J + 2 grad_e J . d grad_e J + 2 d grad_e J . grad_e Sigma / Sigma).
     __syncthreads();  // the per-electron rows are no longer read
     {
         double *sP = wsm;                                   // [LW][3]
-        Dual *dF = (Dual *)(wsm + 3 * S.LW);                // [LW][n_atoms][2 een_n]
-        Dual *dG = dF + S.LW * S.n_atoms * 2 * S.een_n;     // [LW][n_atoms][kEenGeo]
+        double *sF = wsm + 3 * S.LW;                        // [LW][n_atoms][2 een_n]
+        double *sG = sF + S.LW * S.n_atoms * 2 * S.een_n;   // [LW][n_atoms][kEenGeo]
         sP[3 * L.lw + 0] = x0;
         sP[3 * L.lw + 1] = x1;
         sP[3 * L.lw + 2] = x2;
-        const int n_en = S.jas_en ? 3 * S.n_atoms : 0, n_een = 7 * S.een_n;
-        const bool jas_R = (S.jas_en || S.een_n > 0) && (G.dlogpsi_dR || G.deloc_dR);
-        const int n_dir = 1 + n_en + n_een + (jas_R ? 3 * S.n_atoms : 0);
-        const int p_b = S.n_prim + S.n_ao * S.n_mo;        // output index of b
-        for (int dir = 0; dir < n_dir; ++dir) {
-            int kind, i, k, out;
-            if (dir == 0) {
-                kind = 0, i = 0, k = 0, out = p_b;
-            } else if (dir <= n_en) {
-                kind = 1, i = (dir - 1) / 3, k = (dir - 1) % 3, out = p_b + dir;
-            } else if (dir <= n_en + n_een) {
-                kind = 2, i = (dir - 1 - n_en) / 7, k = (dir - 1 - n_en) % 7, out = p_b + dir;
-            } else {
-                kind = 3, i = (dir - 1 - n_en - n_een) / 3, k = (dir - 1 - n_en - n_een) % 3, out = -1;
-            }
-            const SeedPrm sp{S, kind, i, k};
-            een_table_fill<Dual>(S, L, x0, x1, x2, dF, dG, sp);
-            __syncthreads();
-            const JasTerms<Dual> jd = jastrow_terms<Dual>(S, L, x0, x1, x2, sP, dF, dG, sp);
-            double dl = 0.0, de = 0.0;
-            if (L.active) {
-                dl = jd.J.d;
-                de = -0.5 * (jd.lap.d + 2.0 * (gJ[0] * jd.g0.d + gJ[1] * jd.g1.d + gJ[2] * jd.g2.d) +
-                             2.0 * (jd.g0.d * gS[0] + jd.g1.d * gS[1] + jd.g2.d * gS[2]));
-            }
-            dl = walker_sum(dl, S.LW);
-            de = walker_sum(de, S.LW);
-            if (L.wvalid && L.lw == 0) {
-                if (out >= 0) {
-                    if (G.dlogpsi) G.dlogpsi[w * G.n_param + out] = dl;
-                    if (G.deloc_dth) G.deloc_dth[w * G.n_param + out] = de;
-                } else {
-                    sAtom[6 * i + k] += dl;
-                    sAtom[6 * i + 3 + k] += de;
-                }
-            }
-            __syncthreads();  // the tables are rewritten by the next direction
-        }
+        een_table_fill<true>(S, L, x0, x1, x2, sF, sG);
+        __syncthreads();
+        const double h[3] = {gJ[0] + gS[0], gJ[1] + gS[1], gJ[2] + gS[2]};
+        jastrow_derivs(S, L, w, x0, x1, x2, h, sP, sF, sG, G, sAtom);
     }
     if (L.wvalid && L.lw == 0) {
         // nuclear gradients, with the n-n repulsion

@@ -447,7 +447,7 @@ namespace walker {
 constexpr int kEenGeo = 5;
 
 __host__ __device__ inline int een_table(const DevSystem &S) {
-    return S.een_n > 0 ? S.LW * S.n_atoms * (2 * S.een_n + kEenGeo) : 0;
+    return S.LW * S.n_atoms * 2 * S.een_n;
 }
 
 template <int NMO, bool FULL = true>
@@ -481,206 +481,198 @@ __host__ __device__ inline int walker_lds(const DevSystem &S) {
     return ((tc > pp ? tc : pp) + 1) & ~1;  // 16-byte aligned rows
 }
 
-// ---- Jastrow stage, generic in its scalar type ------------------------------
-// The evaluation runs it on doubles; the adjoint runs it on Dual numbers
-// (value and one directional derivative) to differentiate J, grad_e J and
-// lap_e J with respect to a Jastrow parameter or a nuclear coordinate
-// (forward mode).  Parameters come through an accessor: PlainPrm returns
-// the system's values, SeedPrm the same values as Duals with derivative 1 on
-// one chosen entry.
-struct Dual {
-    double v, d;
-    __device__ Dual() : v(0.0), d(0.0) {}
-    __device__ explicit Dual(double x) : v(x), d(0.0) {}
-    __device__ Dual(double x, double dx) : v(x), d(dx) {}
-};
-__device__ __forceinline__ Dual operator+(Dual a, Dual b) { return Dual(a.v + b.v, a.d + b.d); }
-__device__ __forceinline__ Dual operator-(Dual a, Dual b) { return Dual(a.v - b.v, a.d - b.d); }
-__device__ __forceinline__ Dual operator-(Dual a) { return Dual(-a.v, -a.d); }
-__device__ __forceinline__ Dual operator*(Dual a, Dual b) { return Dual(a.v * b.v, a.d * b.v + a.v * b.d); }
-__device__ __forceinline__ Dual operator/(Dual a, Dual b) {
-    const double q = a.v / b.v;
-    return Dual(q, (a.d - q * b.d) / b.v);
-}
-__device__ __forceinline__ Dual operator+(Dual a, double b) { return Dual(a.v + b, a.d); }
-__device__ __forceinline__ Dual operator+(double a, Dual b) { return Dual(a + b.v, b.d); }
-__device__ __forceinline__ Dual operator-(Dual a, double b) { return Dual(a.v - b, a.d); }
-__device__ __forceinline__ Dual operator-(double a, Dual b) { return Dual(a - b.v, -b.d); }
-__device__ __forceinline__ Dual operator*(Dual a, double b) { return Dual(a.v * b, a.d * b); }
-__device__ __forceinline__ Dual operator*(double a, Dual b) { return Dual(a * b.v, a * b.d); }
-__device__ __forceinline__ Dual operator/(double a, Dual b) {
-    const double q = a / b.v;
-    return Dual(q, -q * b.d / b.v);
-}
-__device__ __forceinline__ Dual &operator+=(Dual &a, Dual b) { return a = a + b; }
-__device__ __forceinline__ Dual &operator-=(Dual &a, Dual b) { return a = a - b; }
-using ::sqrt;  // the overload below must not hide the double one
-__device__ __forceinline__ Dual sqrt(Dual a) {
-    const double r = ::sqrt(a.v);
-    return Dual(r, 0.5 * a.d / r);
-}
-__device__ __forceinline__ Dual rcp_ge1(Dual x) {
-    const double y = rcp_ge1(x.v);
-    return Dual(y, -x.d * y * y);
-}
-__device__ __forceinline__ double value_of(double x) { return x; }
-__device__ __forceinline__ double value_of(Dual x) { return x.v; }
-
-struct PlainPrm {
-    const DevSystem &S;
-    // which terms to evaluate (all of them)
-    __device__ bool use_pade() const { return true; }
-    __device__ bool use_en(int) const { return true; }
-    __device__ bool use_een_term(int) const { return true; }
-    __device__ bool use_een(int, int) const { return true; }  // term m, nucleus a
-    __device__ double b() const { return S.b; }
-    __device__ double R(int a, int k) const { return const_tab(S.atoms)[4 * a + k]; }
-    __device__ double en(int a, int k) const { return const_tab(S.jas_en)[3 * a + k]; }
-    __device__ double een(int m, int k) const { return const_tab(S.jas_een)[7 * m + k]; }
+// ---- Jastrow stage -----------------------------------------------------------
+// Separation of two points: r, 1 / r.  The hardware reciprocal root with one
+// third-order step, and r corrected by its residual: the root within half an
+// ulp or so, its reciprocal within an ulp, without the scaling and division
+// of the full-range functions.
+struct Sep {
+    double r, ri;
 };
 
-// Seeded entry: kind 0 the Pade b, 1 the e-n parameter (i, k), 2 the e-e-n
-// parameter (i, k), 3 the coordinate k of nucleus i; -1 none.
-struct SeedPrm {
-    const DevSystem &S;
-    int kind, i, k;
-    // only the terms that depend on the seeded entry (the others have zero
-    // derivative)
-    __device__ bool use_pade() const { return kind == 0; }
-    __device__ bool use_en(int a) const { return (kind == 1 || kind == 3) && a == i; }
-    __device__ bool use_een_term(int m) const { return (kind == 2 && m == i) || kind == 3; }
-    __device__ bool use_een(int m, int a) const { return (kind == 2 && m == i) || (kind == 3 && a == i); }
-    __device__ Dual b() const { return Dual(S.b, kind == 0 ? 1.0 : 0.0); }
-    __device__ Dual R(int a, int kk) const { return Dual(S.atoms[4 * a + kk], (kind == 3 && a == i && kk == k) ? 1.0 : 0.0); }
-    __device__ Dual en(int a, int kk) const { return Dual(S.jas_en[3 * a + kk], (kind == 1 && a == i && kk == k) ? 1.0 : 0.0); }
-    __device__ Dual een(int m, int kk) const { return Dual(S.jas_een[7 * m + kk], (kind == 2 && m == i && kk == k) ? 1.0 : 0.0); }
+__device__ __forceinline__ Sep separation(double d0, double d1, double d2) {
+    const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+    double y = __builtin_amdgcn_rsq(r2);
+    const double e = __builtin_fma(-(r2 * y), y, 1.0);
+    y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+    const double r = r2 * y;
+    return {__builtin_fma(__builtin_fma(-r, r, r2), 0.5 * y, r), y};
+}
+
+// Partner t = 1 .. N_e - 1 of electron e, cyclic, and its lane in the walker:
+// every lane has N_e - 1 partners, none of them itself, so the pair loops
+// have no idle trip.
+__device__ __forceinline__ int partner(const DevSystem &S, int e, int t, int *lane) {
+    int j = e + t;
+    if (j >= S.ne) j -= S.ne;
+    *lane = j < S.n_up ? j : S.G + (j - S.n_up);
+    return j;
+}
+
+// g(r) = r / (1 + b r), the radial form of every Pade-type factor, with
+// q = 1 / (1 + b r): g = r q, g' = q^2, g'' = -2 b q^3.
+struct Pade {
+    double q, g, g1, g2;
 };
 
-// The lane's e-e-n factor table: per nucleus a, [een_n][2] factor values
-// f(a1, b1; u) and f(a2, b2; u) of its electron at u = r_a e, then [kEenGeo] the
-// geometry (u, the unit vector from the nucleus, 1 / u).  T values, LDS.
-template <typename T, typename Prm>
+__device__ __forceinline__ Pade pade(double b, double r) {
+    const double q = rcp_ge1(1.0 + b * r), q2 = q * q;
+    return {q, r * q, q2, -2.0 * b * q2 * q};
+}
+
+// What the partners of the lane's electron read in the e-e-n terms: per
+// nucleus a and term the factors g(b1; r_a), g(b2; r_a) (sF, [een_n][2]); with
+// GEO (the adjoint) also its geometry (r_a, the unit vector from the nucleus,
+// 1 / r_a: sG, [kEenGeo]).
+template <bool GEO>
 __device__ __forceinline__ void een_table_fill(const DevSystem &S, const Lane &L, double x0, double x1, double x2,
-                                               T *sF, T *sG, const Prm &prm) {
+                                               double *sF, double *sG) {
     if (S.een_n == 0 || !L.active) return;
     for (int a = 0; a < S.n_atoms; ++a) {
-        const T e0 = x0 - prm.R(a, 0), e1 = x1 - prm.R(a, 1), e2 = x2 - prm.R(a, 2);
-        const T u = sqrt(e0 * e0 + e1 * e1 + e2 * e2);
-        const T ui = 1.0 / u;
-        T *g = sG + (L.lw * S.n_atoms + a) * kEenGeo;
-        g[0] = u;
-        g[1] = e0 * ui;
-        g[2] = e1 * ui;
-        g[3] = e2 * ui;
-        g[4] = ui;
-        T *f = sF + (L.lw * S.n_atoms + a) * 2 * S.een_n;
+        const auto *R = const_tab(S.atoms) + 4 * a;
+        const double e0 = x0 - R[0], e1 = x1 - R[1], e2 = x2 - R[2];
+        const Sep s = separation(e0, e1, e2);
+        if constexpr (GEO) {
+            double *g = sG + (L.lw * S.n_atoms + a) * kEenGeo;
+            g[0] = s.r;
+            g[1] = e0 * s.ri;
+            g[2] = e1 * s.ri;
+            g[3] = e2 * s.ri;
+            g[4] = s.ri;
+        }
+        double *f = sF + (L.lw * S.n_atoms + a) * 2 * S.een_n;
         for (int m = 0; m < S.een_n; ++m) {
-            f[2 * m] = prm.een(m, 1) * u * rcp_ge1(1.0 + prm.een(m, 2) * u);
-            f[2 * m + 1] = prm.een(m, 3) * u * rcp_ge1(1.0 + prm.een(m, 4) * u);
+            const auto *t = const_tab(S.jas_een) + 7 * m;
+            f[2 * m] = s.r * rcp_ge1(1.0 + t[2] * s.r);
+            f[2 * m + 1] = s.r * rcp_ge1(1.0 + t[4] * s.r);
         }
     }
 }
 
-template <typename T>
 struct JasTerms {
-    T J, g0, g1, g2, lap;
-    double vpot;  // Coulomb terms of the electron (evaluated when T is double)
+    double J, g0, g1, g2, lap;
+    double vpot;  // Coulomb terms of the electron
 };
 
 // Jastrow factor (eq. jastrow: Pade e-e kernel of eq. pade_kernel, e-n and
 // e-e-n kernels of the many-body appendix) of the lane's electron: its share
-// of J, grad_e J and lap_e J; with T = double also its Coulomb terms
-// (eq. Hmol: half of each e-e pair, the e-n attraction).  sPos holds the
-// walker's positions, sF / sG the e-e-n tables of een_table_fill.  A seeded
-// accessor skips the terms that do not depend on its entry.
-template <typename T, typename Prm>
-__device__ __forceinline__ JasTerms<T> jastrow_terms(const DevSystem &S, const Lane &L, double x0, double x1,
-                                                     double x2, const double *sPos, const T *sF, const T *sG,
-                                                     const Prm &prm) {
-    constexpr bool kPlain = sizeof(T) == sizeof(double);
-    JasTerms<T> o;
-    o.J = T(0.0);
-    o.g0 = T(0.0);
-    o.g1 = T(0.0);
-    o.g2 = T(0.0);
-    o.lap = T(0.0);
-    o.vpot = 0.0;
+// of J, grad_e J and lap_e J, and its Coulomb terms (eq. Hmol: half of each
+// e-e pair, the e-n attraction).  sPos holds the walker's positions, sF the
+// e-e-n factors of een_table_fill.
+__device__ __forceinline__ JasTerms jastrow_terms(const DevSystem &S, const Lane &L, double x0, double x1, double x2,
+                                                  const double *sPos, const double *sF) {
+    JasTerms o = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!L.active) return o;
-    const T b = prm.b();
-    for (int j = 0; j < S.ne && prm.use_pade(); ++j) {
-        if (j == L.e) continue;
-        const int lj = j < S.n_up ? j : S.G + (j - S.n_up);
+    const bool up = L.e < S.n_up;
+#pragma unroll 2
+    for (int t = 1; t < S.ne; ++t) {
+        int lj;
+        const int j = partner(S, L.e, t, &lj);
         const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
-        const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-        const bool same = (j < S.n_up) == (L.e < S.n_up);
-        const double a = same ? S.a_par : S.a_anti;
-        // one division gives both 1/r and 1/(1 + b r)
-        const T den = 1.0 + b * r;
-        const T q = 1.0 / (r * den);
-        const T rinv = q * den, dinv = q * r;
-        const T k1 = a * dinv * dinv;                 // K'(r)
-        const T k2 = -2.0 * a * b * dinv * dinv * dinv;  // K''(r)
-        o.J += 0.5 * a * r * dinv;
-        o.g0 += k1 * d0 * rinv;
-        o.g1 += k1 * d1 * rinv;
-        o.g2 += k1 * d2 * rinv;
-        o.lap += k2 + 2.0 * k1 * rinv;
-        if constexpr (kPlain) o.vpot += 0.5 * rinv;
+        const Sep s = separation(d0, d1, d2);
+        const double a = (j < S.n_up) == up ? S.a_par : S.a_anti;
+        const Pade p = pade(S.b, s.r);
+        const double k1 = a * p.g1, kr = k1 * s.ri;
+        o.J += 0.5 * a * p.g;
+        o.g0 += kr * d0;
+        o.g1 += kr * d1;
+        o.g2 += kr * d2;
+        o.lap += a * p.g2 + 2.0 * kr;
+        o.vpot += 0.5 * s.ri;
     }
     for (int a = 0; a < S.n_atoms; ++a) {
-        const T d0 = x0 - prm.R(a, 0), d1 = x1 - prm.R(a, 1), d2 = x2 - prm.R(a, 2);
-        if constexpr (kPlain) o.vpot -= const_tab(S.atoms)[4 * a + 3] / sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-        if (S.jas_en && prm.use_en(a)) {
+        const auto *R = const_tab(S.atoms) + 4 * a;
+        const double d0 = x0 - R[0], d1 = x1 - R[1], d2 = x2 - R[2];
+        const Sep s = separation(d0, d1, d2);
+        o.vpot -= R[3] * s.ri;
+        if (S.jas_en) {
             // e-n kernel K = N / D, N = w0 r + w1 r^2, D = 1 + w2 r:
             // K' = (N' - K D') / D and K'' = (N'' - 2 K' D') / D
-            const T r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-            const T w0 = prm.en(a, 0), w1 = prm.en(a, 1), w2 = prm.en(a, 2);
-            const T q = 1.0 / (1.0 + w2 * r), rinv = 1.0 / r;
-            const T K = (w0 + w1 * r) * r * q;
-            const T K1 = (w0 + 2.0 * w1 * r - K * w2) * q;
-            const T K2 = (2.0 * w1 - 2.0 * K1 * w2) * q;
+            const auto *w = const_tab(S.jas_en) + 3 * a;
+            const double q = rcp_ge1(1.0 + w[2] * s.r);
+            const double K = (w[0] + w[1] * s.r) * s.r * q;
+            const double K1 = (w[0] + 2.0 * w[1] * s.r - K * w[2]) * q;
+            const double K2 = (2.0 * w[1] - 2.0 * K1 * w[2]) * q;
+            const double kr = K1 * s.ri;
             o.J += K;
-            o.g0 += K1 * d0 * rinv;
-            o.g1 += K1 * d1 * rinv;
-            o.g2 += K1 * d2 * rinv;
-            o.lap += K2 + 2.0 * K1 * rinv;
+            o.g0 += kr * d0;
+            o.g1 += kr * d1;
+            o.g2 += kr * d2;
+            o.lap += K2 + 2.0 * kr;
         }
     }
     // e-e-n kernel: for the ordered pair (i, j), i > j, the term is
-    // c f1(r_ai) f2(r_aj) f3(r_ij).  This electron takes the role of i
-    // against lower-numbered partners and of j against higher ones; its
-    // own factor carries the derivatives, the partner's factor is a value
-    // from the table.  The pair's value is counted at i.
-    for (int j = 0; j < S.ne && S.een_n > 0; ++j) {
-        if (j == L.e) continue;
-        const int lj = j < S.n_up ? j : S.G + (j - S.n_up);
-        const bool first = L.e > j;
-        const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
-        const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-        const double rinv = 1.0 / r;
-        const double w0 = d0 * rinv, w1 = d1 * rinv, w2 = d2 * rinv;
-        for (int m = 0; m < S.een_n; ++m) {
-            if (!prm.use_een_term(m)) continue;
-            const T a3 = prm.een(m, 5), b3 = prm.een(m, 6);
-            const T q3 = rcp_ge1(1.0 + b3 * r);
-            const T f3 = a3 * r * q3, f31 = a3 * q3 * q3, f32 = -2.0 * b3 * f31 * q3;
-            const T ao = first ? prm.een(m, 1) : prm.een(m, 3), bo = first ? prm.een(m, 2) : prm.een(m, 4);
-            const T cm = prm.een(m, 0);
-            for (int a = 0; a < S.n_atoms; ++a) {
-                if (!prm.use_een(m, a)) continue;
-                const T *g = sG + (L.lw * S.n_atoms + a) * kEenGeo;
-                const T u = g[0];
-                const T qo = rcp_ge1(1.0 + bo * u);
-                const T fo = ao * u * qo, fo1 = ao * qo * qo, fo2 = -2.0 * bo * fo1 * qo;
-                const T cp = cm * sF[((lj * S.n_atoms + a) * S.een_n + m) * 2 + (first ? 1 : 0)];
-                const T uw = g[1] * w0 + g[2] * w1 + g[3] * w2;
-                if (first) o.J += cp * fo * f3;
-                o.g0 += cp * (fo1 * f3 * g[1] + fo * f31 * w0);
-                o.g1 += cp * (fo1 * f3 * g[2] + fo * f31 * w1);
-                o.g2 += cp * (fo1 * f3 * g[3] + fo * f31 * w2);
-                o.lap += cp * ((fo2 + 2.0 * fo1 * g[4]) * f3 + 2.0 * fo1 * f31 * uw + fo * (f32 + 2.0 * f31 * rinv));
+    // c f1(r_ai) f2(r_aj) f3(r_ij), f_k = a_k g(b_k).  This electron takes
+    // the role of i against lower-numbered partners and of j against higher
+    // ones; its own factor carries the derivatives, the partner's is a value
+    // from the table.  Per term, nucleus and role the partners enter through
+    // five sums only,
+    //   A = sum p s,  B = sum p s' w,  D = sum p (s'' + 2 s' / r)
+    // (p the partner's factor, s = g(b3; r_ij), w the unit vector from the
+    // partner), so the own factor's derivatives are formed once per role, not
+    // once per partner.  A term symmetric in its electrons (f1 = f2, the
+    // physical choice) has one role, in which every pair's value is met twice.
+    // (CO, 5 symmetric terms: with a factor pair per partner this stage took
+    // 75 k cycles of one wave, half of the step.)
+    for (int m = 0; m < S.een_n; ++m) {
+        const auto *tm = const_tab(S.jas_een) + 7 * m;
+        const double b3 = tm[6], kc = tm[0] * tm[1] * tm[3] * tm[5];
+        auto term = [&](auto roles) {
+            constexpr int NR = decltype(roles)::value;
+            for (int a0 = 0; a0 < S.n_atoms; a0 += 2) {  // two nuclei share a pair's s
+                const int na = a0 + 1 < S.n_atoms ? 2 : 1;
+                double A[2][NR], B[2][NR][3], D[2][NR];  // [nucleus][role]
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) A[n][r] = B[n][r][0] = B[n][r][1] = B[n][r][2] = D[n][r] = 0.0;
+#pragma unroll 2
+                for (int t = 1; t < S.ne; ++t) {
+                    int lj;
+                    const int j = partner(S, L.e, t, &lj);
+                    const bool first = L.e > j;
+                    const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
+                    const Sep s = separation(d0, d1, d2);
+                    const Pade p = pade(b3, s.r);
+                    const double sr = p.g1 * s.ri, sd = p.g2 + 2.0 * sr;
+                    const double *f = sF + ((lj * S.n_atoms + a0) * S.een_n + m) * 2 + (first ? 1 : 0);
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) {
+                        const double pv = f[n < na ? n * 2 * S.een_n : 0];
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) {
+                            const double pr = NR == 1 || first == (r == 0) ? pv : 0.0;
+                            const double ps = pr * sr;
+                            A[n][r] += pr * p.g;
+                            B[n][r][0] += ps * d0;
+                            B[n][r][1] += ps * d1;
+                            B[n][r][2] += ps * d2;
+                            D[n][r] += pr * sd;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int n = 0; n < 2; ++n) {
+                    if (n >= na) break;
+                    const auto *R = const_tab(S.atoms) + 4 * (a0 + n);
+                    const double d0 = x0 - R[0], d1 = x1 - R[1], d2 = x2 - R[2];
+                    const Sep u = separation(d0, d1, d2);
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        const Pade q = pade(r == 0 ? tm[2] : tm[4], u.r);
+                        const double k0 = kc * q.g, k1 = kc * q.g1, k2 = kc * q.g2, kr = k1 * u.ri;
+                        const double dB = d0 * B[n][r][0] + d1 * B[n][r][1] + d2 * B[n][r][2];
+                        if (r == 0) o.J += (NR == 1 ? 0.5 : 1.0) * k0 * A[n][r];
+                        o.g0 += kr * A[n][r] * d0 + k0 * B[n][r][0];
+                        o.g1 += kr * A[n][r] * d1 + k0 * B[n][r][1];
+                        o.g2 += kr * A[n][r] * d2 + k0 * B[n][r][2];
+                        o.lap += (k2 + 2.0 * kr) * A[n][r] + 2.0 * kr * dB + k0 * D[n][r];
+                    }
+                }
             }
-        }
+        };
+        if (tm[1] == tm[3] && tm[2] == tm[4]) term(std::integral_constant<int, 1>());
+        else term(std::integral_constant<int, 2>());
     }
     return o;
 }
@@ -737,10 +729,8 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     double *sPos = wsm + (BF ? bf_pos_offset<NMO, !EXPL>(S) : pos_offset<NMO, kFull>(S));
     double *sPiv = sPos + 3 * S.LW;          // [2][NMO] during it
     // e-e-n table before the elimination: per lane [n_atoms][een_n][2]
-    // factor values (f1, f2) of its electron, then [n_atoms][kEenGeo] geometry
-    // (r, unit vector from the nucleus)
+    // factor values (f1, f2) of its electron
     double *sF = wsm;
-    double *sG = wsm + S.LW * S.n_atoms * 2 * S.een_n;
     double *Tg = sT + L.grp * tstride;
     double *Cg = sC + L.grp * cstride;
     double *piv_row = sPiv + L.grp * NMO;
@@ -753,12 +743,11 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     sPos[3 * L.lw + 0] = x0;
     sPos[3 * L.lw + 1] = x1;
     sPos[3 * L.lw + 2] = x2;
-    const PlainPrm prm{S};
-    een_table_fill<double>(S, L, x0, x1, x2, sF, sG, prm);
+    een_table_fill<false>(S, L, x0, x1, x2, sF, nullptr);
     wave_sync();
 
     // ---- Jastrow and Coulomb terms of this electron (FP64) ----------------
-    const JasTerms<double> jt = jastrow_terms<double>(S, L, x0, x1, x2, sPos, sF, sG, prm);
+    const JasTerms jt = jastrow_terms(S, L, x0, x1, x2, sPos, sF);
     const double J = jt.J, gJ0 = jt.g0, gJ1 = jt.g1, gJ2 = jt.g2, lapJ = jt.lap, vpot = jt.vpot;
 
     c.J = J;
