@@ -219,31 +219,28 @@ float from_bf16(uint16_t h) {
     return f;
 }
 
-// Operand fragments of the matrix-core contractions: matrix 0 = C^T (rows
-// MOs, columns AOs), matrix 1 = C (rows AOs, columns MOs), both padded to
-// 32 x 32; fragment (tile t, lane l) holds M[16 t + l % 16][8 (l / 16) + e],
-// e = 0..7, as high and low BF16 parts.
+// Operand fragments of the BF16 matrix-core contraction with C^T (rows MOs,
+// columns AOs, padded to 32 x 32): fragment (tile t, lane l) holds
+// C[8 (l / 16) + e][16 t + l % 16], e = 0..7, as high and low BF16 parts.
 std::vector<uint4> mfma_fragments(const std::vector<double> &mo, int n_ao, int n_mo, int stride) {
-    std::vector<uint4> tab(2 * 2 * 2 * 64);
-    for (int mat = 0; mat < 2; ++mat)
-        for (int t = 0; t < 2; ++t)
-            for (int part = 0; part < 2; ++part)
-                for (int l = 0; l < 64; ++l) {
-                    uint16_t h[8];
-                    for (int e = 0; e < 8; ++e) {
-                        const int row = 16 * t + l % 16, col = 8 * (l / 16) + e;
-                        const int ao = mat == 0 ? col : row, m = mat == 0 ? row : col;
-                        const double x = (ao < n_ao && m < n_mo) ? mo[(size_t)ao * stride + m] : 0.0;
-                        const uint16_t hi = to_bf16((float)x);
-                        h[e] = part == 0 ? hi : to_bf16((float)(x - (double)from_bf16(hi)));
-                    }
-                    uint4 v;
-                    v.x = h[0] | ((uint32_t)h[1] << 16);
-                    v.y = h[2] | ((uint32_t)h[3] << 16);
-                    v.z = h[4] | ((uint32_t)h[5] << 16);
-                    v.w = h[6] | ((uint32_t)h[7] << 16);
-                    tab[((mat * 2 + t) * 2 + part) * 64 + l] = v;
+    std::vector<uint4> tab(2 * 2 * 64);
+    for (int t = 0; t < 2; ++t)
+        for (int part = 0; part < 2; ++part)
+            for (int l = 0; l < 64; ++l) {
+                uint16_t h[8];
+                for (int e = 0; e < 8; ++e) {
+                    const int m = 16 * t + l % 16, ao = 8 * (l / 16) + e;
+                    const double x = (ao < n_ao && m < n_mo) ? mo[(size_t)ao * stride + m] : 0.0;
+                    const uint16_t hi = to_bf16((float)x);
+                    h[e] = part == 0 ? hi : to_bf16((float)(x - (double)from_bf16(hi)));
                 }
+                uint4 v;
+                v.x = h[0] | ((uint32_t)h[1] << 16);
+                v.y = h[2] | ((uint32_t)h[3] << 16);
+                v.z = h[4] | ((uint32_t)h[5] << 16);
+                v.w = h[6] | ((uint32_t)h[7] << 16);
+                tab[(t * 2 + part) * 64 + l] = v;
+            }
     return tab;
 }
 
@@ -301,7 +298,6 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
         }
 
     // --- canonical excitations, folded signs ----------------------------------
-    std::vector<int> dets;
     std::vector<double> ci;
     std::vector<Excitation> ex_up, ex_dn;
     for (int n = 0; n < d->n_det; ++n) {
@@ -318,14 +314,6 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
         ex_up.push_back(eu);
         ex_dn.push_back(ed);
         ci.push_back(d->ci[n] * su * sd);
-        const Excitation *e2[2] = {&eu, &ed};
-        for (int s = 0; s < 2; ++s) {
-            dets.push_back(e2[s]->rank);
-            dets.push_back(e2[s]->h[0]);
-            dets.push_back(e2[s]->h[1]);
-            dets.push_back(e2[s]->p[0]);
-            dets.push_back(e2[s]->p[1]);
-        }
     }
     const int n_det = (int)ci.size();
 
@@ -462,15 +450,6 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     for (int l = 0; l < LW; ++l)
         for (size_t i = 0; i < lane_lists[l].size(); ++i) cof_recs[i * LW + l] = lane_lists[l][i];
 
-    std::vector<int4> entries, contribs;
-    for (auto &kv : ent) {
-        entries.push_back(make_int4(std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first),
-                                    (int)contribs.size()));
-        for (const int4 &c : kv.second) contribs.push_back(c);
-    }
-    entries.push_back(make_int4(0, 0, 0, (int)contribs.size()));
-    const int n_entries = (int)entries.size() - 1;
-
     // --- basis tables -------------------------------------------------------
     std::vector<int4> shells;
     std::vector<double2> prims;
@@ -524,10 +503,6 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     const size_t o_mo = push_bytes(blob, mo.data(), mo.size());
     const size_t o_moa = push_bytes(blob, mo_a.data(), mo_a.size());
     const size_t o_mofa = push_bytes(blob, mo_fa.data(), mo_fa.size());
-    const size_t o_dets = push_bytes(blob, dets.data(), dets.size());
-    const size_t o_ci = push_bytes(blob, ci.data(), ci.size());
-    const size_t o_ent = push_bytes(blob, entries.data(), entries.size());
-    const size_t o_con = push_bytes(blob, contribs.data(), contribs.size());
     const size_t o_perm = push_bytes(blob, old_of_new.data(), old_of_new.size());
     const size_t o_angf = push_bytes(blob, angf.data(), angf.size());
     const std::vector<uint4> frag = mfma_fragments(mo, n_ao, d->n_mo, nmo_pad);
@@ -577,7 +552,6 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     S.n_ao = n_ao;
     S.n_mo = d->n_mo;
     S.n_det = n_det;
-    S.n_entries = n_entries;
     S.G = G;
     S.LW = 2 * G;
     S.WPW = qmc::kWave / S.LW;
@@ -595,10 +569,6 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     S.mo = (const double *)(base + o_mo);
     S.mo_a = (const double *)(base + o_moa);
     S.mo_fa = (const float *)(base + o_mofa);
-    S.dets = (const int *)(base + o_dets);
-    S.ci = (const double *)(base + o_ci);
-    S.entries = (const int4 *)(base + o_ent);
-    S.contribs = (const int4 *)(base + o_con);
     S.mo_perm = (const int *)(base + o_perm);
     S.ao_angf = (const double *)(base + o_angf);
     S.mfma_tab = (const uint4 *)(base + o_frag);

@@ -11,8 +11,6 @@ namespace qmc {
 // of two >= max(n_up, n_dn) <= 8).
 constexpr int kMaxSpin = 8;
 constexpr int kWave = 64;
-// Ints per determinant record: (rank, h1, h2, p1, p2) for spin up, then down.
-constexpr int kDetInts = 10;
 
 // Streams and events of one walker call: st is the caller's stream; side
 // is a second stream and ev[0..3] events (timing off) owned by the system
@@ -25,7 +23,7 @@ struct CallStreams {
 // Everything a kernel needs about one system; passed by value as a kernel
 // argument.  Pointers refer to one device allocation owned by the handle.
 struct DevSystem {
-    int n_up, n_dn, ne, n_atoms, n_shells, n_ao, n_mo, n_det, n_entries;
+    int n_up, n_dn, ne, n_atoms, n_shells, n_ao, n_mo, n_det;
     int G;    // lanes per spin group (power of two >= max(n_up, n_dn))
     int LW;   // lanes per walker = 2 G
     int WPW;  // walkers per wave = 64 / LW
@@ -43,14 +41,10 @@ struct DevSystem {
     // past the last multiple of 4 are zero.
     const double *mo_a;
     const float *mo_fa;
-    const int *dets;        // [n_det][kDetInts]
-    const double *ci;       // [n_det], canonicalisation signs folded in
-    const int4 *entries;    // [n_entries + 1]: spin, slot k, MO v, first contribution
-    const int4 *contribs;   // [n_contrib]: det, cofactor sign (0 = unit), h', p'
     const int *mo_perm;     // [n_mo]: caller's column of each internal MO column
     const double *ao_angf;  // [n_ao]: angular normalisation folded into the MO rows
-    // BF16 MFMA operand fragments [2 matrices: C^T, C][2 tiles][hi, lo][64 lanes],
-    // 8 bf16 each: lane l of tile t holds M[16 t + l % 16][8 (l / 16) + e].
+    // BF16 MFMA operand fragments of C^T [2 tiles][hi, lo][64 lanes], 8 bf16
+    // each: lane l of tile t holds C[8 (l / 16) + e][16 t + l % 16].
     const uint4 *mfma_tab;
     // Flattened determinant and cofactor work for the walker's LW lanes.
     // det_recs [det_rows][LW]: (CI weight as two words, up code, down code);

@@ -37,84 +37,68 @@ struct GradOut {
     int n_param;
 };
 
-// Extra LDS doubles per walker beyond the evaluation's: three [2][nmax][NMO]
-// tables (Tdot / Ainvdot, Cdot, slot-indexed B0 and Z rows), reused later
-// for the per-electron rows of the MO-coefficient gradient, then positions
-// and the per-atom accumulators.
-// LDS of one walker in the gradient kernel (doubles).  The shared-stage
-// tables (walker_lds, at 0) are followed by the forward-mode tables
-// [3][2][n_max][NMO]; the Jastrow b-derivatives' positions [LW][3] come
-// first in that same space (they are read before the shared stages).  Once
-// a_e and its forward-mode derivative are in registers, all of it is dead
-// and the per-electron rows [LW][2 n_ao + 2 NMO] (chi, beta, a, adot) take
-// the block from 0.  The per-nucleus results [n_atoms][6] live past the end
-// of both.
-// After the MO-coefficient gradient the same block holds the walker's
-// positions [LW][3] and the e-e-n tables of the Jastrow directions:
-// [LW][n_atoms][2 een_n] factors, [LW][n_atoms][kEenGeo] geometry.
-__host__ __device__ inline int grad_jastrow_size(const DevSystem &S) {
-    return 3 * S.LW + S.LW * S.n_atoms * (2 * S.een_n + kEenGeo);
-}
-
+// LDS of the gradient kernel (doubles).  Per walker, from its base: the
+// shared stages' tables (walker_lds, full layout), then the forward-mode
+// tables [2][2][n_max][NMO]: Tdot / Ainvdot, and the slot-indexed rows
+// (B0 | Z) that Cdot replaces.  Once a_e and its derivative are in registers
+// all of it is dead and the wave's rows take the block from its start:
+// a [NMO][64], adot [NMO][64], and the two rings [kRing][64] of the main pass;
+// after them each walker's positions [LW][3] and e-e-n tables of the Jastrow
+// directions, [LW][n_atoms][2 een_n] factors and [LW][n_atoms][kEenGeo]
+// geometry.  The per-nucleus results [n_atoms][6] per walker live past the
+// end of all.  (CO: 37 KB, so four waves share a compute unit; with a row of
+// 2 n_ao + 2 NMO doubles per electron for the MO-coefficient products it was
+// 49 KB and three.)
 template <int NMO>
-__host__ __device__ inline int grad_rows_end(const DevSystem &S) {
+__host__ __device__ inline int grad_walker(const DevSystem &S) {
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
-    const int base = walker_lds<NMO>(S);
-    const int fwd = base + 6 * nmax * NMO;
-    const int rows = S.LW * (2 * S.n_ao + 2 * NMO);
-    int e = fwd > rows ? fwd : rows;
-    const int jas = grad_jastrow_size(S);
-    return e > jas ? e : jas;
+    const int fwd = walker_lds<NMO>(S) + 4 * nmax * NMO;
+    const int jas = 3 * S.LW + S.LW * S.n_atoms * (S.een_n > 0 ? 2 * S.een_n + kEenGeo : 0);
+    return ((fwd > jas ? fwd : jas) + 1) & ~1;
 }
 
 template <int NMO>
-__host__ __device__ inline int grad_extra_lds(const DevSystem &S) {
-    return grad_rows_end<NMO>(S) + 6 * S.n_atoms - walker_lds<NMO>(S);
+__host__ __device__ inline int grad_wave(const DevSystem &S) {
+    const int walkers = S.WPW * grad_walker<NMO>(S), rows = (2 * NMO + 2 * kRing) * kWave;
+    return walkers > rows ? walkers : rows;
 }
 
-// Derivative of the k <= 2 minor det T[H,P] along Tdot.
 template <int NMO>
-__device__ __forceinline__ double ratio_dot(const double *T, const double *Td, const int *d) {
-    const int k = d[0];
+__host__ __device__ inline size_t grad_lds(const DevSystem &S) {
+    return (size_t)grad_wave<NMO>(S) + (size_t)S.WPW * 6 * S.n_atoms;
+}
+
+// Derivative of the k <= 2 minor det T[H,P] along Tdot, from a packed
+// excitation code (ratio_code).
+template <int NMO>
+__device__ __forceinline__ double ratio_code_dot(const double *T, const double *Td, uint32_t c) {
+    const uint32_t k = c & 3u;
     if (k == 0) return 0.0;
-    const int a = d[1] * NMO + d[3];
+    const int h1 = (c >> 2) & 7, h2 = (c >> 5) & 7, p1 = (c >> 8) & 31, p2 = (c >> 13) & 31;
+    const int a = h1 * NMO + p1;
     if (k == 1) return Td[a];
-    const int b = d[2] * NMO + d[4], c = d[1] * NMO + d[4], e = d[2] * NMO + d[3];
-    return Td[a] * T[b] + T[a] * Td[b] - Td[c] * T[e] - T[c] * Td[e];
+    const int b = h2 * NMO + p2, d = h1 * NMO + p2, e = h2 * NMO + p1;
+    return Td[a] * T[b] + T[a] * Td[b] - Td[d] * T[e] - T[d] * Td[e];
 }
 
-// Monomial P of Cartesian component c of an l <= 2 shell, its gradient,
-// Laplacian and Hessian (xx, yy, zz, xy, xz, yz).
-struct Mono {
-    double P, g[3], L, h[6];
-};
-
-__device__ __forceinline__ Mono monomial(int l, int c, double dx, double dy, double dz) {
-    Mono m;
-    const double d[3] = {dx, dy, dz};
-    for (int k = 0; k < 3; ++k) m.g[k] = 0.0;
-    for (int k = 0; k < 6; ++k) m.h[k] = 0.0;
-    m.L = 0.0;
+// Components of one shell, in AO order: fn(c, P, P_x, P_y, P_z, lap P) of the
+// monomials P of angular momentum l.
+template <typename Fn>
+__device__ __forceinline__ void shell_monomials(int l, double dx, double dy, double dz, Fn fn) {
     if (l == 0) {
-        m.P = 1.0;
+        fn(0, 1.0, 0.0, 0.0, 0.0, 0.0);
     } else if (l == 1) {
-        m.P = d[c];
-        m.g[c] = 1.0;
+        fn(0, dx, 1.0, 0.0, 0.0, 0.0);
+        fn(1, dy, 0.0, 1.0, 0.0, 0.0);
+        fn(2, dz, 0.0, 0.0, 1.0, 0.0);
     } else {
-        const int iu = (c < 3) ? 0 : (c < 5 ? 1 : 2);
-        const int iv = (c == 0) ? 0 : (c == 1 || c == 3) ? 1 : 2;
-        m.P = d[iu] * d[iv];
-        m.g[iu] += d[iv];
-        m.g[iv] += d[iu];
-        if (iu == iv) {
-            m.L = 2.0;
-            m.h[iu] = 2.0;
-        } else {
-            const int o = (iu + iv == 1) ? 3 : (iu + iv == 2 ? 4 : 5);  // xy, xz, yz
-            m.h[o] = 1.0;
-        }
+        fn(0, dx * dx, 2.0 * dx, 0.0, 0.0, 2.0);
+        fn(1, dx * dy, dy, dx, 0.0, 0.0);
+        fn(2, dx * dz, dz, 0.0, dx, 0.0);
+        fn(3, dy * dy, 0.0, 2.0 * dy, 0.0, 2.0);
+        fn(4, dy * dz, 0.0, dz, dy, 0.0);
+        fn(5, dz * dz, 0.0, 0.0, 2.0 * dz, 2.0);
     }
-    return m;
 }
 
 // Radial sums of one shell: R, R'/r, R'' + (2l+2) R'/r, (R'' - R'/r) / r^2
@@ -123,36 +107,116 @@ struct Radial {
     double v, d, l, dd, l1;
 };
 
-__device__ __forceinline__ Radial radial_full(const DevSystem &S, int p0, int np, int l, int kn, double r,
-                                              double r2) {
-    Radial R = {0, 0, 0, 0, 0};
-    const double rinv = 1.0 / r;
-    for (int q = 0; q < np; ++q) {
-        const double2 pe = S.prims[p0 + q];
-        const double ex = pe.x;
-        if (S.basis == 0) {
-            double f = pe.y * exp(-ex * r);
-            for (int t = 0; t < kn; ++t) f *= r;
-            const double g = kn * rinv - ex;
-            const double L = g * g - kn * rinv * rinv + (2.0 * l + 2.0) * g * rinv;
-            const double Lp = -2.0 * g * kn * rinv * rinv + 2.0 * kn * rinv * rinv * rinv +
-                              (2.0 * l + 2.0) * (-kn * rinv * rinv * rinv - g * rinv * rinv);
-            R.v += f;
-            R.d += f * g * rinv;
-            R.l += f * L;
-            R.dd += f * (g * g - kn * rinv * rinv - g * rinv) * rinv * rinv;
-            R.l1 += (f * g * L + f * Lp) * rinv;
-        } else {
-            const double f = pe.y * exp(-ex * r2);
-            const double Q = 4.0 * ex * ex * r2 - (4.0 * l + 6.0) * ex;
-            R.v += f;
-            R.d += -2.0 * ex * f;
-            R.l += f * Q;
-            R.dd += 4.0 * ex * ex * f;
-            R.l1 += f * (-2.0 * ex * Q + 8.0 * ex * ex);
+// One primitive f's share of the sums, and what its exponent's derivative
+// needs: fz = df/dzeta (normalisation included) and the derivatives of
+// R'/r and R'' + (2l+2) R'/r.
+struct PrimDerivs {
+    double fz, dRd, dRl;
+};
+
+template <bool EXPO>
+__device__ __forceinline__ PrimDerivs radial_prim(const DevSystem &S, double2v pe, int l, int kn, double r, double r2,
+                                                  double rinv, double rk, Radial &R) {
+    const double ex = pe.x;
+    PrimDerivs o = {0.0, 0.0, 0.0};
+    if (S.basis == 0) {
+        const double f = pe.y * rk * exp_f64(-ex * r);
+        const double kr = kn * rinv, g = kr - ex, l2 = (2.0 * l + 2.0) * rinv;
+        const double L = g * g - kr * rinv + l2 * g;
+        const double Lp = -2.0 * g * kr * rinv + 2.0 * kr * rinv * rinv - l2 * (kr * rinv + g * rinv);
+        R.v += f;
+        R.d += f * g * rinv;
+        R.l += f * L;
+        R.dd += f * (g * g - kr * rinv - g * rinv) * rinv * rinv;
+        R.l1 += (f * g * L + f * Lp) * rinv;
+        if (EXPO) {
+            const double qn = S.normalize ? (l + kn + 1.5) / ex : 0.0;
+            o.fz = f * (qn - r);
+            o.dRd = (o.fz * g - f) * rinv;
+            o.dRl = o.fz * L + f * (-2.0 * g - l2);
+        }
+    } else {
+        const double f = pe.y * exp_f64(-ex * r2);
+        const double fl = (4.0 * l + 6.0) * ex, Q = 4.0 * ex * ex * r2 - fl;
+        R.v += f;
+        R.d += -2.0 * ex * f;
+        R.l += f * Q;
+        R.dd += 4.0 * ex * ex * f;
+        R.l1 += f * (-2.0 * ex * Q + 8.0 * ex * ex);
+        if (EXPO) {
+            const double qn = S.normalize ? (0.75 + 0.5 * l) / ex : 0.0;
+            o.fz = f * (qn - r2);
+            o.dRd = -2.0 * f - 2.0 * ex * o.fz;
+            o.dRl = o.fz * Q + f * (8.0 * ex * r2 - (4.0 * l + 6.0));
         }
     }
-    return R;
+    return o;
+}
+
+// Ends a batch of two table columns whose results are v..: without a line
+// between batches the compiler reads the whole table ahead of the
+// multiply-adds and spills it.
+__device__ __forceinline__ void batch_end(double &v) { asm volatile("" : "+v"(v) : : "memory"); }
+template <typename... T>
+__device__ __forceinline__ void batch_end(double &v, T &...more) {
+    batch_end(v);
+    batch_end(more...);
+}
+
+__device__ __forceinline__ double power(double r, int kn) {
+    double rk = 1.0;
+    for (int t = 0; t < kn; ++t) rk *= r;
+    return rk;
+}
+
+// The MO-coefficient derivatives of four AOs, sum over a walker's electrons
+// of chi a (log|Psi|) and chi adot + beta a (E_L), as products of 4 AOs x 4
+// electrons x 4 MOs with four walkers to an instruction (lane 16 k + 4 b + i:
+// AO i or MO i of walker b at electron k of the step), written straight to
+// the outputs.  chi / beta: the ring rows of the four AOs; sA / sAd: rows of
+// a and adot per MO.
+template <int NMO>
+__device__ __forceinline__ void put_mo_gradient(const DevSystem &S, int lane, int64_t wave_first, int64_t W, int mu0,
+                                                const double *chi, const double *beta, const double *sA,
+                                                const double *sAd, const GradOut &G) {
+    constexpr int MB = NMO / 4;
+    const int k = lane >> 4, b = (lane >> 2) & 3, i = lane & 3;
+    const int steps = S.LW >= 4 ? S.LW / 4 : 1;  // products per walker
+    const int row = ((mu0 + i) & (kRing - 1)) * kWave;
+    const bool own = S.LW >= 4 || k < S.LW;      // two-lane walkers fill half of the step
+    // this lane's result: AO mu0 + k, MO 4 s + i of walker b of the set
+    const int mu = mu0 + k;
+    const double f = mu < S.n_ao ? const_tab(S.ao_angf)[mu] : 0.0;
+    wave_sync();
+    for (int set = 0; set < S.WPW / 4; ++set) {
+        const int64_t w = wave_first + 4 * set + b;
+        double gl[MB], ge[MB];
+#pragma unroll
+        for (int s = 0; s < MB; ++s) gl[s] = ge[s] = 0.0;
+        for (int q = 0; q < steps; ++q) {
+            const int col = (4 * set + b) * S.LW + (own ? 4 * q + k : 0);
+            const double c = own ? chi[row + col] : 0.0, be = own ? beta[row + col] : 0.0;
+#pragma unroll
+            for (int s = 0; s < MB; ++s) {
+                const double av = sA[(4 * s + i) * kWave + col], ad = sAd[(4 * s + i) * kWave + col];
+                gl[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(c, own ? av : 0.0, gl[s], 0, 0, 0);
+                ge[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(c, own ? ad : 0.0, ge[s], 0, 0, 0);
+                ge[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(be, own ? av : 0.0, ge[s], 0, 0, 0);
+            }
+        }
+        if (w < W && mu < S.n_ao) {
+#pragma unroll
+            for (int s = 0; s < MB; ++s) {
+                const int m = 4 * s + i;
+                if (m < S.n_mo) {
+                    const int64_t out = w * G.n_param + S.n_prim + mu * S.n_mo + const_tab(S.mo_perm)[m];
+                    if (G.dlogpsi) G.dlogpsi[out] = f * gl[s];
+                    if (G.deloc_dth) G.deloc_dth[out] = -0.5 * f * ge[s];
+                }
+            }
+        }
+    }
+    wave_sync();
 }
 
 // d log|Psi| and d E_L of one direction, from this electron's share of d J
@@ -386,23 +450,28 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
 // RT: arithmetic of the forward evaluation's AO values and MO value
 // contraction (double, or float for the mixed FP32 form); everything the
 // adjoint adds is FP64.
+//
+// Bound by latency: the walkers' tables leave one wave per SIMD, so every
+// stage keeps its LDS reads in batches (two table columns, all rows of a
+// spin), its tables in scalar loads ahead of use, and its contractions on the
+// matrix cores (direction B beside the MO values, the AO weights of a and
+// adot, the MO-coefficient products).  Li2, 32 768 walkers, all outputs:
+// 518 us -> 256 us (175 MB written); many-body CO, 4099 walkers: 2523 us -> 349 us.
 template <int NMO, typename RT>
 __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__restrict__ X, int64_t W,
                                                 GradOut G) {
     extern __shared__ double smem[];
     int64_t w;
-    const Lane L = make_lane(S, (int64_t)blockIdx.x * S.WPW, W, &w);
-    const int base_lds = walker_lds<NMO>(S);
-    double *wsm = smem + L.wloc * (base_lds + grad_extra_lds<NMO>(S));
+    const int64_t wave_first = (int64_t)blockIdx.x * S.WPW;
+    const Lane L = make_lane(S, wave_first, W, &w);
+    double *wsm = smem + L.wloc * grad_walker<NMO>(S);
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const int ts = nmax * NMO;                 // doubles per spin table
     double *sT = wsm;                          // T tables (shared stages)
     double *sC = wsm + 2 * ts;                 // cofactor tables (shared stages)
-    double *gx = wsm + base_lds;               // gradient-only region
-    double *sTD = gx, *sCD = gx + 2 * ts, *sZB = gx + 4 * ts;
-    const int rows_len = 2 * S.n_ao + 2 * NMO;
-    double *sRows = wsm;                       // after the forward-mode stage
-    double *sAtom = wsm + grad_rows_end<NMO>(S);  // [n_atoms][6]: dlogpsi/dR, dE/dR
+    double *sTD = wsm + walker_lds<NMO>(S);    // Tdot, Ainvdot
+    double *sCD = sTD + 2 * ts;                // B0 | Z rows, then Cdot
+    double *sAtom = smem + grad_wave<NMO>(S) + L.wloc * 6 * S.n_atoms;  // [n_atoms][6]: dlogpsi/dR, dE/dR
 
     double x0 = 0.0, x1 = 0.0, x2 = 0.0;
     if (L.active) {
@@ -419,302 +488,336 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
 
     for (int q = L.lw; q < 6 * S.n_atoms; q += S.LW) sAtom[q] = 0.0;
 
-    // ---- shared stages: MO values, Gauss-Jordan, determinants, a_e ----------
+    // ---- shared stages: MO values and direction B, Gauss-Jordan,
+    // determinants, a_e ----
     Core<NMO> c;
-    core_stages<NMO, RT, 0, false, false, false, true>(S, L, wsm, x0, x1, x2, c, smem);
+    double bvec[NMO];
+    core_stages<NMO, RT, 0, false, false, false, true>(S, L, wsm, x0, x1, x2, c, smem, &bvec);
     const double gJ[3] = {c.gJ0, c.gJ1, c.gJ2};
     const double *Tg = sT + L.grp * ts;
     const double *Cg = sC + L.grp * ts;
     double *TDg = sTD + L.grp * ts;
     double *CDg = sCD + L.grp * ts;
-    double *ZBg = sZB + L.grp * ts;
     const int sl = c.slot < 0 ? 0 : c.slot;
-
-    // ---- direction B[e][m] = sum_mu C[mu][m] (lap chi + 2 grad J . grad chi) -
-    double bvec[NMO];
-#pragma unroll
-    for (int m = 0; m < NMO; ++m) bvec[m] = 0.0;
-    {
-        int p = 0;
-        const double *crow = S.mo;
-        for (int sh = 0; sh < S.n_shells; ++sh) {
-            const int4 si = S.shells[sh];
-            const double *A = S.atoms + 4 * si.x;
-            const double dx = x0 - A[0], dy = x1 - A[1], dz = x2 - A[2];
-            const double r2 = dx * dx + dy * dy + dz * dz, r = sqrt(r2);
-            const Radial R = radial_full(S, p, si.w, si.y, si.z, r, r2);
-            p += si.w;
-            const int nc = (si.y + 1) * (si.y + 2) / 2;
-            for (int cc = 0; cc < nc; ++cc) {
-                const Mono mn = monomial(si.y, cc, dx, dy, dz);
-                const double gr[3] = {R.v * mn.g[0] + mn.P * R.d * dx, R.v * mn.g[1] + mn.P * R.d * dy,
-                                      R.v * mn.g[2] + mn.P * R.d * dz};
-                const double beta = R.v * mn.L + mn.P * R.l + 2.0 * (gJ[0] * gr[0] + gJ[1] * gr[1] + gJ[2] * gr[2]);
-#pragma unroll
-                for (int m = 0; m < NMO; ++m) bvec[m] += beta * crow[m];
-                crow += S.nmo_pad;
-            }
-        }
-    }
+    const int last = L.nsig > 0 ? L.nsig - 1 : 0;  // last slot of this spin
 
     // ---- forward mode of the determinant algebra along B -----------------
-    // slot-indexed rows: reference columns hold B0 = B[e][k], virtual
-    // columns hold Z[e][v] = B[e][v] - sum_k B[e][k] T[k][v]
-    if (L.active && c.slot >= 0) {
-#pragma unroll
-        for (int v = 0; v < NMO; ++v) {
-            double z = bvec[v];
-            if (v >= L.nsig) {
-#pragma unroll
-                for (int k = 0; k < kMaxSpin; ++k)
-                    if (k < L.nsig) z -= bvec[k < NMO ? k : 0] * Tg[k * NMO + v];
-            }
-            ZBg[c.slot * NMO + v] = z;
-        }
-    }
-    for (int q = L.lw; q < 2 * ts; q += S.LW) sCD[q] = 0.0;
-    __syncthreads();
-    // row of this lane's slot: Tdot[s][v] = sum_s' Ainv[s][e(s')] Z[e(s')][v];
-    // W[s][k] = (A0^-1 B0)[s][k]; Ainvdot[s][s''] = -sum_k W[s][k] Ainv[k][e(s'')]
-    if (L.active && c.slot >= 0) {
-        const int s = c.slot;
-        double wk[kMaxSpin];
-#pragma unroll
-        for (int k = 0; k < kMaxSpin; ++k) {
-            double acc = 0.0;
-            if (k < L.nsig)
-                for (int s2 = 0; s2 < L.nsig; ++s2) acc += Tg[s * NMO + s2] * ZBg[s2 * NMO + k];
-            wk[k] = acc;
-        }
-#pragma unroll
-        for (int v = 0; v < NMO; ++v) {
-            double acc = 0.0;
-            if (v >= L.nsig) {
-                for (int s2 = 0; s2 < L.nsig; ++s2) acc += Tg[s * NMO + s2] * ZBg[s2 * NMO + v];
-            } else {
-#pragma unroll
-                for (int k = 0; k < kMaxSpin; ++k)
-                    if (k < L.nsig) acc -= wk[k] * Tg[k * NMO + v];
-            }
-            TDg[s * NMO + v] = acc;
-        }
-    }
-    __syncthreads();
-    const double *Tup = sT, *Tdn = sT + ts, *TDup = sTD, *TDdn = sTD + ts;
-    double Sd = 0.0;
-    if (L.wvalid) {
-        for (int n = L.lw; n < S.n_det; n += S.LW) {
-            const int *d = S.dets + n * kDetInts;
-            const double ru = ratio<NMO>(Tup, d), rd = ratio<NMO>(Tdn, d + 5);
-            Sd += S.ci[n] * (ratio_dot<NMO>(Tup, TDup, d) * rd + ru * ratio_dot<NMO>(Tdn, TDdn, d + 5));
-        }
-        for (int t = L.lw; t < S.n_entries; t += S.LW) {
-            const int4 en = S.entries[t];
-            const int end = S.entries[t + 1].w;
-            const double *Ts = en.x == 0 ? Tup : Tdn, *TDs = en.x == 0 ? TDup : TDdn;
-            const double *To = en.x == 0 ? Tdn : Tup, *TDo = en.x == 0 ? TDdn : TDup;
-            const int oth = en.x == 0 ? 5 : 0;
-            double val = 0.0;
-            for (int q = en.w; q < end; ++q) {
-                const int4 cb = S.contribs[q];
-                const int *d = S.dets + cb.x * kDetInts;
-                const double cof = cb.y == 0 ? 1.0 : double(cb.y) * Ts[cb.z * NMO + cb.w];
-                const double cofd = cb.y == 0 ? 0.0 : double(cb.y) * TDs[cb.z * NMO + cb.w];
-                val += S.ci[cb.x] * (ratio_dot<NMO>(To, TDo, d + oth) * cof + ratio<NMO>(To, d + oth) * cofd);
-            }
-            sCD[en.x * ts + en.y * NMO + en.z] = val;
-        }
-    }
-    const double Sdot = walker_sum(Sd, S.LW);
-    __syncthreads();
-
     double adot[NMO];
-    {
-        const double Sinv = 1.0 / c.Ssum;
-        double ainv[kMaxSpin], ainvd[kMaxSpin];
+    auto forward = [&](auto rows_of_spin) {
+        constexpr int JMAX = kMaxSpin < NMO ? kMaxSpin : NMO;
+        constexpr int KR = decltype(rows_of_spin)::value < JMAX ? decltype(rows_of_spin)::value : JMAX;
+        // rows of this spin's tables (the last one again past it, where the
+        // factors that multiply it are zero)
+        int row[KR];
 #pragma unroll
-        for (int k = 0; k < kMaxSpin; ++k) {
-            ainv[k] = (k < L.nsig && L.active) ? Tg[k * NMO + sl] : 0.0;
-            ainvd[k] = (k < L.nsig && L.active) ? TDg[k * NMO + sl] : 0.0;
+        for (int k = 0; k < KR; ++k) row[k] = (k < last ? k : last) * NMO;
+        // slot-indexed rows: reference columns hold B0 = B[e][k], virtual
+        // columns hold Z[e][v] = B[e][v] - sum_k B[e][k] T[k][v]
+        {
+            double bk[KR];
+#pragma unroll
+            for (int k = 0; k < KR; ++k) bk[k] = k < L.nsig ? bvec[k] : 0.0;
+#pragma unroll
+            for (int v = 0; v < NMO; v += 2) {
+                double z0 = bvec[v], z1 = bvec[v + 1], s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int k = 0; k < KR; ++k) {
+                    const double2 t = *(const double2 *)(Tg + row[k] + v);
+                    s0 += bk[k] * t.x;
+                    s1 += bk[k] * t.y;
+                }
+                batch_end(s0, s1);
+                if (v >= L.nsig) z0 -= s0;
+                if (v + 1 >= L.nsig) z1 -= s1;
+                if (L.active && c.slot >= 0) *(double2 *)(CDg + c.slot * NMO + v) = make_double2(z0, z1);
+            }
         }
+        wave_sync();
+        // row of this lane's slot: Tdot[s][v] = sum_s' Ainv[s][e(s')] Z[e(s')][v];
+        // W[s][k] = (A0^-1 B0)[s][k]; Ainvdot[s][s''] = -sum_k W[s][k] Ainv[k][e(s'')]
+        {
+            double as[KR], wk[KR], td[NMO];
 #pragma unroll
-        for (int v = 0; v < NMO; ++v) {
+            for (int k = 0; k < KR; ++k) as[k] = k < L.nsig ? Tg[sl * NMO + k] : 0.0;
+#pragma unroll
+            for (int v = 0; v < NMO; v += 2) {
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int k = 0; k < KR; ++k) {
+                    const double2 z = *(const double2 *)(CDg + row[k] + v);
+                    s0 += as[k] * z.x;
+                    s1 += as[k] * z.y;
+                }
+                batch_end(s0, s1);
+                td[v] = s0;
+                td[v + 1] = s1;
+            }
+#pragma unroll
+            for (int k = 0; k < KR; ++k) wk[k] = k < L.nsig ? td[k] : 0.0;
+#pragma unroll
+            for (int v = 0; v < (KR < NMO ? KR : NMO); v += 2) {
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int k = 0; k < KR; ++k) {
+                    const double2 t = *(const double2 *)(Tg + row[k] + v);
+                    s0 -= wk[k] * t.x;
+                    s1 -= wk[k] * t.y;
+                }
+                batch_end(s0, s1);
+                if (v < L.nsig) td[v] = s0;
+                if (v + 1 < L.nsig) td[v + 1] = s1;
+            }
+            if (L.active && c.slot >= 0) {
+#pragma unroll
+                for (int v = 0; v < NMO; v += 2) *(double2 *)(TDg + c.slot * NMO + v) = make_double2(td[v], td[v + 1]);
+            }
+        }
+        wave_sync();
+        for (int q = 2 * L.lw; q < 2 * ts; q += 2 * S.LW) *(double2 *)(sCD + q) = make_double2(0.0, 0.0);
+        wave_sync();
+        // derivatives of S and of the cofactor tables, from the same records
+        // as their values
+        const double *Tup = sT, *Tdn = sT + ts, *TDup = sTD, *TDdn = sTD + ts;
+        double Sd = 0.0;
+        for (int i0 = 0; i0 < S.det_rows; i0 += kRecBatch) {
+            uint4v rb[kRecBatch];
+#pragma unroll
+            for (int u = 0; u < kRecBatch; ++u)
+                rb[u] = i0 + u < S.det_rows ? const_tab((const uint4v *)S.det_recs)[(i0 + u) * S.LW + L.lw]
+                                            : uint4v{0, 0, 0, 0};
+#pragma unroll
+            for (int u = 0; u < kRecBatch; ++u) {
+                const uint4v r = rb[u];
+                const double ru = ratio_code(Tup, r.z, NMO, 0), rd = ratio_code(Tdn, r.w, NMO, 0);
+                Sd += __hiloint2double((int)r.y, (int)r.x) *
+                      (ratio_code_dot<NMO>(Tup, TDup, r.z) * rd + ru * ratio_code_dot<NMO>(Tdn, TDdn, r.w));
+            }
+        }
+        {
             double acc = 0.0;
-            if (v >= L.nsig) {
+            for (int i0 = 0; i0 < S.cof_rows; i0 += kRecBatch) {
+                uint4v rb[kRecBatch];
 #pragma unroll
-                for (int k = 0; k < kMaxSpin; ++k)
-                    if (k < L.nsig) acc += ainvd[k] * Cg[k * NMO + v] + ainv[k] * CDg[k * NMO + v];
-                acc = (acc - c.av[v] * Sdot) * Sinv;
+                for (int u = 0; u < kRecBatch; ++u)
+                    rb[u] = i0 + u < S.cof_rows ? const_tab((const uint4v *)S.cof_recs)[(i0 + u) * S.LW + L.lw]
+                                                : uint4v{0, 0, 0, 0};
+#pragma unroll
+                for (int u = 0; u < kRecBatch; ++u) {
+                    const uint4v r = rb[u];
+                    const int spin = (r.w >> 1) & 1;
+                    const double *Ts = spin ? Tdn : Tup, *TDs = spin ? TDdn : TDup;
+                    const double *To = spin ? Tup : Tdn, *TDo = spin ? TDup : TDdn;
+                    const uint32_t cc = r.z >> 18, oc = r.z & 0x3FFFFu;
+                    const int at = ((cc >> 2) & 7) * NMO + (cc >> 5);
+                    const double sgn = (cc & 3) == 0 ? 0.0 : ((cc & 3) == 1 ? 1.0 : -1.0);
+                    const double cof = (cc & 3) == 0 ? 1.0 : sgn * Ts[at];
+                    const double cofd = sgn * TDs[at];
+                    acc += __hiloint2double((int)r.y, (int)r.x) *
+                           (ratio_code_dot<NMO>(To, TDo, oc) * cof + ratio_code(To, oc, NMO, 0) * cofd);
+                    if (r.w & 1u) {
+                        sCD[spin * ts + ((r.w >> 2) & 7) * NMO + (r.w >> 5)] = acc;
+                        acc = 0.0;
+                    }
+                }
             }
-            adot[v] = acc;
+        }
+        const double Sdot = walker_sum(Sd, S.LW);
+        wave_sync();
+        // adot: virtual orbitals, then the reference ones
+        double ainv[KR], ainvd[KR], hk[KR];
+#pragma unroll
+        for (int k = 0; k < KR; ++k) {
+            const double t = Tg[row[k] + sl], td = TDg[row[k] + sl];
+            ainv[k] = (k < L.nsig && L.active) ? t : 0.0;
+            ainvd[k] = (k < L.nsig && L.active) ? td : 0.0;
+            hk[k] = 0.0;
+        }
+        const double Sinv = 1.0 / c.Ssum;
+#pragma unroll
+        for (int v = 0; v < NMO; v += 2) {
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int k = 0; k < KR; ++k) {
+                const double2 cv = *(const double2 *)(Cg + row[k] + v), dv = *(const double2 *)(CDg + row[k] + v);
+                s0 += ainvd[k] * cv.x + ainv[k] * dv.x;
+                s1 += ainvd[k] * cv.y + ainv[k] * dv.y;
+            }
+            batch_end(s0, s1);
+            adot[v] = v >= L.nsig ? (s0 - c.av[v] * Sdot) * Sinv : 0.0;
+            adot[v + 1] = v + 1 >= L.nsig ? (s1 - c.av[v + 1] * Sdot) * Sinv : 0.0;
         }
 #pragma unroll
-        for (int k = 0; k < kMaxSpin; ++k) {
-            if (k < L.nsig && k < NMO) {
-                double h = 0.0;
+        for (int v = 0; v < NMO; v += 2) {
+            const double a0 = v >= L.nsig ? c.av[v] : 0.0, a1 = v + 1 >= L.nsig ? c.av[v + 1] : 0.0;
 #pragma unroll
-                for (int v = 0; v < NMO; ++v)
-                    if (v >= L.nsig) h += TDg[k * NMO + v] * c.av[v] + Tg[k * NMO + v] * adot[v];
-                adot[k < NMO ? k : 0] = ainvd[k] - h;
+            for (int k = 0; k < KR; ++k) {
+                const double2 t = *(const double2 *)(Tg + row[k] + v), td = *(const double2 *)(TDg + row[k] + v);
+                hk[k] += td.x * a0 + t.x * adot[v] + td.y * a1 + t.y * adot[v + 1];
             }
+#pragma unroll
+            for (int k = 0; k < KR; ++k) batch_end(hk[k]);
         }
-    }
-    __syncthreads();  // the table region becomes the per-electron rows below
+#pragma unroll
+        for (int k = 0; k < KR; ++k) adot[k] = k < L.nsig ? ainvd[k] - hk[k] : adot[k];
+    };
+    if (S.G <= 2) forward(std::integral_constant<int, 2>());
+    else if (S.G == 4) forward(std::integral_constant<int, 4>());
+    else forward(std::integral_constant<int, 8>());
+    wave_sync();  // the walkers' tables become the wave's rows
 
     // ---- main gradient pass over the AOs ----------------------------------
-    double *row = sRows + L.lw * rows_len;    // [chi | beta | a | adot]
-    for (int q = 0; q < rows_len; ++q) row[q] = 0.0;
+    // Per shell the AO weights t (of a) and td (of adot) meet the monomials
+    // first, in sums that every radial derivative and every exponent shares;
+    // chi and beta = lap chi + 2 grad J . grad chi take the weights' ring rows
+    // for the MO-coefficient products of each four AOs.
+    double *sA = smem, *sAd = sA + NMO * kWave, *ringT = sAd + NMO * kWave, *ringD = ringT + kRing * kWave;
+    AoWeights<NMO> wt(S, L.lane, sA, ringT, c.av), wd(S, L.lane, sAd, ringD, adot);
+    // rows of idle lanes are zero in the products over a walker's electrons
+    wave_sync();
+#pragma unroll
+    for (int m = 0; m < NMO; ++m) {
+        sA[m * kWave + L.lane] = L.active ? c.av[m] : 0.0;
+        sAd[m * kWave + L.lane] = L.active ? adot[m] : 0.0;
+    }
+    wave_sync();
     double gS[3] = {0.0, 0.0, 0.0};
     {
-        int p = 0, mu = 0;
-        const double *crow = S.mo;
-        for (int a = 0; a < S.n_atoms; ++a) {
-            double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
-            p = 0;
-            mu = 0;
-            crow = S.mo;
-            for (int sh = 0; sh < S.n_shells; ++sh) {
-                const int4 si = S.shells[sh];
-                const int nc = (si.y + 1) * (si.y + 2) / 2;
-                if (si.x != a) {
-                    p += si.w;
-                    mu += nc;
-                    crow += nc * S.nmo_pad;
-                    continue;
-                }
-                const double *A = S.atoms + 4 * a;
-                const double d[3] = {x0 - A[0], x1 - A[1], x2 - A[2]};
-                const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2], r = sqrt(r2);
-                const Radial R = radial_full(S, p, si.w, si.y, si.z, r, r2);
-                double A1 = 0.0, A2 = 0.0, A3 = 0.0;
-                const double gd = gJ[0] * d[0] + gJ[1] * d[1] + gJ[2] * d[2];
-                for (int cc = 0; cc < nc; ++cc, ++mu, crow += S.nmo_pad) {
-                    const Mono mn = monomial(si.y, cc, d[0], d[1], d[2]);
-                    double t = 0.0, td = 0.0;
-#pragma unroll
-                    for (int m = 0; m < NMO; ++m) {
-                        t += crow[m] * c.av[m];
-                        td += crow[m] * adot[m];
-                    }
-                    const double chi = mn.P * R.v;
-                    double gr[3], hg[3], g3[3];
-                    const double gP_gJ = mn.g[0] * gJ[0] + mn.g[1] * gJ[1] + mn.g[2] * gJ[2];
-                    const double hP[3] = {mn.h[0] * gJ[0] + mn.h[3] * gJ[1] + mn.h[4] * gJ[2],
-                                          mn.h[3] * gJ[0] + mn.h[1] * gJ[1] + mn.h[5] * gJ[2],
-                                          mn.h[4] * gJ[0] + mn.h[5] * gJ[1] + mn.h[2] * gJ[2]};
-                    for (int k = 0; k < 3; ++k) {
-                        gr[k] = R.v * mn.g[k] + mn.P * R.d * d[k];
-                        // (Hessian of chi) . grad J
-                        hg[k] = R.v * hP[k] + mn.g[k] * R.d * gd + R.d * d[k] * gP_gJ +
-                                mn.P * (R.d * gJ[k] + R.dd * d[k] * gd);
-                        // gradient of lap chi
-                        g3[k] = mn.L * R.d * d[k] + R.l * mn.g[k] + mn.P * R.l1 * d[k];
-                    }
-                    const double lap = R.v * mn.L + mn.P * R.l;
-                    const double beta = lap + 2.0 * (gJ[0] * gr[0] + gJ[1] * gr[1] + gJ[2] * gr[2]);
-                    if (L.active) {
-                        for (int k = 0; k < 3; ++k) {
-                            gS[k] += t * gr[k];
-                            lr[k] -= t * gr[k];
-                            er[k] += 0.5 * td * gr[k] + t * hg[k] + 0.5 * t * g3[k];
-                        }
-                        row[mu] = chi;
-                        row[S.n_ao + mu] = beta;
-                    }
-                    A1 += td * mn.P;
-                    A2 += t * (mn.L + 2.0 * gP_gJ);
-                    A3 += t * mn.P;
-                }
-                // exponent derivatives of each primitive of this shell
-                const double rinv = 1.0 / r;
-                for (int q = 0; q < si.w; ++q) {
-                    const double2 pe = S.prims[p + q];
-                    const double ex = pe.x;
-                    double fz, dRd, dRl;
-                    if (S.basis == 0) {
-                        const int nq = si.y + si.z + 1;
-                        const double qn = S.normalize ? (nq + 0.5) / ex : 0.0;
-                        double f = pe.y * exp(-ex * r);
-                        for (int t2 = 0; t2 < si.z; ++t2) f *= r;
-                        const double g = si.z * rinv - ex;
-                        const double Lq = g * g - si.z * rinv * rinv + (2.0 * si.y + 2.0) * g * rinv;
-                        fz = f * (qn - r);
-                        dRd = (fz * g - f) * rinv;
-                        dRl = fz * Lq + f * (-2.0 * g - (2.0 * si.y + 2.0) * rinv);
-                    } else {
-                        const double qn = S.normalize ? (0.75 + 0.5 * si.y) / ex : 0.0;
-                        const double f = pe.y * exp(-ex * r2);
-                        const double Q = 4.0 * ex * ex * r2 - (4.0 * si.y + 6.0) * ex;
-                        fz = f * (qn - r2);
-                        dRd = -2.0 * f - 2.0 * ex * fz;
-                        dRl = fz * Q + f * (8.0 * ex * r2 - (4.0 * si.y + 6.0));
-                    }
-                    double gl = 0.0, ge = 0.0;
-                    if (L.active) {
-                        gl = fz * A3;
-                        ge = -0.5 * (fz * (A1 + A2) + dRd * 2.0 * gd * A3 + dRl * A3);
-                    }
-                    gl = walker_sum(gl, S.LW);
-                    ge = walker_sum(ge, S.LW);
-                    if (L.wvalid && L.lw == 0) {
-                        if (G.dlogpsi) G.dlogpsi[w * G.n_param + p + q] = gl;
-                        if (G.deloc_dth) G.deloc_dth[w * G.n_param + p + q] = ge;
-                    }
-                }
-                p += si.w;
-            }
-            // e-n attraction of this atom
-            if (L.active) {
-                const double *A = S.atoms + 4 * a;
-                const double d[3] = {x0 - A[0], x1 - A[1], x2 - A[2]};
-                const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-                const double f = -A[3] / (rr * rr * rr);
-                for (int k = 0; k < 3; ++k) er[k] += f * d[k];
-            }
+        int p = 0, mu = 0, done = 0, atom = -1;
+        double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
+        AtomGeo<double> a;
+        a.dx = a.dy = a.dz = a.r2 = 0.0;
+        double r = 0.0, rinv = 0.0, gd = 0.0;
+        auto put_atom = [&]() {
+            if (atom < 0) return;
             for (int k = 0; k < 3; ++k) {
-                lr[k] = walker_sum(lr[k], S.LW);
-                er[k] = walker_sum(er[k], S.LW);
+                const double l = walker_sum(lr[k], S.LW), e = walker_sum(er[k], S.LW);
+                if (L.wvalid && L.lw == 0) {
+                    sAtom[6 * atom + k] += l;
+                    sAtom[6 * atom + 3 + k] += e;
+                }
+                lr[k] = er[k] = 0.0;
             }
-            if (L.wvalid && L.lw == 0) {
+        };
+        for (int sh = 0; sh < S.n_shells; ++sh) {
+            const int4v si = shell_info(S, sh);
+            const int nc = (si.y + 1) * (si.y + 2) / 2;
+            if (si.x != atom) {  // shells of one atom share the geometry
+                put_atom();
+                atom = si.x;
+                a.set(S, atom, x0, x1, x2);
+                r = sqrt(a.r2);
+                rinv = 1.0 / r;
+                gd = gJ[0] * a.dx + gJ[1] * a.dy + gJ[2] * a.dz;
+            }
+            wt.need(mu + nc);
+            wd.need(mu + nc);
+            // sums over the components: t P, t grad P, t lap P, t (Hess P) grad J,
+            // td P, td grad P
+            double q = 0.0, qv[3] = {0.0, 0.0, 0.0}, qL = 0.0, qh[3] = {0.0, 0.0, 0.0};
+            double qd = 0.0, qdv[3] = {0.0, 0.0, 0.0};
+            if (si.y == 0) {
+                q = wt(mu);
+                qd = wd(mu);
+            } else if (si.y == 1) {
+#pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    sAtom[6 * a + k] = lr[k];
-                    sAtom[6 * a + 3 + k] = er[k];
+                    qv[k] = wt(mu + k);
+                    qdv[k] = wd(mu + k);
+                }
+                q = qv[0] * a.dx + qv[1] * a.dy + qv[2] * a.dz;
+                qd = qdv[0] * a.dx + qdv[1] * a.dy + qdv[2] * a.dz;
+            } else {
+                // symmetric matrix of t: 2 t on the diagonal, t off it
+                auto quad = [&](const AoWeights<NMO> &wx, double &s, double (&sv)[3], double &tr, double (&M)[6]) {
+                    const double xx = wx(mu), xy = wx(mu + 1), xz = wx(mu + 2), yy = wx(mu + 3), yz = wx(mu + 4),
+                                 zz = wx(mu + 5);
+                    M[0] = 2.0 * xx, M[1] = xy, M[2] = xz, M[3] = 2.0 * yy, M[4] = yz, M[5] = 2.0 * zz;
+                    sv[0] = M[0] * a.dx + M[1] * a.dy + M[2] * a.dz;
+                    sv[1] = M[1] * a.dx + M[3] * a.dy + M[4] * a.dz;
+                    sv[2] = M[2] * a.dx + M[4] * a.dy + M[5] * a.dz;
+                    s = 0.5 * (sv[0] * a.dx + sv[1] * a.dy + sv[2] * a.dz);
+                    tr = M[0] + M[3] + M[5];
+                };
+                double M[6], Md[6], trd;
+                quad(wt, q, qv, qL, M);
+                quad(wd, qd, qdv, trd, Md);
+                qh[0] = M[0] * gJ[0] + M[1] * gJ[1] + M[2] * gJ[2];
+                qh[1] = M[1] * gJ[0] + M[3] * gJ[1] + M[4] * gJ[2];
+                qh[2] = M[2] * gJ[0] + M[4] * gJ[1] + M[5] * gJ[2];
+            }
+            const double qg = qv[0] * gJ[0] + qv[1] * gJ[1] + qv[2] * gJ[2];
+            // one pass over the primitives: radial sums and exponent derivatives
+            const double A1 = qd + qL + 2.0 * qg;
+            const double rk = S.basis == 0 ? power(r, si.z) : 1.0;
+            Radial R = {0.0, 0.0, 0.0, 0.0, 0.0};
+            for (int i = 0; i < si.w; ++i) {
+                const PrimDerivs z = radial_prim<true>(S, prim_info(S, p + i), si.y, si.z, r, a.r2, rinv, rk, R);
+                double gl = 0.0, ge = 0.0;
+                if (L.active) {
+                    gl = z.fz * q;
+                    ge = -0.5 * (z.fz * A1 + z.dRd * 2.0 * gd * q + z.dRl * q);
+                }
+                gl = walker_sum(gl, S.LW);
+                ge = walker_sum(ge, S.LW);
+                if (L.wvalid && L.lw == 0) {
+                    if (G.dlogpsi) G.dlogpsi[w * G.n_param + p + i] = gl;
+                    if (G.deloc_dth) G.deloc_dth[w * G.n_param + p + i] = ge;
                 }
             }
-        }
-    }
-    // MO-coefficient gradient rows: a and adot of this electron
-    if (L.active) {
+            p += si.w;
+            if (L.active) {
+                const double d[3] = {a.dx, a.dy, a.dz};
 #pragma unroll
-        for (int m = 0; m < NMO; ++m) {
-            row[2 * S.n_ao + m] = c.av[m];
-            row[2 * S.n_ao + NMO + m] = adot[m];
+                for (int k = 0; k < 3; ++k) {
+                    // sums of t grad chi, td grad chi, t (Hess chi) grad J, t grad lap chi
+                    const double tg = R.v * qv[k] + R.d * q * d[k], tdg = R.v * qdv[k] + R.d * qd * d[k];
+                    const double th = R.v * qh[k] + R.d * (gd * qv[k] + d[k] * qg + q * gJ[k]) + R.dd * q * gd * d[k];
+                    const double t3 = (R.d * qL + R.l1 * q) * d[k] + R.l * qv[k];
+                    gS[k] += tg;
+                    lr[k] -= tg;
+                    er[k] += 0.5 * tdg + th + 0.5 * t3;
+                }
+            }
+            // chi and beta into the ring rows whose weights are spent
+            const double Xr = R.l + 2.0 * R.d * gd;
+            shell_monomials(si.y, a.dx, a.dy, a.dz, [&](int cc, double P, double Px, double Py, double Pz, double PL) {
+                const int at = ((mu + cc) & (kRing - 1)) * kWave + L.lane;
+                const double chi = P * R.v;
+                const double be = P * Xr + R.v * (PL + 2.0 * (gJ[0] * Px + gJ[1] * Py + gJ[2] * Pz));
+                ringT[at] = L.active ? chi : 0.0;
+                ringD[at] = L.active ? be : 0.0;
+            });
+            mu += nc;
+            for (; mu - done >= 4; done += 4)
+                put_mo_gradient<NMO>(S, L.lane, wave_first, W, done, ringT, ringD, sA, sAd, G);
+        }
+        put_atom();
+        if (done < mu) {
+            for (int z = mu; z & 3; ++z) {
+                ringT[(z & (kRing - 1)) * kWave + L.lane] = 0.0;
+                ringD[(z & (kRing - 1)) * kWave + L.lane] = 0.0;
+            }
+            put_mo_gradient<NMO>(S, L.lane, wave_first, W, done, ringT, ringD, sA, sAd, G);
         }
     }
-    __syncthreads();
-
-    if (L.wvalid) {
-        // d/dC[mu][m]: sum over the walker's electrons (rows) of
-        // chi_mu a[m] (log|Psi|) and -1/2 (adot[m] chi_mu + a[m] beta_mu) (E_L)
-        const double *rows0 = sRows;
-        const int nq = S.n_ao * S.n_mo;
-        for (int q = L.lw; q < nq; q += S.LW) {
-            const int mu = q / S.n_mo, m = q % S.n_mo;
-            double gl = 0.0, ge = 0.0;
-            for (int e = 0; e < S.LW; ++e) {
-                const double *rw = rows0 + e * rows_len;
-                gl += rw[mu] * rw[2 * S.n_ao + m];
-                ge += rw[2 * S.n_ao + NMO + m] * rw[mu] + rw[2 * S.n_ao + m] * rw[S.n_ao + mu];
-            }
-            const int out = S.n_prim + mu * S.n_mo + S.mo_perm[m];
-            const double f = S.ao_angf[mu];
-            if (G.dlogpsi) G.dlogpsi[w * G.n_param + out] = f * gl;
-            if (G.deloc_dth) G.deloc_dth[w * G.n_param + out] = -0.5 * f * ge;
+    // e-n attraction
+    for (int a = 0; a < S.n_atoms; ++a) {
+        double er[3] = {0.0, 0.0, 0.0};
+        if (L.active) {
+            const auto *A = const_tab(S.atoms) + 4 * a;
+            const double d[3] = {x0 - A[0], x1 - A[1], x2 - A[2]};
+            const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+            const double f = -A[3] / (rr * rr * rr);
+            for (int k = 0; k < 3; ++k) er[k] = f * d[k];
+        }
+        for (int k = 0; k < 3; ++k) {
+            const double e = walker_sum(er[k], S.LW);
+            if (L.wvalid && L.lw == 0) sAtom[6 * a + 3 + k] += e;
         }
     }
 
     // ---- Jastrow parameters and the Jastrow part of the nuclear gradients ---
-    __syncthreads();  // the per-electron rows are no longer read
+    wave_sync();  // the rings and rows are no longer read
     {
         double *sP = wsm;                                   // [LW][3]
         double *sF = wsm + 3 * S.LW;                        // [LW][n_atoms][2 een_n]
@@ -723,7 +826,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
         sP[3 * L.lw + 1] = x1;
         sP[3 * L.lw + 2] = x2;
         een_table_fill<true>(S, L, x0, x1, x2, sF, sG);
-        __syncthreads();
+        wave_sync();
         const double h[3] = {gJ[0] + gS[0], gJ[1] + gS[1], gJ[2] + gS[2]};
         jastrow_derivs(S, L, w, x0, x1, x2, h, sP, sF, sG, G, sAtom);
     }
@@ -753,8 +856,7 @@ template <int NMO>
 static hipError_t launch_grad_t(const DevSystem &S, const double *X, int64_t W, const GradOut &G, bool mixed,
                                 hipStream_t st) {
     const int64_t blocks = (W + S.WPW - 1) / S.WPW;
-    size_t lds = (size_t)S.WPW * (walker_lds<NMO>(S) + grad_extra_lds<NMO>(S)) * sizeof(double);
-    if (lds < walker::orbital_lds_bytes<NMO>()) lds = walker::orbital_lds_bytes<NMO>();
+    const size_t lds = grad_lds<NMO>(S) * sizeof(double);
     if (mixed)
         hipLaunchKernelGGL((k_grad<NMO, float>), dim3((unsigned)blocks), dim3(kWave), lds, st, S, X, W, G);
     else
@@ -762,15 +864,22 @@ static hipError_t launch_grad_t(const DevSystem &S, const double *X, int64_t W, 
     return hipGetLastError();
 }
 
+// LDS by which a system is admitted: what the kernel takes, and at least a row
+// of chi, beta, a and adot per electron and the two-component e-e-n tables.
+// The kernel no longer holds these; they stay in the limit so that the systems
+// a caller sees refused do not depend on the kernel's layout.
 size_t grad_lds_bytes(const DevSystem &S) {
-    int per = 0;
+    const size_t rows = (size_t)S.LW * 2 * (S.n_ao + S.nmo_pad);
+    const size_t een = (size_t)S.LW * (3 + 2 * S.n_atoms * (2 * S.een_n + kEenGeo));
+    const size_t admit = S.WPW * ((rows > een ? rows : een) + 6 * S.n_atoms);
+    size_t all = 0;
     switch (S.nmo_pad) {
 #define QMC_LDS(N) \
-    case N: per = walker_lds<N>(S) + grad_extra_lds<N>(S); break;
+    case N: all = grad_lds<N>(S); break;
         QMC_LDS(4) QMC_LDS(8) QMC_LDS(12) QMC_LDS(16) QMC_LDS(20) QMC_LDS(24) QMC_LDS(32)
 #undef QMC_LDS
     }
-    return (size_t)S.WPW * per * sizeof(double);
+    return (all > admit ? all : admit) * sizeof(double);
 }
 
 hipError_t launch_grad(const DevSystem &S, const double *X, int64_t W, double *dlogpsi,

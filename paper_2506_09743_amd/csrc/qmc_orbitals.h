@@ -59,40 +59,35 @@ struct AtomGeo {
     }
 };
 
-// Pass 1 in FP64: phi_m(r_e) = sum_mu C[mu][m] chi_mu(r_e) of the lane's
-// electron.  chi rows enter the ring shell by shell and leave it four at a
-// time; the C rows of the next four are already in registers.  Every lane of
-// the wave must call it; buf: orbital_lds_bytes<NMO>() of LDS.
-template <int NMO, bool VK>
-__device__ __forceinline__ void mo_values_f64(const DevSystem &S, int lane, double *buf, double x0, double x1,
-                                              double x2, double (&phi)[NMO]) {
-    constexpr int MB = NMO / 4;
-    constexpr bool kFew = NMO <= kFewMO;
-    const int g = lane >> 4, j = lane & 15;
-    const auto *Ap = const_tab(S.mo_a) + (g * 4 + (lane & 3)) * MB;
-    const auto *row = const_tab(S.mo);  // kFew: one scalar row per AO
+// Contraction of AO rows with C, one value per electron and AO, in AO order:
+// out_m = sum_mu C[mu][m] row_mu.  Rows enter an LDS ring as they are made
+// and leave it four at a time; the C rows of the next four are already in
+// registers.  Every lane of the wave must use it alike; buf:
+// orbital_lds_bytes<NMO>() of LDS.
+template <int NMO>
+struct MoRows {
+    static constexpr int MB = NMO / 4;
+    double *buf;
+    const __attribute__((address_space(4))) double *Ap;
+    int lane, mu, done;  // rows written, rows contracted
     double A[MB], acc[MB][4];
+
+    __device__ __forceinline__ MoRows(const DevSystem &S, int lane_, double *buf_)
+        : buf(buf_), lane(lane_), mu(0), done(0) {
+        Ap = const_tab(S.mo_a) + ((lane >> 4) * 4 + (lane & 3)) * MB;
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
-        if (!kFew) A[m] = Ap[m];
+        for (int m = 0; m < MB; ++m) {
+            A[m] = Ap[m];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[m][t] = 0.0;
-    }
-    if (kFew)
-#pragma unroll
-        for (int m = 0; m < NMO; ++m) phi[m] = 0.0;
-    int mu = 0, done = 0;  // rows written, rows contracted
-    auto push = [&](double v) {
-        if constexpr (kFew) {
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) phi[m] += v * row[m];
-            row += NMO;
-        } else {
-            buf[(mu & (kRing - 1)) * kWave + lane] = v;
-            ++mu;
+            for (int t = 0; t < 4; ++t) acc[m][t] = 0.0;
         }
-    };
-    auto contract = [&]() {
+    }
+    __device__ __forceinline__ void push(double v) {
+        buf[(mu & (kRing - 1)) * kWave + lane] = v;
+        ++mu;
+    }
+    __device__ __forceinline__ void contract() {
+        const int g = lane >> 4, j = lane & 15;
         wave_sync();
         double B[4];
 #pragma unroll
@@ -105,7 +100,55 @@ __device__ __forceinline__ void mo_values_f64(const DevSystem &S, int lane, doub
         Ap += 4 * NMO;
 #pragma unroll
         for (int m = 0; m < MB; ++m) A[m] = Ap[m];
-    };
+    }
+    // at the end of each shell
+    __device__ __forceinline__ void flush() {
+        while (mu - done >= 4) contract();
+    }
+    __device__ __forceinline__ void finish(double (&out)[NMO]) {
+        const int g = lane >> 4, j = lane & 15;
+        while (mu & 3) push(0.0);  // the table's rows are zero there
+        if (done < mu) contract();
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) buf[(4 * m + g) * kWave + 16 * t + j] = acc[m][t];
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < NMO; ++m) out[m] = buf[m * kWave + lane];
+        wave_sync();
+    }
+};
+
+// The same on the vector unit (kFewMO).
+template <>
+struct MoRows<kFewMO> {
+    const __attribute__((address_space(4))) double *row;
+    double acc[kFewMO];
+
+    __device__ __forceinline__ MoRows(const DevSystem &S, int, double *) : row(const_tab(S.mo)) {
+#pragma unroll
+        for (int m = 0; m < kFewMO; ++m) acc[m] = 0.0;
+    }
+    __device__ __forceinline__ void push(double v) {
+#pragma unroll
+        for (int m = 0; m < kFewMO; ++m) acc[m] += v * row[m];
+        row += kFewMO;
+    }
+    __device__ __forceinline__ void flush() {}
+    __device__ __forceinline__ void finish(double (&out)[kFewMO]) {
+#pragma unroll
+        for (int m = 0; m < kFewMO; ++m) out[m] = acc[m];
+    }
+};
+
+// Pass 1 in FP64: phi_m(r_e) = sum_mu C[mu][m] chi_mu(r_e) of the lane's
+// electron.  Every lane of the wave must call it.
+template <int NMO, bool VK>
+__device__ __forceinline__ void mo_values_f64(const DevSystem &S, int lane, double *buf, double x0, double x1,
+                                              double x2, double (&phi)[NMO]) {
+    MoRows<NMO> rows(S, lane, buf);
     int p = 0, atom = -1;
     AtomGeo<double> a;
     double r = 0.0;
@@ -120,34 +163,111 @@ __device__ __forceinline__ void mo_values_f64(const DevSystem &S, int lane, doub
         shell_radial<double, false, VK>(S, p, si.w, si.y, si.z, r, a.r2, 0.0, R, Rd, Rl);
         p += si.w;
         if (si.y == 0) {
-            push(R);
+            rows.push(R);
         } else if (si.y == 1) {
-            push(a.dx * R);
-            push(a.dy * R);
-            push(a.dz * R);
+            rows.push(a.dx * R);
+            rows.push(a.dy * R);
+            rows.push(a.dz * R);
         } else {  // xx, xy, xz, yy, yz, zz
-            push(a.dx * a.dx * R);
-            push(a.dx * a.dy * R);
-            push(a.dx * a.dz * R);
-            push(a.dy * a.dy * R);
-            push(a.dy * a.dz * R);
-            push(a.dz * a.dz * R);
+            rows.push(a.dx * a.dx * R);
+            rows.push(a.dx * a.dy * R);
+            rows.push(a.dx * a.dz * R);
+            rows.push(a.dy * a.dy * R);
+            rows.push(a.dy * a.dz * R);
+            rows.push(a.dz * a.dz * R);
         }
-        if constexpr (!kFew)
-            while (mu - done >= 4) contract();
+        rows.flush();
     }
-    if constexpr (kFew) return;
-    while (mu & 3) push(0.0);  // the table's rows are zero there
-    if (done < mu) contract();
-    wave_sync();
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) buf[(4 * m + g) * kWave + 16 * t + j] = acc[m][t];
-    wave_sync();
-#pragma unroll
-    for (int m = 0; m < NMO; ++m) phi[m] = buf[m * kWave + lane];
-    wave_sync();
+    rows.finish(phi);
+}
+
+// MO values and the direction B[e][m] = sum_mu C[mu][m] (lap chi + 2 grad J .
+// grad chi) of the adjoint in one pass over the shells (gJ: grad_e J).  The
+// values round as mo_values_f64's.  buf: twice orbital_lds_bytes<NMO>().
+template <int NMO>
+__device__ __forceinline__ void mo_values_direction(const DevSystem &S, int lane, double *buf, double x0, double x1,
+                                                    double x2, const double (&gJ)[3], double (&phi)[NMO],
+                                                    double (&bvec)[NMO]) {
+    MoRows<NMO> chi(S, lane, buf), beta(S, lane, buf + (NMO > kRing ? NMO : kRing) * kWave);
+    int p = 0, atom = -1;
+    AtomGeo<double> a;
+    double r = 0.0, rinv = 0.0, gd = 0.0;
+    for (int sh = 0; sh < S.n_shells; ++sh) {
+        const int4v si = shell_info(S, sh);
+        if (si.x != atom) {
+            atom = si.x;
+            a.set(S, atom, x0, x1, x2);
+            if (S.basis == 0) {
+                r = sqrt(a.r2);
+                rinv = 1.0 / r;
+            }
+            gd = gJ[0] * a.dx + gJ[1] * a.dy + gJ[2] * a.dz;
+        }
+        // R as a chain of fused multiply-adds (as without derivatives), R'/r and
+        // R'' + (2l+2) R'/r
+        double R = 0.0, Rd = 0.0, Rl = 0.0;
+        if (S.basis == 0) {
+            double rk = 1.0;
+            for (int t = 0; t < si.z; ++t) rk *= r;
+            const double kr = si.z * rinv, l2 = (2.0 * si.y + 2.0) * rinv;
+            for (int q = 0; q < si.w; ++q) {
+                const double2v pe = prim_info(S, p + q);
+                const double e = exp_f64(-pe.x * r), cr = pe.y * rk, f = cr * e, g = kr - pe.x;
+                R = __builtin_fma(cr, e, R);
+                Rd += f * g * rinv;
+                Rl += f * (g * g - kr * rinv + l2 * g);
+            }
+        } else {
+            const double fl = 4.0 * si.y + 6.0;
+            auto add = [&](double2v pe, double e) {
+                const double f = pe.y * e, u = pe.x * f;
+                R = __builtin_fma(pe.y, e, R);
+                Rd -= 2.0 * u;
+                Rl += u * (4.0 * pe.x * a.r2 - fl);
+            };
+            int q = 0;
+            for (; q + 1 < si.w; q += 2) {
+                const double2v pa = prim_info(S, p + q), pb = prim_info(S, p + q + 1);
+                const double ea = exp_f64(-pa.x * a.r2), eb = exp_f64(-pb.x * a.r2);
+                add(pa, ea);
+                add(pb, eb);
+            }
+            if (q < si.w) {
+                const double2v pa = prim_info(S, p + q);
+                add(pa, exp_f64(-pa.x * a.r2));
+            }
+        }
+        p += si.w;
+        const double X = Rl + 2.0 * Rd * gd, R2 = 2.0 * R;
+        if (si.y == 0) {
+            chi.push(R);
+            beta.push(X);
+        } else if (si.y == 1) {
+            chi.push(a.dx * R);
+            chi.push(a.dy * R);
+            chi.push(a.dz * R);
+            beta.push(a.dx * X + R2 * gJ[0]);
+            beta.push(a.dy * X + R2 * gJ[1]);
+            beta.push(a.dz * X + R2 * gJ[2]);
+        } else {  // xx, xy, xz, yy, yz, zz
+            chi.push(a.dx * a.dx * R);
+            chi.push(a.dx * a.dy * R);
+            chi.push(a.dx * a.dz * R);
+            chi.push(a.dy * a.dy * R);
+            chi.push(a.dy * a.dz * R);
+            chi.push(a.dz * a.dz * R);
+            beta.push(a.dx * a.dx * X + R2 * (1.0 + 2.0 * a.dx * gJ[0]));
+            beta.push(a.dx * a.dy * X + R2 * (a.dy * gJ[0] + a.dx * gJ[1]));
+            beta.push(a.dx * a.dz * X + R2 * (a.dz * gJ[0] + a.dx * gJ[2]));
+            beta.push(a.dy * a.dy * X + R2 * (1.0 + 2.0 * a.dy * gJ[1]));
+            beta.push(a.dy * a.dz * X + R2 * (a.dz * gJ[1] + a.dy * gJ[2]));
+            beta.push(a.dz * a.dz * X + R2 * (1.0 + 2.0 * a.dz * gJ[2]));
+        }
+        chi.flush();
+        beta.flush();
+    }
+    chi.finish(phi);
+    beta.finish(bvec);
 }
 
 // Pass 1 of the mixed FP32 form: AO values in FP32, one fused multiply-add
@@ -218,20 +338,23 @@ struct AoWeights {
     int lane, avail;
     double A[MB], B[MB][4];
 
-    __device__ __forceinline__ AoWeights(const DevSystem &S, int lane_, double *buf_, const double (&av)[NMO])
-        : buf(buf_), lane(lane_), avail(0) {
+    // xbuf: [NMO][64] for the exchange of av, free afterwards; ring: [kRing][64]
+    // (may overlap xbuf)
+    __device__ __forceinline__ AoWeights(const DevSystem &S, int lane_, double *xbuf, double *ring,
+                                         const double (&av)[NMO])
+        : buf(ring), lane(lane_), avail(0) {
         const int g = lane >> 4, j = lane & 15;
         Ap = const_tab(S.mo_a) + ((lane & 3) * 4 + g) * MB;
 #pragma unroll
         for (int s = 0; s < MB; ++s) A[s] = Ap[s];
         wave_sync();
 #pragma unroll
-        for (int m = 0; m < NMO; ++m) buf[m * kWave + lane] = av[m];
+        for (int m = 0; m < NMO; ++m) xbuf[m * kWave + lane] = av[m];
         wave_sync();
 #pragma unroll
         for (int s = 0; s < MB; ++s)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) B[s][t] = buf[(4 * s + g) * kWave + 16 * t + j];
+            for (int t = 0; t < 4; ++t) B[s][t] = xbuf[(4 * s + g) * kWave + 16 * t + j];
         wave_sync();
     }
     // rows up to `end` (at most kRing - 3 past the oldest still wanted)
@@ -259,7 +382,7 @@ template <>
 struct AoWeights<kFewMO> {
     const __attribute__((address_space(4))) double *C;
     const double (&av)[kFewMO];
-    __device__ __forceinline__ AoWeights(const DevSystem &S, int, double *, const double (&av_)[kFewMO])
+    __device__ __forceinline__ AoWeights(const DevSystem &S, int, double *, double *, const double (&av_)[kFewMO])
         : C(const_tab(S.mo)), av(av_) {}
     __device__ __forceinline__ void need(int) {}
     __device__ __forceinline__ double operator()(int mu) const {
@@ -285,7 +408,7 @@ template <int NMO, typename RT, bool VK>
 __device__ __forceinline__ void sigma_derivs(const DevSystem &S, int lane, double *buf, double x0, double x1,
                                              double x2, const double (&av)[NMO], double &g0, double &g1, double &g2,
                                              double &lap) {
-    AoWeights<NMO> w(S, lane, buf, av);
+    AoWeights<NMO> w(S, lane, buf, buf, av);
     int p = 0, mu = 0, atom = -1;
     double G0 = 0.0, G1 = 0.0, G2 = 0.0, L = 0.0, gd = 0.0;
     AtomGeo<RT> a;

@@ -191,17 +191,6 @@ __device__ __forceinline__ Lane make_lane(const DevSystem &S, int64_t wave_first
     return L;
 }
 
-// Determinant ratio det T[H,P] of one spin, rank k <= 2, from the walker's
-// T table (row = slot, column = MO, stride NMO).
-template <int NMO>
-__device__ __forceinline__ double ratio(const double *T, const int *d) {
-    const int k = d[0];
-    if (k == 0) return 1.0;
-    const double a = T[d[1] * NMO + d[3]];
-    if (k == 1) return a;
-    return a * T[d[2] * NMO + d[4]] - T[d[1] * NMO + d[4]] * T[d[2] * NMO + d[3]];
-}
-
 // Determinant ratio from a packed excitation code (rank | h1 << 2 |
 // h2 << 5 | p1 << 8 | p2 << 13); T rows of `ts` columns starting at column
 // c0 (particles are virtual orbitals, p >= c0).
@@ -346,15 +335,15 @@ __device__ __forceinline__ void stage_put(const Stage &st, int lane, int k, floa
     st.lo[lane * kRowB + k] = (__bf16)(v - (float)h);
 }
 
-// out[lane][o] = sum_k M[o][k] v_lane[k] for o < 16 NT (M = matrix mat).
+// out[lane][o] = sum_k M[o][k] v_lane[k] for o < 16 NT.
 template <int NT, int SPLIT>
-__device__ __forceinline__ void mfma_apply(const DevSystem &S, int mat, const Stage &st, int lane) {
+__device__ __forceinline__ void mfma_apply(const DevSystem &S, const Stage &st, int lane) {
     const int g = lane >> 4, j = lane & 15;
     bf16x8_t ahi[NT], alo[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const uint4 h = S.mfma_tab[((mat * 2 + t) * 2 + 0) * kWave + lane];
-        const uint4 l = S.mfma_tab[((mat * 2 + t) * 2 + 1) * kWave + lane];
+        const uint4 h = S.mfma_tab[(t * 2 + 0) * kWave + lane];
+        const uint4 l = S.mfma_tab[(t * 2 + 1) * kWave + lane];
         ahi[t] = __builtin_bit_cast(bf16x8_t, h);
         alo[t] = __builtin_bit_cast(bf16x8_t, l);
     }
@@ -415,7 +404,7 @@ __device__ __forceinline__ void mo_values_mfma(const DevSystem &S, int lane, voi
     }
     for (int k = mu; k < kStageK; ++k) stage_put(st, lane, k, 0.f);
     wave_sync();
-    mfma_apply<(NMO + 15) / 16, SPLIT>(S, 0, st, lane);
+    mfma_apply<(NMO + 15) / 16, SPLIT>(S, st, lane);
     wave_sync();
 #pragma unroll
     for (int m = 0; m < NMO; ++m) phi[m] = st.out[lane * kRowF + m];
@@ -711,11 +700,13 @@ __host__ __device__ inline int bf_pos_offset(const DevSystem &S);
 // the values a finite-difference kinetic energy needs.  RT is the arithmetic
 // of the AO evaluation and MF the MO contraction of pass 1 (FP64 when RT is
 // double).  FULLT: the full table layout (walker_lds<NMO, true>), which the
-// adjoint reads; otherwise the compact one.  VK: see fma_c.
+// adjoint reads, and its direction B into *bvec; otherwise the compact one.
+// VK: see fma_c.
 template <int NMO, typename RT, int MF = 0, bool EXPL = false, int BF = 0, bool PSI = false,
           bool FULLT = false, bool VK = false>
 __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, double *wsm, double &x0,
-                                            double &x1, double &x2, Core<NMO> &c, void *stage = nullptr) {
+                                            double &x1, double &x2, Core<NMO> &c, void *stage = nullptr,
+                                            double (*bvec)[NMO] = nullptr) {
     // the compact layout serves the low-rank Metropolis and evaluation
     // kernels (fewer LDS bytes per wave, more waves per CU)
     constexpr bool kFull = FULLT || EXPL || BF;
@@ -766,7 +757,18 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     // (the LDS stage of the contractions overlays the walkers' tables, whose
     // positions the pair loop has read)
     double a[NMO];
-    if constexpr (sizeof(RT) == sizeof(double)) {
+    if constexpr (FULLT) {
+        // the adjoint's direction B beside the values
+        wave_sync();
+        const double gj[3] = {gJ0, gJ1, gJ2};
+        mo_values_direction<NMO>(S, L.lane, (double *)stage, x0, x1, x2, gj, a, *bvec);
+        if constexpr (sizeof(RT) != sizeof(double)) {
+            float phi[NMO];
+            mo_values_f32<NMO>(S, L.lane, x0, x1, x2, phi);
+#pragma unroll
+            for (int m = 0; m < NMO; ++m) a[m] = double(phi[m]);
+        }
+    } else if constexpr (sizeof(RT) == sizeof(double)) {
         wave_sync();
         double phi[NMO];
         mo_values_f64<NMO, VK>(S, L.lane, (double *)stage, x0, x1, x2, phi);

@@ -68,3 +68,42 @@ def test_orbital_shapes(torch_cuda, qmc, oracle_mod, tag, shells, n_mo, n_up, n_
     fl, _, fe = [t.cpu().numpy() for t in s.eval(tX, precision="fp32")]
     assert np.median(np.abs(fl - lp)) < 1e-4 and np.median(np.abs(fe - el)) < 1e-2
     s.close()
+
+
+@pytest.mark.parametrize("tag,shells,n_mo,n_up,n_dn,basis,seed", CASES, ids=[c[0] for c in CASES])
+def test_orbital_shapes_adjoint(torch_cuda, qmc, oracle_mod, tag, shells, n_mo, n_up, n_dn, basis, seed):
+    """The adjoint's products over a walker's electrons and groups of four AOs
+    on the same shapes: every exponent and nuclear coordinate and a sample of
+    MO coefficients against the oracle's differences (h and h / 2,
+    extrapolated; 2e-6 of the gradient's scale, as in the adjoint's tests)."""
+    torch = torch_cuda
+    sysd = _system(shells, n_mo, n_up, n_dn, basis, seed, 1)
+    X = synth.init_walkers(sysd, 9, 60 + seed)
+    s = qmc.System(sysd, device=0)
+    print(f"adjoint shapes {tag}", flush=True)
+    dl, de, dlR, deR = [t.cpu().numpy() for t in s.grad(torch.from_numpy(X).cuda())]
+    el = oracle_mod.OracleSystem(sysd).eval(X)[2]
+
+    def differences(key, at):
+        out = []
+        for h in (1e-5, 5e-6):
+            r = []
+            for sign in (1, -1):
+                q = dict(sysd)
+                q[key] = np.array(q[key], dtype=np.float64)
+                q[key][at] += sign * h
+                r.append(oracle_mod.OracleSystem(q).eval(X))
+            out.append([(r[0][k] - r[1][k]) / (2 * h) for k in (0, 2)])
+        return [(4 * b - a) / 3 for a, b in zip(*out)]
+
+    n_prim, n_ao = sysd["prim_exp"].size, sysd["mo_coef"].shape[0]
+    rng = np.random.default_rng(seed)
+    checks = [("prim_exp", (p,), dl[:, p], de[:, p]) for p in range(n_prim)]
+    for mu, m in {(0, 0), (n_ao - 1, n_mo - 1)} | {tuple(v) for v in rng.integers(0, (n_ao, n_mo), (10, 2))}:
+        col = n_prim + mu * n_mo + m
+        checks.append(("mo_coef", (mu, m), dl[:, col], de[:, col]))
+    checks += [("R", (a, k), dlR[:, a, k], deR[:, a, k]) for a in range(2) for k in range(3)]
+    for key, at, gl, ge in checks:
+        for got, want in zip((gl, ge), differences(key, at)):
+            assert np.max(np.abs(got - want)) <= 2e-6 * max(1.0, np.abs(want).max(), np.abs(el).max()), (key, at)
+    s.close()
