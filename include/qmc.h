@@ -243,6 +243,16 @@ qmc_status qmc_eval_eloc_fd(qmc_system *sys, const double *d_X, int64_t W, doubl
 qmc_status qmc_grad(qmc_system *sys, int32_t precision, const double *d_X, int64_t W, double *d_dlogpsi,
                     double *d_deloc_dtheta, double *d_dlogpsi_dR, double *d_deloc_dR, void *stream);
 
+/* Products of the qmc_grad outputs with per-walker weights, the backward pass
+   of a scalar of log|Psi| and E_L: out[P + 3 n_atoms] = sum over walkers of
+   g_logpsi[w] (d_dlogpsi | d_dlogpsi_dR)[w] + g_eloc[w] (d_deloc_dtheta |
+   d_deloc_dR)[w], parameters first.  A walker of weight zero adds nothing, also
+   where its row is not finite.  d_work: qmc_vjp_work_bytes(sys, W) bytes. */
+qmc_status qmc_vjp(qmc_system *sys, const double *d_g_logpsi, const double *d_g_eloc, const double *d_dlogpsi,
+                   const double *d_deloc_dtheta, const double *d_dlogpsi_dR, const double *d_deloc_dR, int64_t W,
+                   double *d_work, double *d_out, void *stream);
+size_t qmc_vjp_work_bytes(const qmc_system *sys, int64_t W);
+
 /* Number of variational parameters in the qmc_grad layout. */
 int64_t qmc_param_count(const qmc_system *sys);
 

@@ -104,6 +104,14 @@ class Wavefunction:
             self._system = None
 
 
+def _readable(t) -> bool:
+    """Whether t's memory can be passed to a kernel (not under vmap and the like)."""
+    try:
+        return t.data_ptr() is not None
+    except RuntimeError:
+        return False
+
+
 class _PsiEloc(torch.autograd.Function):
     @staticmethod
     def forward(ctx, wf: Wavefunction, X, theta, R):
@@ -124,6 +132,12 @@ class _PsiEloc(torch.autograd.Function):
         W = X.shape[0]
         g_lp = torch.zeros(W, dtype=torch.float64, device=X.device) if g_lp is None else g_lp
         g_el = torch.zeros(W, dtype=torch.float64, device=X.device) if g_el is None else g_el
+
+        # the kernel's products are outside torch: only where no graph of this
+        # backward pass is recorded and the weights are tensors with memory
+        if not torch.is_grad_enabled() and _readable(g_lp) and _readable(g_el):
+            g_theta, g_R = ctx.system.vjp(g_lp.contiguous(), g_el.contiguous(), (dl, de, dlR, deR))
+            return (None, None, g_theta.cpu() if need_theta else None, g_R.cpu() if need_R else None)
 
         def vjp(g, J):
             # walkers that receive no gradient contribute nothing, even where

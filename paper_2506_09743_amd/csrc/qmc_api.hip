@@ -25,6 +25,10 @@ hipError_t launch_grad(const DevSystem &S, const double *X, int64_t W, double *d
                        double *deloc_dth, double *dlogpsi_dR, double *deloc_dR, int n_param, bool mixed,
                        hipStream_t st);
 size_t grad_lds_bytes(const DevSystem &S);
+int vjp_splits(int64_t W);
+hipError_t launch_vjp(const double *ga, const double *gb, const double *a0, const double *b0, int n0,
+                      const double *a1, const double *b1, int n1, int64_t W, double *work, double *out,
+                      hipStream_t st);
 size_t explicit_lds_bytes(const DevSystem &S);
 size_t backflow_lds_bytes(const DevSystem &S, bool low_rank);
 hipError_t launch_eval_fd(const DevSystem &S, const double *X, int64_t W, double h, double *LP, double *EL,
@@ -699,6 +703,25 @@ qmc_status qmc_grad(qmc_system *sys, int32_t precision, const double *d_X, int64
     if (!g.ok) return QMC_EDEVICE;
     hipError_t e = qmc::launch_grad(sys->S, d_X, W, d_dlogpsi, d_deloc_dtheta, d_dlogpsi_dR, d_deloc_dR,
                                     (int)sys->n_params, precision == QMC_MIXED_FP32, (hipStream_t)stream);
+    return e == hipSuccess ? QMC_OK : QMC_EDEVICE;
+}
+
+size_t qmc_vjp_work_bytes(const qmc_system *sys, int64_t W) {
+    if (!sys || W < 0) return 0;
+    return (size_t)qmc::vjp_splits(W) * (size_t)(sys->n_params + 3 * sys->S.n_atoms) * sizeof(double);
+}
+
+qmc_status qmc_vjp(qmc_system *sys, const double *d_g_logpsi, const double *d_g_eloc, const double *d_dlogpsi,
+                   const double *d_deloc_dtheta, const double *d_dlogpsi_dR, const double *d_deloc_dR, int64_t W,
+                   double *d_work, double *d_out, void *stream) {
+    if (!sys || W < 0 || W > (int64_t)0x7FFFFFFF || !d_work || !d_out) return QMC_EINVAL;
+    if (W > 0 && (!d_g_logpsi || !d_g_eloc || !d_dlogpsi || !d_deloc_dtheta || !d_dlogpsi_dR || !d_deloc_dR))
+        return QMC_EINVAL;
+    DeviceGuard g(sys->device);
+    if (!g.ok) return QMC_EDEVICE;
+    hipError_t e = qmc::launch_vjp(d_g_logpsi, d_g_eloc, d_dlogpsi, d_deloc_dtheta, (int)sys->n_params,
+                                   d_dlogpsi_dR, d_deloc_dR, 3 * sys->S.n_atoms, W, d_work, d_out,
+                                   (hipStream_t)stream);
     return e == hipSuccess ? QMC_OK : QMC_EDEVICE;
 }
 

@@ -23,7 +23,7 @@ PRECISIONS = {"fp64": QMC_FP64, "fp32": QMC_MIXED_FP32, "bf16": QMC_MIXED_BF16,
 
 # every symbol include/qmc.h declares
 EXPORTS = ("qmc_system_create", "qmc_system_destroy", "qmc_eval_psi_eloc", "qmc_metropolis_block",
-           "qmc_grad", "qmc_eval_eloc_fd", "qmc_param_count", "qmc_bytes_per_walker",
+           "qmc_grad", "qmc_vjp", "qmc_vjp_work_bytes", "qmc_eval_eloc_fd", "qmc_param_count", "qmc_bytes_per_walker",
            "qmc_reduce_accumulators", "qmc_status_string")
 # columns of the Metropolis accumulators [W][ACC_COLS]: sum E_L, sum E_L^2,
 # accepted steps, steps whose state had no finite log|Psi| or E_L
@@ -77,6 +77,10 @@ def lib():
         L.qmc_grad.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p,
                                C.c_void_p, C.c_void_p, C.c_void_p]
         L.qmc_grad.restype = C.c_int
+        L.qmc_vjp.argtypes = [C.c_void_p] * 7 + [C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p]
+        L.qmc_vjp.restype = C.c_int
+        L.qmc_vjp_work_bytes.argtypes = [C.c_void_p, C.c_int64]
+        L.qmc_vjp_work_bytes.restype = C.c_size_t
         L.qmc_eval_eloc_fd.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_double, C.c_void_p,
                                        C.c_void_p, C.c_void_p]
         L.qmc_eval_eloc_fd.restype = C.c_int
@@ -289,6 +293,20 @@ class System:
                torch.empty((W, A, 3), dtype=torch.float64, device=X.device)]
         qmc_grad(self.handle, X, *out, precision=PRECISIONS[precision])
         return tuple(out)
+
+    def vjp(self, g_logpsi, g_eloc, jac):
+        """(grad theta [P], grad R [A, 3]) on the device: the walkers' weights
+        g_logpsi and g_eloc [W] applied to the outputs of grad()."""
+        import torch
+        W, P, A = g_logpsi.shape[0], self.param_count, self.n_atoms
+        dl, de, dlR, deR = jac
+        out = torch.empty(P + 3 * A, dtype=torch.float64, device=dl.device)
+        work = torch.empty(lib().qmc_vjp_work_bytes(self.handle, W) // 8, dtype=torch.float64, device=dl.device)
+        _check(lib().qmc_vjp(self.handle, _dev_ptr(g_logpsi, "g_logpsi", (W,)), _dev_ptr(g_eloc, "g_eloc", (W,)),
+                             _dev_ptr(dl, "dlogpsi", (W, P)), _dev_ptr(de, "deloc_dtheta", (W, P)),
+                             _dev_ptr(dlR, "dlogpsi_dR", (W, A, 3)), _dev_ptr(deR, "deloc_dR", (W, A, 3)), W,
+                             _dev_ptr(work, "work"), _dev_ptr(out, "out"), _stream()), "qmc_vjp")
+        return out[:P], out[P:].view(A, 3)
 
     def metropolis(self, X, logpsi, sign, eloc, n_steps, sigma, seed, step0=0, walker_offset=0,
                    acc=None, precision="fp64"):
