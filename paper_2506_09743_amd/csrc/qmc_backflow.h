@@ -36,6 +36,10 @@
 // per configuration of its spin, its g_i and, per configuration of the
 // other spin, v_i = sum over its cross partners i' of Y_ii' g_i', so the
 // cross term of a determinant is the sum of g_i . v_i over all lanes.
+// CO, 81 determinants, 8192 walkers, a Metropolis step: 278 -> 207 us (MO
+// channels on the matrix cores, J blocks from a table).  What bounds it now:
+// one wave per SIMD at 512 registers, FP64 work, and moves between vector and
+// accumulation registers where the Y blocks are used.
 #pragma once
 
 namespace qmc {
@@ -47,24 +51,28 @@ __device__ __forceinline__ int lane_of(const DevSystem &S, int j) {
 }
 
 // LDS of one walker with backflow (doubles), from the walker's base.  A
-// shared region holds in turn the diagonal Jacobian blocks [LW][6] (while
-// the Y rows are built), the determinant tables of the configuration loop
-// (low-rank: the reference rows [2][nmax][NMO] = A0^-1 | T and pivot rows
+// shared region holds in turn the determinant tables of the configuration
+// loop (low-rank: the reference rows [2][nmax][NMO] = A0^-1 | T and pivot rows
 // [2][NMO]; explicit: inverse tables [2][G][8] and pivot rows [2][8]) and
 // the weighted g [LW][3] (at the end).  Then Mt rows [2][G][3][8], published
 // g [2][G][3] and per configuration (log|D|, sign, weight, L, scaled value)
-// [2][n_cfg_max][5]; the positions follow at bf_pos_offset.
+// [2][n_cfg_max][5]; the positions follow at bf_pos_offset.  Before all of
+// these the walker's Jacobian blocks J_ij, i >= j, packed by rows
+// [ne (ne + 1) / 2][6], take the same space, and between the two the wave's
+// AO rows of the MO stage (MoChannels), which reach past the positions: they
+// are written again after it.
 template <int NMO, bool LR>
 __host__ __device__ inline int bf_shared_size(const DevSystem &S) {
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const int dets = LR ? 2 * nmax * NMO + 2 * NMO : 2 * S.G * kMaxSpin + 2 * kMaxSpin;
-    const int a = 6 * S.LW > dets ? 6 * S.LW : dets;
-    return a > 3 * S.LW ? a : 3 * S.LW;
+    return dets > 3 * S.LW ? dets : 3 * S.LW;
 }
 
 template <int NMO, bool LR>
 __host__ __device__ inline int bf_table_size(const DevSystem &S) {
-    return bf_shared_size<NMO, LR>(S) + 2 * S.G * 3 * kMaxSpin + 2 * S.G * 3 + 10 * S.n_cfg_max;
+    const int t = bf_shared_size<NMO, LR>(S) + 2 * S.G * 3 * kMaxSpin + 2 * S.G * 3 + 10 * S.n_cfg_max;
+    const int blocks = 6 * (S.ne * (S.ne + 1) / 2);
+    return t > blocks ? t : blocks;
 }
 
 template <int NMO, bool LR>
@@ -76,52 +84,6 @@ __host__ __device__ inline int bf_pos_offset(const DevSystem &S) {
 template <int NMO, bool LR>
 __host__ __device__ inline int walker_lds_bf(const DevSystem &S) {
     return bf_pos_offset<NMO, LR>(S) + 3 * S.LW;
-}
-
-// In-place Gauss-Jordan of the spin group's reference rows [A0 | Phi]
-// (NMO entries per lane, reference orbitals in columns 0..n-1): afterwards
-// the row of slot s holds A0^-1[s][slot(e)] in the columns < n and
-// T[s][v] = (A0^-1 Phi)[s][v] in the others.  Every lane of the block runs
-// the same steps (block barriers inside).
-template <int NMO>
-__device__ __forceinline__ void reference_gauss_jordan(const DevSystem &S, const Lane &L, double (&a)[NMO], int nmax,
-                                                       double *piv_row, int &slot, double &dprod, bool &singular) {
-    constexpr int JMAX = kMaxSpin < NMO ? kMaxSpin : NMO;
-    bool done = !L.active;
-    slot = -1;
-    dprod = 1.0;
-    singular = false;
-#pragma unroll
-    for (int j = 0; j < JMAX; ++j) {
-        if (j >= nmax) break;
-        const bool work = j < L.nsig;
-        double cand = (work && !done) ? fabs(a[j]) : -1.0;
-        int cl = L.i;
-        span_argmax(cand, cl, S.G);
-        const bool ok = work && cand > 0.0;
-        if (work && !ok) singular = true;
-        const bool is_piv = ok && L.active && L.i == cl;
-        if (is_piv) {
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) piv_row[m] = a[m];
-            const double inv = 1.0 / a[j];
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) a[m] *= inv;
-            a[j] = inv;
-            done = true;
-            slot = j;
-        }
-        __syncthreads();
-        const double piv = ok ? piv_row[j] : 0.0;
-        if (work) dprod *= piv;
-        if (ok && L.active && !is_piv) {
-            const double f = a[j] / piv;
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) a[m] -= f * piv_row[m];
-            a[j] = -f;
-        }
-        __syncthreads();
-    }
 }
 
 // Symmetric 3 x 3 block (xx, xy, xz, yy, yz, zz) of J_ij for i != j from the
@@ -143,127 +105,256 @@ __device__ __forceinline__ void jblock_pair(double om, const double *pi, const d
 // qr = R'/r and wr = (R'' - R'/r) / r^2.  Slater f = c r^kn exp(-zeta r):
 // R' = f g, R'' = f (g^2 - kn/r^2), g = kn/r - zeta; Gaussian
 // f = c exp(-alpha r^2): R'/r = -2 alpha f, (R'' - R'/r)/r^2 = 4 alpha^2 f.
+// The sums over primitives are of f, f g and f g^2 (or with alpha for g).
 __device__ __forceinline__ void shell_radial_h(const DevSystem &S, int p, int np, int kn, double r, double r2,
                                                double rinv, double &R, double &qr, double &wr) {
-    R = 0.0;
-    qr = 0.0;
-    wr = 0.0;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     if (S.basis == 0) {
         double rk = 1.0;
         for (int t = 0; t < kn; ++t) rk *= r;
         const double kr = double(kn) * rinv;
         for (int q = 0; q < np; ++q) {
-            const double2 pe = S.prims[p + q];
-            const double f = pe.y * rk * exp_f64(-pe.x * r);
-            const double g = kr - pe.x;
-            R += f;
-            qr += f * g * rinv;
-            wr += f * (g * g - kr * rinv - g * rinv) * rinv * rinv;
+            const double2v pe = prim_info(S, p + q);
+            const double f = pe.y * rk * exp_f64(-pe.x * r), g = kr - pe.x, fg = f * g;
+            s0 += f;
+            s1 += fg;
+            s2 += fg * g;
         }
+        R = s0;
+        qr = s1 * rinv;
+        wr = (s2 - kr * rinv * s0 - qr) * rinv * rinv;
     } else {
-        for (int q = 0; q < np; ++q) {
-            const double2 pe = S.prims[p + q];
-            const double f = pe.y * exp_f64(-pe.x * r2);
-            R += f;
-            qr -= 2.0 * pe.x * f;
-            wr += 4.0 * pe.x * pe.x * f;
+        auto add = [&](double2v pe, double e) {
+            const double f = pe.y * e, fa = f * pe.x;
+            s0 += f;
+            s1 += fa;
+            s2 += fa * pe.x;
+        };
+        int q = 0;  // two at a time: one scalar load and two independent exponentials
+        for (; q + 1 < np; q += 2) {
+            const double2v pa = prim_info(S, p + q), pb = prim_info(S, p + q + 1);
+            const double ea = exp_f64(-pa.x * r2), eb = exp_f64(-pb.x * r2);
+            add(pa, ea);
+            add(pb, eb);
+        }
+        if (q < np) {
+            const double2v pa = prim_info(S, p + q);
+            add(pa, exp_f64(-pa.x * r2));
+        }
+        R = s0;
+        qr = -2.0 * s1;
+        wr = 4.0 * s2;
+    }
+}
+
+// NC channels of AO rows contracted with the MO coefficients, the way MoRows
+// does one: out[c][m] = sum_mu C[mu][m] row_mu[c].  buf: mo_channel_lds<NMO, NC>
+// bytes of LDS, a ring of kRows rows per channel (at most 3 + 6 are pending).
+template <int NMO, int NC>
+struct MoChannels {
+    static constexpr int MB = NMO / 4, kRows = 12;
+    double *buf;
+    const __attribute__((address_space(4))) double *Ap;
+    int lane, wr, rd, pending;  // next row to write, to contract, rows between
+    double A[MB], acc[NC][MB][4];
+
+    __device__ __forceinline__ MoChannels(const DevSystem &S, int lane_, double *buf_)
+        : buf(buf_), lane(lane_), wr(0), rd(0), pending(0) {
+        Ap = const_tab(S.mo_a) + ((lane >> 4) * 4 + (lane & 3)) * MB;
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            A[m] = Ap[m];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[c][m][t] = 0.0;
         }
     }
+    __device__ __forceinline__ void push(const double (&v)[NC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) buf[(c * kRows + wr) * kWave + lane] = v[c];
+        wr = wr + 1 == kRows ? 0 : wr + 1;
+        ++pending;
+    }
+    __device__ __forceinline__ void contract() {
+        const int g = lane >> 4, j = lane & 15;
+        wave_sync();
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            double B[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) B[t] = buf[(c * kRows + rd + g) * kWave + 16 * t + j];
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[c][m][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[m], B[t], acc[c][m][t], 0, 0, 0);
+        }
+        rd = rd + 4 == kRows ? 0 : rd + 4;
+        pending -= 4;
+        Ap += 4 * NMO;
+#pragma unroll
+        for (int m = 0; m < MB; ++m) A[m] = Ap[m];
+    }
+    __device__ __forceinline__ void flush() {  // at the end of each shell
+        while (pending >= 4) contract();
+    }
+    __device__ __forceinline__ void finish(double *out) {  // out[c * NMO + m]
+        const int g = lane >> 4, j = lane & 15;
+        if (pending > 0) {
+            const double zero[NC] = {};
+            while (pending < 4) push(zero);  // the table's rows are zero there
+            contract();
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            wave_sync();
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) buf[(4 * m + g) * kWave + 16 * t + j] = acc[c][m][t];
+            wave_sync();
+#pragma unroll
+            for (int m = 0; m < NMO; ++m) out[c * NMO + m] = buf[m * kWave + lane];
+        }
+        wave_sync();
+    }
+};
+
+// The same on the vector unit (kFewMO).
+template <int NC>
+struct MoChannels<kFewMO, NC> {
+    static constexpr int kRows = 0;
+    const __attribute__((address_space(4))) double *row;
+    double acc[NC][kFewMO];
+
+    __device__ __forceinline__ MoChannels(const DevSystem &S, int, double *) : row(const_tab(S.mo)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int m = 0; m < kFewMO; ++m) acc[c][m] = 0.0;
+    }
+    __device__ __forceinline__ void push(const double (&v)[NC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int m = 0; m < kFewMO; ++m) acc[c][m] += v[c] * row[m];
+        row += kFewMO;
+    }
+    __device__ __forceinline__ void flush() {}
+    __device__ __forceinline__ void finish(double *out) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int m = 0; m < kFewMO; ++m) out[c * kFewMO + m] = acc[c][m];
+    }
+};
+
+// All five channels are contracted in one pass over the shells while their
+// accumulators (10 NMO registers) fit beside the Y blocks; wider tables take
+// value and psi, then the gradient.
+template <int NMO>
+constexpr int bf_channels() { return NMO <= 20 ? 5 : 3; }
+
+template <int NMO>
+constexpr size_t bf_orbital_lds_bytes() {
+    return (size_t)bf_channels<NMO>() * MoChannels<NMO, 1>::kRows * kWave * sizeof(double);
 }
 
 // Channels C0 .. C0 + NC - 1 of the lane's MO table at q in one pass over
 // the shells: channel 0 value, 1 psi (Hessian contracted with Y_ii plus
 // gradient dotted with k_i), 2..4 the gradient.  For chi = P(d) R(r):
 //   d_a chi = R d_a P + P qr d_a,
-//   H chi : Y = R (dd P : Y) + 2 qr grad P^T Y d + P (qr tr Y + wr d^T Y d).
-// Returns sum_mu C[mu][m] (channel C0 + c of chi_mu) in out[c][m].
+//   psi = R dd P : Y + grad P . u + P w1,  u = R k + 2 qr Y d,
+//   w1 = qr (tr Y + k . d) + wr d^T Y d.
+// Writes sum_mu C[mu][m] (channel C0 + c of chi_mu) to out[c * NMO + m].  Every
+// lane of the wave must call it.  Like the other orbital stages this is bound
+// by FP64 vector work; the rows of C used to come through the scalar cache once
+// per channel and AO.  CO: 112 k -> 38 k cycles of a wave.
 template <int NMO, int C0, int NC>
-__device__ __forceinline__ void mo_channels_bf(const DevSystem &S, double q0, double q1, double q2,
-                                               const double (&Y)[6], double k0, double k1, double k2,
-                                               double (&out)[NC][NMO]) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int m = 0; m < NMO; ++m) out[c][m] = 0.0;
-    const double *crow = S.mo;
+__device__ __forceinline__ void mo_channels_bf(const DevSystem &S, int lane, double *buf, double q0, double q1,
+                                               double q2, const double (&Y)[6], double k0, double k1, double k2,
+                                               double *out) {
+    MoChannels<NMO, NC> rows(S, lane, buf);
     int p = 0, atom = -1;
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0, r = 0.0, r2 = 0.0, rinv = 0.0;
-    double Yd0 = 0.0, Yd1 = 0.0, Yd2 = 0.0, dYd = 0.0;
-    const double trY = Y[0] + Y[3] + Y[5];
+    double r = 0.0, r2 = 0.0, rinv = 0.0, dYd = 0.0, kd = 0.0;
+    double d[3] = {0.0, 0.0, 0.0}, Yd[3] = {0.0, 0.0, 0.0};
+    const double trY = Y[0] + Y[3] + Y[5], kk[3] = {k0, k1, k2};
     for (int sh = 0; sh < S.n_shells; ++sh) {
-        const int4 si = S.shells[sh];
+        const int4v si = shell_info(S, sh);
         if (si.x != atom) {
             atom = si.x;
-            const double *A = S.atoms + 4 * atom;
-            d0 = q0 - A[0];
-            d1 = q1 - A[1];
-            d2 = q2 - A[2];
-            r2 = d0 * d0 + d1 * d1 + d2 * d2;
-            r = sqrt(r2);
-            rinv = 1.0 / r;
-            Yd0 = Y[0] * d0 + Y[1] * d1 + Y[2] * d2;
-            Yd1 = Y[1] * d0 + Y[3] * d1 + Y[4] * d2;
-            Yd2 = Y[2] * d0 + Y[4] * d1 + Y[5] * d2;
-            dYd = d0 * Yd0 + d1 * Yd1 + d2 * Yd2;
+            const auto *A = const_tab(S.atoms) + 4 * atom;
+            d[0] = q0 - A[0];
+            d[1] = q1 - A[1];
+            d[2] = q2 - A[2];
+            r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+            if (S.basis == 0) {
+                r = sqrt(r2);
+                rinv = 1.0 / r;
+            }
+            Yd[0] = Y[0] * d[0] + Y[1] * d[1] + Y[2] * d[2];
+            Yd[1] = Y[1] * d[0] + Y[3] * d[1] + Y[4] * d[2];
+            Yd[2] = Y[2] * d[0] + Y[4] * d[1] + Y[5] * d[2];
+            dYd = d[0] * Yd[0] + d[1] * Yd[1] + d[2] * Yd[2];
+            kd = d[0] * kk[0] + d[1] * kk[1] + d[2] * kk[2];
         }
         double R, qr, wr;
         shell_radial_h(S, p, si.w, si.z, r, r2, rinv, R, qr, wr);
         p += si.w;
-        const int nc = (si.y + 1) * (si.y + 2) / 2;
-        for (int c = 0; c < nc; ++c) {
-            double P, P0, P1, P2, PY;  // monomial, gradient, dd P : Y
-            if (si.y == 0) {
-                P = 1.0;
-                P0 = P1 = P2 = PY = 0.0;
-            } else if (si.y == 1) {
-                P = c == 0 ? d0 : (c == 1 ? d1 : d2);
-                P0 = c == 0 ? 1.0 : 0.0;
-                P1 = c == 1 ? 1.0 : 0.0;
-                P2 = c == 2 ? 1.0 : 0.0;
-                PY = 0.0;
-            } else {
-                // xx, xy, xz, yy, yz, zz: d_a d_b (x_u x_v) = delta_au delta_bv + delta_av delta_bu
-                const int iu = (c < 3) ? 0 : (c < 5 ? 1 : 2);
-                const int iv = (c == 0) ? 0 : (c == 1 || c == 3) ? 1 : 2;
-                const double u = iu == 0 ? d0 : (iu == 1 ? d1 : d2);
-                const double v = iv == 0 ? d0 : (iv == 1 ? d1 : d2);
-                P = u * v;
-                P0 = (iu == 0 ? v : 0.0) + (iv == 0 ? u : 0.0);
-                P1 = (iu == 1 ? v : 0.0) + (iv == 1 ? u : 0.0);
-                P2 = (iu == 2 ? v : 0.0) + (iv == 2 ? u : 0.0);
-                const int yi = iu == 0 ? iv : (iu == 1 ? 2 + iv : 5);  // packed Y index of (u, v), u <= v
-                PY = 2.0 * Y[yi];
-            }
-            const double g0 = R * P0 + P * qr * d0, g1 = R * P1 + P * qr * d1, g2 = R * P2 + P * qr * d2;
-            double val[NC];
+        double u[3], qd[3];
 #pragma unroll
-            for (int ch = 0; ch < NC; ++ch) {
-                const int comp = C0 + ch;
-                if (comp == 0) val[ch] = P * R;
-                else if (comp == 1)
-                    val[ch] = R * PY + 2.0 * qr * (P0 * Yd0 + P1 * Yd1 + P2 * Yd2) + P * (qr * trY + wr * dYd) +
-                              g0 * k0 + g1 * k1 + g2 * k2;
-                else val[ch] = comp == 2 ? g0 : (comp == 3 ? g1 : g2);
-            }
-#pragma unroll
-            for (int m = 0; m < NMO; ++m)
-#pragma unroll
-                for (int ch = 0; ch < NC; ++ch) out[ch][m] += val[ch] * crow[m];
-            crow += S.nmo_pad;
+        for (int t = 0; t < 3; ++t) {
+            u[t] = R * kk[t] + 2.0 * qr * Yd[t];
+            qd[t] = qr * d[t];
         }
+        const double w1 = qr * (trY + kd) + wr * dYd;
+        // value, psi and gradient to the rows, the channels asked for
+        auto put = [&](double v, double psi, double g0, double g1, double g2) {
+            const double all[5] = {v, psi, g0, g1, g2};
+            double o[NC];
+#pragma unroll
+            for (int ch = 0; ch < NC; ++ch) o[ch] = all[C0 + ch];
+            rows.push(o);
+        };
+        if (si.y == 0) {
+            put(R, w1, qd[0], qd[1], qd[2]);
+        } else if (si.y == 1) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                put(d[t] * R, u[t] + d[t] * w1, d[t] * qd[0] + (t == 0 ? R : 0.0), d[t] * qd[1] + (t == 1 ? R : 0.0),
+                    d[t] * qd[2] + (t == 2 ? R : 0.0));
+        } else {  // xx, xy, xz, yy, yz, zz: d_a d_b (x_i x_j) = delta_ai delta_bj + delta_aj delta_bi
+            const double Rd[3] = {R * d[0], R * d[1], R * d[2]};
+            const double R2 = 2.0 * R;
+            int yi = 0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = i; j < 3; ++j, ++yi) {
+                    const double P = d[i] * d[j];
+                    double g[3];
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+                        g[t] = P * qd[t] + ((i == t ? Rd[j] : 0.0) + (j == t ? Rd[i] : 0.0));
+                    put(P * R, R2 * Y[yi] + (d[j] * u[i] + d[i] * u[j]) + P * w1, g[0], g[1], g[2]);
+                }
+        }
+        rows.flush();
     }
+    rows.finish(out);
 }
 
 // LR: configurations from the reference by the rank <= 2 update of
 // eq. table (only A0 is factorised); otherwise every configuration is
 // factorised on its own.
 template <int NMO, bool LR, int CAP>
-__device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L, double *wsm, const double *sPos,
-                                              double x0, double x1, double x2, Core<NMO> &c) {
+__device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L, double *wsm, double *sPos,
+                                              double x0, double x1, double x2, double *buf, Core<NMO> &c) {
     const int LW = S.LW, nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const double om = S.bf_omega;
     const int G = S.G;
-    double *sJd = wsm;                                      // [LW][6] (shared region)
+    double *sB = wsm;                                       // [ne (ne + 1) / 2][6] (at the start)
     double *sInv = wsm;                                     // [2][G][8] (shared region, explicit)
     double *sPv = sInv + 2 * G * kMaxSpin;                  // [2][8]
     double *sRef = wsm;                                     // [2][nmax][NMO] (shared region, low-rank)
@@ -279,16 +370,29 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     const int ncfg_g = L.grp == 0 ? S.n_cfg_up : S.n_cfg_dn;
     const int ncfg_o = L.grp == 0 ? S.n_cfg_dn : S.n_cfg_up;
     const int nsig_o = L.grp == 0 ? S.n_dn : S.n_up;
-    const int gb_own = L.grp * S.G, gb_oth = (1 - L.grp) * S.G;  // walker-local first lanes
+    const int e_own = L.grp ? S.n_up : 0, e_oth = L.grp ? 0 : S.n_up;  // first electrons
     const int ncmax = S.n_cfg_up > S.n_cfg_dn ? S.n_cfg_up : S.n_cfg_dn;
     const double xs[3] = {x0, x1, x2};
 
-    __syncthreads();  // the Jastrow stage's tables are no longer read
+    wave_sync();  // the Jastrow stage's tables are no longer read
 
     // ---- transformed position, diagonal Jacobian block, k_i -------------
     double q0 = x0, q1 = x1, q2 = x2;
     double Jd[6] = {1.0, 0.0, 0.0, 1.0, 0.0, 1.0};
     double k0 = 0.0, k1 = 0.0, k2 = 0.0;
+    auto tri = [](int i) { return i * (i + 1) / 2; };
+    auto put_block = [&](int at, const double (&B)[6], double sign) {
+#pragma unroll
+        for (int t = 0; t < 6; t += 2) *(double2 *)(sB + 6 * at + t) = make_double2(sign * B[t], sign * B[t + 1]);
+    };
+    auto get_block = [&](int at, double (&B)[6]) {
+#pragma unroll
+        for (int t = 0; t < 6; t += 2) {
+            const double2 v = *(const double2 *)(sB + 6 * at + t);
+            B[t] = v.x;
+            B[t + 1] = v.y;
+        }
+    };
     if (L.active) {
         for (int j = 0; j < S.ne; ++j) {
             if (j == L.e) continue;
@@ -300,21 +404,19 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
             q1 += s * u1;
             q2 += s * u2;
             const double h0 = u0 * rinv, h1 = u1 * rinv, h2 = u2 * rinv;
-            Jd[0] += s * (1.0 - h0 * h0);
-            Jd[1] -= s * h0 * h1;
-            Jd[2] -= s * h0 * h2;
-            Jd[3] += s * (1.0 - h1 * h1);
-            Jd[4] -= s * h1 * h2;
-            Jd[5] += s * (1.0 - h2 * h2);
+            const double B[6] = {s * (1.0 - h0 * h0), -s * h0 * h1, -s * h0 * h2,
+                                 s * (1.0 - h1 * h1), -s * h1 * h2, s * (1.0 - h2 * h2)};  // -J_ij
+#pragma unroll
+            for (int t = 0; t < 6; ++t) Jd[t] += B[t];
+            if (j < L.e) put_block(tri(L.e) + j, B, -1.0);
             const double t = -4.0 * s * rinv * rinv;
             k0 += t * u0;
             k1 += t * u1;
             k2 += t * u2;
         }
     }
-#pragma unroll
-    for (int t = 0; t < 6; ++t) sJd[6 * L.lw + t] = Jd[t];
-    __syncthreads();
+    if (L.active) put_block(tri(L.e) + L.e, Jd, 1.0);
+    wave_sync();
 
     // ---- Y blocks: Y_{e,j'} = sum_m J_em J_j'm over all electrons m --------
     // Both traces summed over a spin's pairs are symmetric in (i, i'), so
@@ -323,7 +425,9 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     // cross term are split between the two groups by the cyclic offset
     // (i' - i) mod M, M = max(n_up, n_dn): below ceil(M/2) the up lane
     // takes the pair, otherwise the down lane.  Every block index is static,
-    // so the blocks stay in registers.
+    // so the blocks stay in registers.  The J blocks come from the packed table:
+    // forming each again for every product of the sums took 71 k cycles of a wave
+    // (CO), the table takes 38 k.
     constexpr int kHalf = kMaxSpin / 2;
     const int mspin = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const int ncross = L.grp == 0 ? (mspin + 1) / 2 : mspin / 2;
@@ -350,29 +454,20 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     }
     if (L.active) {
         for (int m = 0; m < S.ne; ++m) {
-            const int lm = lane_of(S, m);
             double A[6];
-            if (m == L.e) {
-#pragma unroll
-                for (int t = 0; t < 6; ++t) A[t] = Jd[t];
-            } else {
-                jblock_pair(om, xs, sPos + 3 * lm, A);
-            }
+            get_block(m > L.e ? tri(m) + L.e : tri(L.e) + m, A);
             const double a[9] = {A[0], A[1], A[2], A[1], A[3], A[4], A[2], A[4], A[5]};
 #pragma unroll
             for (int d = 0; d < 2 * kHalf + 1; ++d) {
                 const int ip = d <= kHalf ? own_p[d] : oth_p[d - kHalf - 1];
                 if (ip < 0) continue;
-                const int lp = (d <= kHalf ? gb_own : gb_oth) + ip;
+                const int ep = (d <= kHalf ? e_own : e_oth) + ip;
                 double B[6];
                 if (d == 0) {
 #pragma unroll
                     for (int t = 0; t < 6; ++t) B[t] = A[t];
-                } else if (lp == lm) {
-#pragma unroll
-                    for (int t = 0; t < 6; ++t) B[t] = sJd[6 * lp + t];
                 } else {
-                    jblock_pair(om, sPos + 3 * lp, sPos + 3 * lm, B);
+                    get_block(m > ep ? tri(m) + ep : tri(ep) + m, B);
                 }
                 // y += A B with the full 3 x 3 forms of the two symmetric blocks
                 const double b[9] = {B[0], B[1], B[2], B[1], B[3], B[4], B[2], B[4], B[5]};
@@ -401,26 +496,18 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
         } else {
             q0 = q1 = q2 = 100.0;  // a far point keeps idle lanes finite
         }
-        // two passes over the shells: value and psi, then the gradient
-        {
-            double o[2][NMO];
-            mo_channels_bf<NMO, 0, 2>(S, q0, q1, q2, Yii, k0, k1, k2, o);
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int m = 0; m < NMO; ++m) tab[c * NMO + m] = o[c][m];
+        wave_sync();  // every lane has read the J blocks
+        if constexpr (bf_channels<NMO>() == 5) {
+            mo_channels_bf<NMO, 0, 5>(S, L.lane, buf, q0, q1, q2, Yii, k0, k1, k2, tab);
+        } else {
+            mo_channels_bf<NMO, 0, 2>(S, L.lane, buf, q0, q1, q2, Yii, k0, k1, k2, tab);
+            mo_channels_bf<NMO, 2, 3>(S, L.lane, buf, q0, q1, q2, Yii, k0, k1, k2, tab + 2 * NMO);
         }
-        {
-            double o[3][NMO];
-            mo_channels_bf<NMO, 2, 3>(S, q0, q1, q2, Yii, k0, k1, k2, o);
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int m = 0; m < NMO; ++m) tab[(2 + c) * NMO + m] = o[c][m];
-        }
+        sPos[3 * L.lw + 0] = x0;
+        sPos[3 * L.lw + 1] = x1;
+        sPos[3 * L.lw + 2] = x2;
+        wave_sync();
     }
-
-    __syncthreads();  // every lane has read the shared region's J blocks
 
     // ---- low-rank: the reference once --------------------------------------
     // Reference rows [A0 | Phi] by Gauss-Jordan; then per lane the reference
@@ -441,10 +528,10 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
         double a[NMO];
 #pragma unroll
         for (int m = 0; m < NMO; ++m) a[m] = L.active ? tab[m] : 0.0;
-        int slot;
+        int slot, inv_cnt;
         double dprod;
-        reference_gauss_jordan<NMO>(S, L, a, nmax, sPvN + L.grp * NMO, slot, dprod, ref_sing);
-        ref_sgn = group_parity(S, L, slot) * (dprod < 0.0 ? -1.0 : 1.0);
+        eliminate<NMO>(S, L, a, nmax, sPvN + L.grp * NMO, slot, inv_cnt, dprod, ref_sing);
+        ref_sgn = ((span_sum_i(inv_cnt, S.G) & 1) ? -1.0 : 1.0) * (dprod < 0.0 ? -1.0 : 1.0);
         ref_log = log(fabs(dprod));
         if (L.active && slot >= 0) {
 #pragma unroll
@@ -452,7 +539,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
         }
 #pragma unroll
         for (int ip = 0; ip < kMaxSpin; ++ip) rslots[ip] = ip < S.G ? __shfl(slot, L.gbase + ip) : -1;
-        __syncthreads();
+        wave_sync();
 #pragma unroll
         for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -507,7 +594,9 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
 
     // ---- every configuration of each spin --------------------------------
     // per-configuration rows of this lane (CAP >= the system's configurations per spin)
-    double gtab[CAP * 3], vtab[CAP * 3];
+    // of the up and of the down spin: g for the lane's own spin, v for the other
+    double tabs[2][CAP * 3];
+    double *gtab = tabs[L.grp], *vtab = tabs[1 - L.grp];
     for (int q = 0; q < ncmax; ++q) {
         const bool live = q < ncfg_g;
         double t1 = 0.0, clog = -INFINITY, csgn = 0.0;
@@ -602,7 +691,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
             int slots[kMaxSpin];
 #pragma unroll
             for (int ip = 0; ip < kMaxSpin; ++ip) slots[ip] = ip < S.G ? __shfl(slot, L.gbase + ip) : -1;
-            __syncthreads();
+            wave_sync();
 
             // Mt row, g_i and the first trace; A^-1[k][i'] = inv[k][slot(i')]
             ok = live && L.active && !singular;
@@ -644,7 +733,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
             gp[1] = g1;
             gp[2] = g2;
         }
-        __syncthreads();
+        wave_sync();
 
         // third trace and |grad log D|^2 over this lane's share of the
         // spin's pairs; partial v for the other spin's configuration q
@@ -698,7 +787,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
             cfg_g[5 * q + 1] = singular ? 0.0 : csgn;
             cfg_g[5 * q + 3] = singular ? 0.0 : Lc;
         }
-        __syncthreads();
+        wave_sync();
     }
 
     // ---- Sigma, configuration weights ------------------------------------
@@ -714,7 +803,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
         double *own = sCfg + 5 * (sp * S.n_cfg_max + (sp ? q - S.n_cfg_up : q));
         own[4] = none ? 0.0 : own[1] * exp(own[0] - (sp ? md : mu));
     }
-    __syncthreads();
+    wave_sync();
     double Sp = 0.0;
     for (int n = L.lw; n < S.n_det_x; n += LW) {
         const int2 dc = S.det_cfg[n];
@@ -735,7 +824,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
         }
         own[2] = acc * own[4] * Sinv;
     }
-    __syncthreads();
+    wave_sync();
 
     // ---- sum_c W_c L_c, cross term, weighted g ----------------------------
     double lp = 0.0;
@@ -747,19 +836,26 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     double cr = 0.0, gb0 = 0.0, gb1 = 0.0, gb2 = 0.0;
     if (L.active && !zero) {
         // cross term: every lane adds g_i . v_i over its share of the pairs
-        // for each determinant.  The loop runs over the determinants in the
-        // same order on every lane, unrolled so that several determinants'
-        // loads are in flight at once.
+        // for each determinant, in the same order on every lane.  The up
+        // configuration's vector is read once per run of determinants that
+        // share it; four determinants' loads are in flight at once.
         const double *scu = sCfg + 4, *scd = sCfg + 5 * S.n_cfg_max + 4;
         const auto *det_cfg = const_tab((const int *)S.det_cfg);  // (up, down) configuration pairs
         const auto *ci_x = const_tab(S.ci_x);
+        int last = -1;
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0, su = 0.0;
 #pragma unroll 4
         for (int n = 0; n < S.n_det_x; ++n) {
             const int cu = det_cfg[2 * n], cd = det_cfg[2 * n + 1];
-            const double w = ci_x[n] * scu[5 * cu] * scd[5 * cd];
-            const int own = L.grp ? cd : cu, oth = L.grp ? cu : cd;
-            const double gv = gtab[3 * own] * vtab[3 * oth] + gtab[3 * own + 1] * vtab[3 * oth + 1] +
-                              gtab[3 * own + 2] * vtab[3 * oth + 2];
+            if (cu != last) {
+                last = cu;
+                a0 = tabs[0][3 * cu];
+                a1 = tabs[0][3 * cu + 1];
+                a2 = tabs[0][3 * cu + 2];
+                su = scu[5 * cu];
+            }
+            const double w = ci_x[n] * su * scd[5 * cd];
+            const double gv = a0 * tabs[1][3 * cd] + a1 * tabs[1][3 * cd + 1] + a2 * tabs[1][3 * cd + 2];
             cr += w != 0.0 ? w * gv : 0.0;  // a vanishing weight drops the term whatever g is
         }
         cr *= Sinv;
@@ -777,7 +873,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     sGb[3 * L.lw + 1] = gb1;
     sGb[3 * L.lw + 2] = gb2;
     const double lapS = walker_sum(lp + 2.0 * cr, LW);
-    __syncthreads();
+    wave_sync();
 
     // ---- grad Sigma / Sigma at this electron: sum_i J_ie gbar_i -----------
     double G0 = 0.0, G1 = 0.0, G2 = 0.0;

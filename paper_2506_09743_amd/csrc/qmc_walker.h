@@ -690,11 +690,83 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
 // determinants (eq. nabla_d), every configuration explicitly.  Every lane of
 // the block must call it.  sPos holds the walker's bare positions.
 template <int NMO, bool LR, int CAP>
-__device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L, double *wsm, const double *sPos,
-                                              double x0, double x1, double x2, Core<NMO> &c);
+__device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L, double *wsm, double *sPos,
+                                              double x0, double x1, double x2, double *buf, Core<NMO> &c);
 
 template <int NMO, bool LR>
 __host__ __device__ inline int bf_pos_offset(const DevSystem &S);
+
+// In-place Gauss-Jordan of the spin group's reference matrix, a row per lane
+// (NMO entries, this electron's MO values).  Pivot column j (reference orbital
+// j after the create-time column permutation) is overwritten by the inverse,
+// so at the end the row of slot s holds A0^-1[s][slot(e)] in the columns < n
+// and T[s][v] = (A0^-1 Phi)[s][v] in the virtual columns.
+// A step's chain is: largest |a[j]| of the rows left, that row through LDS, one
+// reciprocal, one multiply-add per column.  The largest is taken on one word
+// per lane (the upper bits of |a[j]|, then the lower lane), three cross-lane
+// maxima.  inv_cnt: inversions of the row permutation (slot s <- electron row)
+// at this lane, to be summed over the group.  piv_row: NMO doubles of LDS per
+// group, 16-byte aligned.
+template <int NMO>
+__device__ __forceinline__ void eliminate(const DevSystem &S, const Lane &L, double (&a)[NMO], int nmax,
+                                          double *piv_row, int &slot, int &inv_cnt, double &dprod, bool &singular) {
+    constexpr int JMAX = kMaxSpin < NMO ? kMaxSpin : NMO;
+    bool done = !L.active;
+    slot = -1;
+    inv_cnt = 0;
+    dprod = 1.0;
+    singular = false;
+#pragma unroll
+    for (int j = 0; j < JMAX; ++j) {
+        if (j >= nmax) break;
+        const bool work = j < L.nsig;
+        uint32_t key = 0;  // 8 or more for a non-zero candidate
+        if (work && !done && a[j] != 0.0) {
+            const uint32_t hi = (uint32_t)__double2hiint(a[j]) & 0x7FFFFFF8u;
+            key = (hi > 8u ? hi : 8u) | (uint32_t)(7 - L.i);
+        }
+        key = span_max_u(key, S.G);
+        const int cl = 7 - (int)(key & 7u);
+        const bool is_piv = key >= 8u && L.i == cl;
+        if (is_piv) {
+#pragma unroll
+            for (int m = 0; m < NMO; m += 2) *(double2 *)(piv_row + m) = make_double2(a[m], a[m + 1]);
+        }
+        // rows left above the pivot's: its row permutation's inversions
+        if (key >= 8u && !done && L.i < cl) ++inv_cnt;
+        wave_sync();
+        // the pivot from the published row (none: the column is zero, or NaN)
+        const double piv = key >= 8u ? piv_row[j] : 0.0;
+        const bool ok = fabs(piv) > 0.0;
+        if (work && !ok) singular = true;
+        if (work) dprod *= piv;
+        // multiplier as in Doolittle elimination: equal rows cancel exactly
+        const double y = rcp_ge1(piv);
+        double inv = div_by_rcp(1.0, piv, y), f = div_by_rcp(a[j], piv, y);
+        // (a pivot at the ends of the exponent range takes the full division)
+        const uint32_t top = (uint32_t)__double2hiint(piv) & 0x7FFFFFFFu;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(ok && top - 0x03C00000u > 0x78400000u) != 0, 0)) {
+            inv = 1.0 / piv;
+            f = a[j] / piv;
+        }
+        if (is_piv) {  // this row is scaled in place
+#pragma unroll
+            for (int m = 0; m < NMO; ++m) a[m] *= inv;
+            a[j] = inv;
+            done = true;
+            slot = j;
+        } else if (ok) {
+#pragma unroll
+            for (int m = 0; m < NMO; m += 2) {
+                const double2 pr = *(const double2 *)(piv_row + m);
+                a[m] -= f * pr.x;
+                a[m + 1] -= f * pr.y;
+            }
+            a[j] = -f;
+        }
+        wave_sync();
+    }
+}
 
 // PSI: stop once log|Psi| is known (no cofactor tables, no adjoint vector):
 // the values a finite-difference kinetic energy needs.  RT is the arithmetic
@@ -749,7 +821,8 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     c.vpot = vpot;
 
     if constexpr (BF) {
-        backflow_dets<NMO, !EXPL, (BF == 1 ? kSmallCfgBF : kMaxCfgBF)>(S, L, wsm, sPos, x0, x1, x2, c);
+        backflow_dets<NMO, !EXPL, (BF == 1 ? kSmallCfgBF : kMaxCfgBF)>(S, L, wsm, sPos, x0, x1, x2,
+                                                                             (double *)stage, c);
         return;
     }
 
@@ -793,70 +866,12 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
         return;
     }
 
-    // ---- in-place Gauss-Jordan of the reference matrix across the group --
-    // Row = this electron's MO values.  Pivot column j (reference orbital j
-    // after the create-time column permutation) is overwritten by the
-    // inverse, so at the end the row of slot s holds A0^-1[s][slot(e)] in
-    // the columns < n and T[s][v] = (A0^-1 Phi)[s][v] in the virtual columns.
-    // A step's chain is: largest |a[j]| of the rows left, that row through
-    // LDS, one reciprocal, one multiply-add per column.  The largest is taken
-    // on one word per lane (the upper bits of |a[j]|, then the lower lane),
-    // three cross-lane maxima.
+    // ---- elimination of the reference matrix ------------------------------
     constexpr int JMAX = kMaxSpin < NMO ? kMaxSpin : NMO;
-    bool done = !L.active;
-    int slot = -1, inv_cnt = 0;
-    double dprod = 1.0;
-    bool singular = false;
-#pragma unroll
-    for (int j = 0; j < JMAX; ++j) {
-        if (j >= nmax) break;
-        const bool work = j < L.nsig;
-        uint32_t key = 0;  // 8 or more for a non-zero candidate
-        if (work && !done && a[j] != 0.0) {
-            const uint32_t hi = (uint32_t)__double2hiint(a[j]) & 0x7FFFFFF8u;
-            key = (hi > 8u ? hi : 8u) | (uint32_t)(7 - L.i);
-        }
-        key = span_max_u(key, S.G);
-        const int cl = 7 - (int)(key & 7u);
-        const bool is_piv = key >= 8u && L.i == cl;
-        if (is_piv) {
-#pragma unroll
-            for (int m = 0; m < NMO; m += 2) *(double2 *)(piv_row + m) = make_double2(a[m], a[m + 1]);
-        }
-        // rows left above the pivot's: its row permutation's inversions
-        if (key >= 8u && !done && L.i < cl) ++inv_cnt;
-        wave_sync();
-        // the pivot from the published row (none: the column is zero, or NaN)
-        const double piv = key >= 8u ? piv_row[j] : 0.0;
-        const bool ok = fabs(piv) > 0.0;
-        if (work && !ok) singular = true;
-        if (work) dprod *= piv;
-        // multiplier as in Doolittle elimination: equal rows cancel exactly
-        const double y = rcp_ge1(piv);
-        double inv = div_by_rcp(1.0, piv, y), f = div_by_rcp(a[j], piv, y);
-        // (a pivot at the ends of the exponent range takes the full division)
-        const uint32_t top = (uint32_t)__double2hiint(piv) & 0x7FFFFFFFu;
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(ok && top - 0x03C00000u > 0x78400000u) != 0, 0)) {
-            inv = 1.0 / piv;
-            f = a[j] / piv;
-        }
-        if (is_piv) {  // this row is scaled in place
-#pragma unroll
-            for (int m = 0; m < NMO; ++m) a[m] *= inv;
-            a[j] = inv;
-            done = true;
-            slot = j;
-        } else if (ok) {
-#pragma unroll
-            for (int m = 0; m < NMO; m += 2) {
-                const double2 pr = *(const double2 *)(piv_row + m);
-                a[m] -= f * pr.x;
-                a[m + 1] -= f * pr.y;
-            }
-            a[j] = -f;
-        }
-        wave_sync();
-    }
+    int slot, inv_cnt;
+    double dprod;
+    bool singular;
+    eliminate<NMO>(S, L, a, nmax, piv_row, slot, inv_cnt, dprod, singular);
     // compact layout: the reference part of each slot's row (A0^-1) goes
     // to the cofactor region for a moment, and each lane keeps its column
     double ainv[JMAX];
