@@ -458,6 +458,7 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     std::vector<int4> shells;
     std::vector<double2> prims;
     std::vector<double> angf;  // per AO angular factor
+    std::vector<double> prim_qn;
     int p0 = 0;
     for (int s = 0; s < d->n_shells; ++s) {
         const int l = d->shell_l[s], kn = d->shell_kn[s], np = d->shell_nprim[s];
@@ -466,6 +467,7 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
             const double e = d->prim_exp[p0 + q];
             const double c = d->prim_coef[p0 + q] * (d->normalize ? radial_norm(d->basis, l, kn, e) : 1.0);
             prims.push_back(make_double2(e, c));
+            prim_qn.push_back(!d->normalize ? 0.0 : (d->basis == QMC_STO ? l + kn + 1.5 : 0.75 + 0.5 * l) / e);
         }
         p0 += np;
         for (int a = l; a >= 0; --a)
@@ -504,6 +506,7 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     const size_t o_atoms = push_bytes(blob, atoms.data(), atoms.size());
     const size_t o_shells = push_bytes(blob, shells.data(), shells.size());
     const size_t o_prims = push_bytes(blob, prims.data(), prims.size());
+    const size_t o_qn = push_bytes(blob, prim_qn.data(), prim_qn.size());
     const size_t o_mo = push_bytes(blob, mo.data(), mo.size());
     const size_t o_moa = push_bytes(blob, mo_a.data(), mo_a.size());
     const size_t o_mofa = push_bytes(blob, mo_fa.data(), mo_fa.size());
@@ -570,6 +573,7 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     S.atoms = (const double *)(base + o_atoms);
     S.shells = (const int4 *)(base + o_shells);
     S.prims = (const double2 *)(base + o_prims);
+    S.prim_qn = (const double *)(base + o_qn);
     S.mo = (const double *)(base + o_mo);
     S.mo_a = (const double *)(base + o_moa);
     S.mo_fa = (const float *)(base + o_mofa);

@@ -43,6 +43,7 @@ struct DevSystem {
     const float *mo_fa;
     const int *mo_perm;     // [n_mo]: caller's column of each internal MO column
     const double *ao_angf;  // [n_ao]: angular normalisation folded into the MO rows
+    const double *prim_qn;  // [n_prim]: d log(radial normalisation) / d exponent
     // BF16 MFMA operand fragments of C^T [2 tiles][hi, lo][64 lanes], 8 bf16
     // each: lane l of tile t holds C[8 (l / 16) + e][16 t + l % 16].
     const uint4 *mfma_tab;

@@ -37,16 +37,20 @@ struct GradOut {
     int n_param;
 };
 
+// Doubles from row to row of the main pass: 64 and four more, so that the four
+// rows which put_mo_gradient reads at once lie in different banks.
+constexpr int kGradRow = kWave + 4;
+
 // LDS of the gradient kernel (doubles).  Per walker, from its base: the
 // shared stages' tables (walker_lds, full layout), then the forward-mode
 // tables [2][2][n_max][NMO]: Tdot / Ainvdot, and the slot-indexed rows
 // (B0 | Z) that Cdot replaces.  Once a_e and its derivative are in registers
 // all of it is dead and the wave's rows take the block from its start:
-// a [NMO][64], adot [NMO][64], and the two rings [kRing][64] of the main pass;
+// a [NMO], adot [NMO] and the two rings [kRing] of kGradRow in the main pass;
 // after them each walker's positions [LW][3] and e-e-n tables of the Jastrow
 // directions, [LW][n_atoms][2 een_n] factors and [LW][n_atoms][kEenGeo]
 // geometry.  The per-nucleus results [n_atoms][6] per walker live past the
-// end of all.  (CO: 37 KB, so four waves share a compute unit; with a row of
+// end of all.  (CO: 39.6 KB, so four waves share a compute unit; with a row of
 // 2 n_ao + 2 NMO doubles per electron for the MO-coefficient products it was
 // 49 KB and three.)
 template <int NMO>
@@ -59,7 +63,7 @@ __host__ __device__ inline int grad_walker(const DevSystem &S) {
 
 template <int NMO>
 __host__ __device__ inline int grad_wave(const DevSystem &S) {
-    const int walkers = S.WPW * grad_walker<NMO>(S), rows = (2 * NMO + 2 * kRing) * kWave;
+    const int walkers = S.WPW * grad_walker<NMO>(S), rows = (2 * NMO + 2 * kRing) * kGradRow;
     return walkers > rows ? walkers : rows;
 }
 
@@ -107,18 +111,20 @@ struct Radial {
     double v, d, l, dd, l1;
 };
 
-// One primitive f's share of the sums, and what its exponent's derivative
-// needs: fz = df/dzeta (normalisation included) and the derivatives of
-// R'/r and R'' + (2l+2) R'/r.
-struct PrimDerivs {
-    double fz, dRd, dRl;
+// What an exponent's derivatives need of the shell: the sums q of t P,
+// A1 = td P + t lap P + 2 t grad P . grad J, and B = 2 q d . grad J.
+struct ExpoSums {
+    double q, A1, B;
 };
 
-template <bool EXPO>
-__device__ __forceinline__ PrimDerivs radial_prim(const DevSystem &S, double2v pe, int l, int kn, double r, double r2,
-                                                  double rinv, double rk, Radial &R) {
+// One primitive f's share of the radial sums, and its exponent's derivative of
+// log|Psi| (gl) and E_L (ge) at this electron.  With fz = df/dzeta
+// (normalisation included: fz = f (qn - r) or f (qn - r^2)),
+//   gl = fz q,  ge = -1/2 (fz A1 + d(R'/r)/dzeta B + d(R'' + (2l+2) R'/r)/dzeta q).
+__device__ __forceinline__ void radial_prim(const DevSystem &S, double2v pe, double qn, int l, int kn, double r,
+                                            double r2, double rinv, double rk, const ExpoSums &z, Radial &R, double &gl,
+                                            double &ge) {
     const double ex = pe.x;
-    PrimDerivs o = {0.0, 0.0, 0.0};
     if (S.basis == 0) {
         const double f = pe.y * rk * exp_f64(-ex * r);
         const double kr = kn * rinv, g = kr - ex, l2 = (2.0 * l + 2.0) * rinv;
@@ -129,28 +135,22 @@ __device__ __forceinline__ PrimDerivs radial_prim(const DevSystem &S, double2v p
         R.l += f * L;
         R.dd += f * (g * g - kr * rinv - g * rinv) * rinv * rinv;
         R.l1 += (f * g * L + f * Lp) * rinv;
-        if (EXPO) {
-            const double qn = S.normalize ? (l + kn + 1.5) / ex : 0.0;
-            o.fz = f * (qn - r);
-            o.dRd = (o.fz * g - f) * rinv;
-            o.dRl = o.fz * L + f * (-2.0 * g - l2);
-        }
+        const double fz = f * (qn - r);
+        gl = fz * z.q;
+        ge = -0.5 * (fz * z.A1 + (fz * g - f) * rinv * z.B + (fz * L + f * (-2.0 * g - l2)) * z.q);
     } else {
         const double f = pe.y * exp_f64(-ex * r2);
-        const double fl = (4.0 * l + 6.0) * ex, Q = 4.0 * ex * ex * r2 - fl;
+        const double F = 4.0 * l + 6.0, s = 4.0 * ex * r2 - F, Q = ex * s;  // lap factor Q, 8 ex r^2 - F = 2 s + F
+        const double e2 = -2.0 * ex, ef = e2 * f;
         R.v += f;
-        R.d += -2.0 * ex * f;
+        R.d += ef;
         R.l += f * Q;
-        R.dd += 4.0 * ex * ex * f;
-        R.l1 += f * (-2.0 * ex * Q + 8.0 * ex * ex);
-        if (EXPO) {
-            const double qn = S.normalize ? (0.75 + 0.5 * l) / ex : 0.0;
-            o.fz = f * (qn - r2);
-            o.dRd = -2.0 * f - 2.0 * ex * o.fz;
-            o.dRl = o.fz * Q + f * (8.0 * ex * r2 - (4.0 * l + 6.0));
-        }
+        R.dd += e2 * ef;
+        R.l1 += ef * (Q + 2.0 * e2);
+        const double fz = f * (qn - r2);
+        gl = fz * z.q;
+        ge = -0.5 * (fz * (z.A1 + e2 * z.B + Q * z.q) + f * ((2.0 * s + F) * z.q - 2.0 * z.B));
     }
-    return o;
 }
 
 // Ends a batch of two table columns whose results are v..: without a line
@@ -178,15 +178,22 @@ __device__ __forceinline__ double power(double r, int kn) {
 template <int NMO>
 __device__ __forceinline__ void put_mo_gradient(const DevSystem &S, int lane, int64_t wave_first, int64_t W, int mu0,
                                                 const double *chi, const double *beta, const double *sA,
-                                                const double *sAd, const GradOut &G) {
+                                                const double *sAd, const int (&col_of)[NMO / 4], const GradOut &G) {
     constexpr int MB = NMO / 4;
     const int k = lane >> 4, b = (lane >> 2) & 3, i = lane & 3;
     const int steps = S.LW >= 4 ? S.LW / 4 : 1;  // products per walker
-    const int row = ((mu0 + i) & (kRing - 1)) * kWave;
+    const int row = ((mu0 + i) & (kRing - 1)) * kGradRow;
     const bool own = S.LW >= 4 || k < S.LW;      // two-lane walkers fill half of the step
-    // this lane's result: AO mu0 + k, MO 4 s + i of walker b of the set
+    // this lane's result: AO mu0 + k, MO 4 s + i of walker b of the set.  The
+    // factors come by scalar loads: a vector load would wait for every store
+    // before it.
     const int mu = mu0 + k;
-    const double f = mu < S.n_ao ? const_tab(S.ao_angf)[mu] : 0.0;
+    double f = 0.0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const double ft = const_tab(S.ao_angf)[mu0 + t < S.n_ao ? mu0 + t : 0];
+        f = k == t ? ft : f;
+    }
     wave_sync();
     for (int set = 0; set < S.WPW / 4; ++set) {
         const int64_t w = wave_first + 4 * set + b;
@@ -195,21 +202,26 @@ __device__ __forceinline__ void put_mo_gradient(const DevSystem &S, int lane, in
         for (int s = 0; s < MB; ++s) gl[s] = ge[s] = 0.0;
         for (int q = 0; q < steps; ++q) {
             const int col = (4 * set + b) * S.LW + (own ? 4 * q + k : 0);
-            const double c = own ? chi[row + col] : 0.0, be = own ? beta[row + col] : 0.0;
+            double c = chi[row + col], be = beta[row + col], av[MB], ad[MB];
 #pragma unroll
             for (int s = 0; s < MB; ++s) {
-                const double av = sA[(4 * s + i) * kWave + col], ad = sAd[(4 * s + i) * kWave + col];
-                gl[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(c, own ? av : 0.0, gl[s], 0, 0, 0);
-                ge[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(c, own ? ad : 0.0, ge[s], 0, 0, 0);
-                ge[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(be, own ? av : 0.0, ge[s], 0, 0, 0);
+                av[s] = sA[(4 * s + i) * kGradRow + col];
+                ad[s] = sAd[(4 * s + i) * kGradRow + col];
+            }
+            c = own ? c : 0.0;
+            be = own ? be : 0.0;
+#pragma unroll
+            for (int s = 0; s < MB; ++s) {
+                gl[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(c, av[s], gl[s], 0, 0, 0);
+                ge[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(c, ad[s], ge[s], 0, 0, 0);
+                ge[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(be, av[s], ge[s], 0, 0, 0);
             }
         }
         if (w < W && mu < S.n_ao) {
 #pragma unroll
             for (int s = 0; s < MB; ++s) {
-                const int m = 4 * s + i;
-                if (m < S.n_mo) {
-                    const int64_t out = w * G.n_param + S.n_prim + mu * S.n_mo + const_tab(S.mo_perm)[m];
+                if (col_of[s] >= 0) {
+                    const int64_t out = w * G.n_param + S.n_prim + mu * S.n_mo + col_of[s];
                     if (G.dlogpsi) G.dlogpsi[out] = f * gl[s];
                     if (G.deloc_dth) G.deloc_dth[out] = -0.5 * f * ge[s];
                 }
@@ -219,18 +231,37 @@ __device__ __forceinline__ void put_mo_gradient(const DevSystem &S, int lane, in
     wave_sync();
 }
 
-// d log|Psi| and d E_L of one direction, from this electron's share of d J
-// and of the functional -1/2 d lap_e J - h . d grad_e J, summed over the
-// walker's electrons.
-__device__ __forceinline__ void put_direction(const GradOut &G, const Lane &L, int LW, int64_t w, int out, double dl,
-                                              double de) {
-    dl = walker_sum(dl, LW);
-    de = walker_sum(de, LW);
-    if (L.wvalid && L.lw == 0) {
-        if (G.dlogpsi) G.dlogpsi[w * G.n_param + out] = dl;
-        if (G.deloc_dth) G.deloc_dth[w * G.n_param + out] = de;
+// Sums over a walker's electrons of a derivative of log|Psi| and of E_L.  The
+// walker's first lane keeps the first, the first lane of its upper half the
+// second (span_sum_pair).
+struct WalkerOut {
+    double *param;  // this lane's row of the parameter output, or NULL
+    double *atom;   // this lane's column of the walker's nuclear sums in LDS, or NULL
+    int LW;
+    bool upper;
+
+    __device__ __forceinline__ WalkerOut(const GradOut &G, const Lane &L, int LW_, int64_t w, double *sAtom) {
+        LW = LW_;
+        upper = L.lw >= LW / 2;
+        param = atom = nullptr;
+        if (L.wvalid && (L.lw == 0 || L.lw == LW / 2)) {
+            double *p = upper ? G.deloc_dth : G.dlogpsi;
+            if (p) param = p + w * G.n_param;
+            atom = sAtom + (upper ? 3 : 0);
+        }
     }
-}
+    __device__ __forceinline__ void put(int at, double l, double e) const {
+        const double v = span_sum_pair(l, e, LW, upper);
+        if (param) param[at] = v;
+    }
+    __device__ __forceinline__ void add_atom(int a, const double (&l)[3], const double (&e)[3], double f = 1.0) const {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double v = span_sum_pair(f * l[k], f * e[k], LW, upper);
+            if (atom) atom[6 * a + k] += v;
+        }
+    }
+};
 
 // A radial function f(|x - c|) added to J: lap f = f'' + 2 f'/r, grad f = f' u.
 // Its share of d E_L is -1/2 (f'' + 2 f'/r) - (h . u) f'.
@@ -240,7 +271,7 @@ __device__ __forceinline__ double radial_energy(double f1, double f2, double ri,
 
 // Derivatives with respect to the Jastrow parameters (Pade b; e-n (w0, w1,
 // w2) per nucleus; e-e-n (c, a1, b1, a2, b2, a3, b3) per term) and the
-// Jastrow's part of the nuclear gradients, added to sAtom.  With
+// Jastrow's part of the nuclear gradients, added to the walker's sums.  With
 // h = grad_e log|Psi| a change dJ of the Jastrow factor changes E_L by
 // -1/2 sum_e (lap_e dJ + 2 h_e . grad_e dJ), a functional linear in dJ.
 //
@@ -254,9 +285,9 @@ __device__ __forceinline__ double radial_energy(double f1, double f2, double ri,
 // dp/dR = -p' t_j), b3 replaces s, and the own factor's b and nuclear
 // derivative only need the sums A, B, D of jastrow_terms.  A forward-mode
 // pass per direction ran the pair loop 48 times for CO with 5 terms.
-__device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L, int64_t w, double x0, double x1,
-                                               double x2, const double (&h)[3], const double *sPos, const double *sF,
-                                               const double *sG, const GradOut &G, double *sAtom) {
+__device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L, double x0, double x1, double x2,
+                                               const double (&h)[3], const double *sPos, const double *sF,
+                                               const double *sG, const GradOut &G, const WalkerOut &out) {
     const bool need_R = G.dlogpsi_dR || G.deloc_dR;
     const int p_b = S.n_prim + S.n_ao * S.n_mo;  // output index of b
     const int p_en = p_b + 1, p_een = p_en + (S.jas_en ? 3 * S.n_atoms : 0);
@@ -276,7 +307,7 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
             de += radial_energy(-2.0 * a * p.g * p.g1, a * p.q * p.g1 * (6.0 * S.b * p.g - 2.0), s.ri, hw);
         }
     }
-    put_direction(G, L, S.LW, w, p_b, dl, de);
+    out.put(p_b, dl, de);
     // ---- e-n parameters and nuclear part --------------------------------------
     if (S.jas_en) {
         for (int a = 0; a < S.n_atoms; ++a) {
@@ -311,15 +342,8 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
                     er[k] = c * u[k] + kr * h[k];
                 }
             }
-            for (int k = 0; k < 3; ++k) put_direction(G, L, S.LW, w, p_en + 3 * a + k, l3[k], e3[k]);
-            if (need_R)
-                for (int k = 0; k < 3; ++k) {
-                    const double l = walker_sum(lr[k], S.LW), e = walker_sum(er[k], S.LW);
-                    if (L.wvalid && L.lw == 0) {
-                        sAtom[6 * a + k] += l;
-                        sAtom[6 * a + 3 + k] += e;
-                    }
-                }
+            for (int k = 0; k < 3; ++k) out.put(p_en + 3 * a + k, l3[k], e3[k]);
+            if (need_R) out.add_atom(a, lr, er);
         }
     }
     // ---- e-e-n parameters and nuclear part --------------------------------------
@@ -427,23 +451,16 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
                     }
                 }
             }
-            if (need_R)
-                for (int k = 0; k < 3; ++k) {
-                    const double l = walker_sum(kc * lr[k], S.LW), e = walker_sum(kc * er[k], S.LW);
-                    if (L.wvalid && L.lw == 0) {
-                        sAtom[6 * a + k] += l;
-                        sAtom[6 * a + 3 + k] += e;
-                    }
-                }
+            if (need_R) out.add_atom(a, lr, er, kc);
         }
-        const int out = p_een + 7 * m;
-        put_direction(G, L, S.LW, w, out + 0, a1 * a2 * a3 * l0, a1 * a2 * a3 * e0);
-        put_direction(G, L, S.LW, w, out + 1, c * a2 * a3 * l0, c * a2 * a3 * e0);
-        put_direction(G, L, S.LW, w, out + 2, kc * lb1, kc * eb1);
-        put_direction(G, L, S.LW, w, out + 3, c * a1 * a3 * l0, c * a1 * a3 * e0);
-        put_direction(G, L, S.LW, w, out + 4, kc * lb2, kc * eb2);
-        put_direction(G, L, S.LW, w, out + 5, c * a1 * a2 * l0, c * a1 * a2 * e0);
-        put_direction(G, L, S.LW, w, out + 6, kc * lb3, kc * eb3);
+        const int at = p_een + 7 * m;
+        out.put(at + 0, a1 * a2 * a3 * l0, a1 * a2 * a3 * e0);
+        out.put(at + 1, c * a2 * a3 * l0, c * a2 * a3 * e0);
+        out.put(at + 2, kc * lb1, kc * eb1);
+        out.put(at + 3, c * a1 * a3 * l0, c * a1 * a3 * e0);
+        out.put(at + 4, kc * lb2, kc * eb2);
+        out.put(at + 5, c * a1 * a2 * l0, c * a1 * a2 * e0);
+        out.put(at + 6, kc * lb3, kc * eb3);
     }
 }
 
@@ -455,15 +472,21 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
 // stage keeps its LDS reads in batches (two table columns, all rows of a
 // spin), its tables in scalar loads ahead of use, and its contractions on the
 // matrix cores (direction B beside the MO values, the AO weights of a and
-// adot, the MO-coefficient products).  Li2, 32 768 walkers, all outputs:
-// 518 us -> 256 us (175 MB written); many-body CO, 4099 walkers: 2523 us -> 349 us.
+// adot, the MO-coefficient products).  Two things cost more than the arithmetic
+// and are kept out of the main pass: LDS rows 64 doubles apart, whose reads by
+// four rows at once met in the same banks (put_mo_gradient 82 k -> 28 k cycles
+// of a CO wave with kGradRow), and vector loads behind stores, which wait for
+// them.  All outputs, as first written with LDS rows per electron, then with
+// the contractions here, then with these two and one reduction per pair of
+// results: Li2, 32 768 walkers 542 -> 254 -> 209 us (175 MB written); CO, 8192
+// walkers 564 -> 217 -> 161 us; many-body CO, 4099 walkers 2523 -> 349 -> 288 us.
 template <int NMO, typename RT>
 __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__restrict__ X, int64_t W,
                                                 GradOut G) {
     extern __shared__ double smem[];
     int64_t w;
     const int64_t wave_first = (int64_t)blockIdx.x * S.WPW;
-    const Lane L = make_lane(S, wave_first, W, &w);
+    Lane L = make_lane(S, wave_first, W, &w);
     double *wsm = smem + L.wloc * grad_walker<NMO>(S);
     const int nmax = S.n_up > S.n_dn ? S.n_up : S.n_dn;
     const int ts = nmax * NMO;                 // doubles per spin table
@@ -471,7 +494,6 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
     double *sC = wsm + 2 * ts;                 // cofactor tables (shared stages)
     double *sTD = wsm + walker_lds<NMO>(S);    // Tdot, Ainvdot
     double *sCD = sTD + 2 * ts;                // B0 | Z rows, then Cdot
-    double *sAtom = smem + grad_wave<NMO>(S) + L.wloc * 6 * S.n_atoms;  // [n_atoms][6]: dlogpsi/dR, dE/dR
 
     double x0 = 0.0, x1 = 0.0, x2 = 0.0;
     if (L.active) {
@@ -486,7 +508,6 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
         x2 = 100.0;
     }
 
-    for (int q = L.lw; q < 6 * S.n_atoms; q += S.LW) sAtom[q] = 0.0;
 
     // ---- shared stages: MO values and direction B, Gauss-Jordan,
     // determinants, a_e ----
@@ -583,7 +604,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
             uint4v rb[kRecBatch];
 #pragma unroll
             for (int u = 0; u < kRecBatch; ++u)
-                rb[u] = i0 + u < S.det_rows ? const_tab((const uint4v *)S.det_recs)[(i0 + u) * S.LW + L.lw]
+                rb[u] = i0 + u < S.det_rows ? const_tab((const uint4v *)S.det_recs)[(i0 + u) * S.LW + (lane_now() & (S.LW - 1))]
                                             : uint4v{0, 0, 0, 0};
 #pragma unroll
             for (int u = 0; u < kRecBatch; ++u) {
@@ -599,7 +620,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
                 uint4v rb[kRecBatch];
 #pragma unroll
                 for (int u = 0; u < kRecBatch; ++u)
-                    rb[u] = i0 + u < S.cof_rows ? const_tab((const uint4v *)S.cof_recs)[(i0 + u) * S.LW + L.lw]
+                    rb[u] = i0 + u < S.cof_rows ? const_tab((const uint4v *)S.cof_recs)[(i0 + u) * S.LW + (lane_now() & (S.LW - 1))]
                                                 : uint4v{0, 0, 0, 0};
 #pragma unroll
                 for (int u = 0; u < kRecBatch; ++u) {
@@ -664,23 +685,34 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
     else if (S.G == 4) forward(std::integral_constant<int, 4>());
     else forward(std::integral_constant<int, 8>());
     wave_sync();  // the walkers' tables become the wave's rows
+    L = make_lane(S, wave_first, W, &w, lane_now());
+    double *sAtom = smem + grad_wave<NMO>(S) + L.wloc * 6 * S.n_atoms;  // [n_atoms][6]: dlogpsi/dR, dE/dR
+    for (int q = L.lw; q < 6 * S.n_atoms; q += S.LW) sAtom[q] = 0.0;
+    const WalkerOut out(G, L, S.LW, w, sAtom);
 
     // ---- main gradient pass over the AOs ----------------------------------
     // Per shell the AO weights t (of a) and td (of adot) meet the monomials
     // first, in sums that every radial derivative and every exponent shares;
     // chi and beta = lap chi + 2 grad J . grad chi take the weights' ring rows
     // for the MO-coefficient products of each four AOs.
-    double *sA = smem, *sAd = sA + NMO * kWave, *ringT = sAd + NMO * kWave, *ringD = ringT + kRing * kWave;
-    AoWeights<NMO> wt(S, L.lane, sA, ringT, c.av), wd(S, L.lane, sAd, ringD, adot);
+    double *sA = smem, *sAd = sA + NMO * kGradRow, *ringT = sAd + NMO * kGradRow, *ringD = ringT + kRing * kGradRow;
+    AoWeights<NMO, kGradRow> wt(S, L.lane, sA, ringT, c.av), wd(S, L.lane, sAd, ringD, adot);
     // rows of idle lanes are zero in the products over a walker's electrons
     wave_sync();
 #pragma unroll
     for (int m = 0; m < NMO; ++m) {
-        sA[m * kWave + L.lane] = L.active ? c.av[m] : 0.0;
-        sAd[m * kWave + L.lane] = L.active ? adot[m] : 0.0;
+        sA[m * kGradRow + L.lane] = L.active ? c.av[m] : 0.0;
+        sAd[m * kGradRow + L.lane] = L.active ? adot[m] : 0.0;
     }
     wave_sync();
     double gS[3] = {0.0, 0.0, 0.0};
+    int col_of[NMO / 4];  // caller's columns of the MOs whose derivatives this lane writes, -1: padding
+#pragma unroll
+    for (int s = 0; s < NMO / 4; ++s) {
+        const int m = 4 * s + (L.lane & 3);
+        const int col = const_tab(S.mo_perm)[m < S.n_mo ? m : 0];
+        col_of[s] = m < S.n_mo ? col : -1;
+    }
     {
         int p = 0, mu = 0, done = 0, atom = -1;
         double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
@@ -689,14 +721,8 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
         double r = 0.0, rinv = 0.0, gd = 0.0;
         auto put_atom = [&]() {
             if (atom < 0) return;
-            for (int k = 0; k < 3; ++k) {
-                const double l = walker_sum(lr[k], S.LW), e = walker_sum(er[k], S.LW);
-                if (L.wvalid && L.lw == 0) {
-                    sAtom[6 * atom + k] += l;
-                    sAtom[6 * atom + 3 + k] += e;
-                }
-                lr[k] = er[k] = 0.0;
-            }
+            out.add_atom(atom, lr, er);
+            for (int k = 0; k < 3; ++k) lr[k] = er[k] = 0.0;
         };
         for (int sh = 0; sh < S.n_shells; ++sh) {
             const int4v si = shell_info(S, sh);
@@ -728,7 +754,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
                 qd = qdv[0] * a.dx + qdv[1] * a.dy + qdv[2] * a.dz;
             } else {
                 // symmetric matrix of t: 2 t on the diagonal, t off it
-                auto quad = [&](const AoWeights<NMO> &wx, double &s, double (&sv)[3], double &tr, double (&M)[6]) {
+                auto quad = [&](const AoWeights<NMO, kGradRow> &wx, double &s, double (&sv)[3], double &tr, double (&M)[6]) {
                     const double xx = wx(mu), xy = wx(mu + 1), xz = wx(mu + 2), yy = wx(mu + 3), yz = wx(mu + 4),
                                  zz = wx(mu + 5);
                     M[0] = 2.0 * xx, M[1] = xy, M[2] = xz, M[3] = 2.0 * yy, M[4] = yz, M[5] = 2.0 * zz;
@@ -747,22 +773,16 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
             }
             const double qg = qv[0] * gJ[0] + qv[1] * gJ[1] + qv[2] * gJ[2];
             // one pass over the primitives: radial sums and exponent derivatives
-            const double A1 = qd + qL + 2.0 * qg;
+            // (idle lanes: zero sums, so their shares vanish)
+            const double on = L.active ? 1.0 : 0.0;
+            const ExpoSums z = {on * q, on * (qd + qL + 2.0 * qg), on * (2.0 * gd * q)};
             const double rk = S.basis == 0 ? power(r, si.z) : 1.0;
             Radial R = {0.0, 0.0, 0.0, 0.0, 0.0};
             for (int i = 0; i < si.w; ++i) {
-                const PrimDerivs z = radial_prim<true>(S, prim_info(S, p + i), si.y, si.z, r, a.r2, rinv, rk, R);
-                double gl = 0.0, ge = 0.0;
-                if (L.active) {
-                    gl = z.fz * q;
-                    ge = -0.5 * (z.fz * A1 + z.dRd * 2.0 * gd * q + z.dRl * q);
-                }
-                gl = walker_sum(gl, S.LW);
-                ge = walker_sum(ge, S.LW);
-                if (L.wvalid && L.lw == 0) {
-                    if (G.dlogpsi) G.dlogpsi[w * G.n_param + p + i] = gl;
-                    if (G.deloc_dth) G.deloc_dth[w * G.n_param + p + i] = ge;
-                }
+                double gl, ge;
+                radial_prim(S, prim_info(S, p + i), const_tab(S.prim_qn)[p + i], si.y, si.z, r, a.r2, rinv, rk, z, R,
+                            gl, ge);
+                out.put(p + i, gl, ge);
             }
             p += si.w;
             if (L.active) {
@@ -781,7 +801,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
             // chi and beta into the ring rows whose weights are spent
             const double Xr = R.l + 2.0 * R.d * gd;
             shell_monomials(si.y, a.dx, a.dy, a.dz, [&](int cc, double P, double Px, double Py, double Pz, double PL) {
-                const int at = ((mu + cc) & (kRing - 1)) * kWave + L.lane;
+                const int at = ((mu + cc) & (kRing - 1)) * kGradRow + L.lane;
                 const double chi = P * R.v;
                 const double be = P * Xr + R.v * (PL + 2.0 * (gJ[0] * Px + gJ[1] * Py + gJ[2] * Pz));
                 ringT[at] = L.active ? chi : 0.0;
@@ -789,15 +809,15 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
             });
             mu += nc;
             for (; mu - done >= 4; done += 4)
-                put_mo_gradient<NMO>(S, L.lane, wave_first, W, done, ringT, ringD, sA, sAd, G);
+                put_mo_gradient<NMO>(S, L.lane, wave_first, W, done, ringT, ringD, sA, sAd, col_of, G);
         }
         put_atom();
         if (done < mu) {
             for (int z = mu; z & 3; ++z) {
-                ringT[(z & (kRing - 1)) * kWave + L.lane] = 0.0;
-                ringD[(z & (kRing - 1)) * kWave + L.lane] = 0.0;
+                ringT[(z & (kRing - 1)) * kGradRow + L.lane] = 0.0;
+                ringD[(z & (kRing - 1)) * kGradRow + L.lane] = 0.0;
             }
-            put_mo_gradient<NMO>(S, L.lane, wave_first, W, done, ringT, ringD, sA, sAd, G);
+            put_mo_gradient<NMO>(S, L.lane, wave_first, W, done, ringT, ringD, sA, sAd, col_of, G);
         }
     }
     // e-n attraction
@@ -810,10 +830,8 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
             const double f = -A[3] / (rr * rr * rr);
             for (int k = 0; k < 3; ++k) er[k] = f * d[k];
         }
-        for (int k = 0; k < 3; ++k) {
-            const double e = walker_sum(er[k], S.LW);
-            if (L.wvalid && L.lw == 0) sAtom[6 * a + 3 + k] += e;
-        }
+        const double none[3] = {0.0, 0.0, 0.0};
+        out.add_atom(a, none, er);
     }
 
     // ---- Jastrow parameters and the Jastrow part of the nuclear gradients ---
@@ -828,8 +846,9 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
         een_table_fill<true>(S, L, x0, x1, x2, sF, sG);
         wave_sync();
         const double h[3] = {gJ[0] + gS[0], gJ[1] + gS[1], gJ[2] + gS[2]};
-        jastrow_derivs(S, L, w, x0, x1, x2, h, sP, sF, sG, G, sAtom);
+        jastrow_derivs(S, L, x0, x1, x2, h, sP, sF, sG, G, out);
     }
+    wave_sync();  // the nuclear sums of both halves of a walker's lanes
     if (L.wvalid && L.lw == 0) {
         // nuclear gradients, with the n-n repulsion
         for (int a = 0; a < S.n_atoms; ++a) {

@@ -330,7 +330,7 @@ __device__ __forceinline__ void mo_values_f32(const DevSystem &S, int lane, doub
 // AO weights t_mu = sum_m C[mu][m] a_e[m] of the lane's electron, four rows
 // at a time into a ring of LDS rows; the C rows of the next four are already
 // in registers.
-template <int NMO>
+template <int NMO, int ROW = kWave>
 struct AoWeights {
     static constexpr int MB = NMO / 4;
     double *buf;
@@ -338,7 +338,7 @@ struct AoWeights {
     int lane, avail;
     double A[MB], B[MB][4];
 
-    // xbuf: [NMO][64] for the exchange of av, free afterwards; ring: [kRing][64]
+    // xbuf: [NMO][64] for the exchange of av, free afterwards; ring: [kRing][ROW]
     // (may overlap xbuf)
     __device__ __forceinline__ AoWeights(const DevSystem &S, int lane_, double *xbuf, double *ring,
                                          const double (&av)[NMO])
@@ -370,16 +370,16 @@ struct AoWeights {
 #pragma unroll
             for (int s = 0; s < MB; ++s) A[s] = Ap[s];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) buf[((avail + g) & (kRing - 1)) * kWave + 16 * t + j] = d[t];
+            for (int t = 0; t < 4; ++t) buf[((avail + g) & (kRing - 1)) * ROW + 16 * t + j] = d[t];
             avail += 4;
         }
         wave_sync();
     }
-    __device__ __forceinline__ double operator()(int mu) const { return buf[(mu & (kRing - 1)) * kWave + lane]; }
+    __device__ __forceinline__ double operator()(int mu) const { return buf[(mu & (kRing - 1)) * ROW + lane]; }
 };
 
-template <>
-struct AoWeights<kFewMO> {
+template <int ROW>
+struct AoWeights<kFewMO, ROW> {
     const __attribute__((address_space(4))) double *C;
     const double (&av)[kFewMO];
     __device__ __forceinline__ AoWeights(const DevSystem &S, int, double *, double *, const double (&av_)[kFewMO])

@@ -94,6 +94,27 @@ __device__ __forceinline__ double span_sum(double v, int n) {
     return v;
 }
 
+// Two sums over an aligned span of n = 2, 4, 8 or 16 lanes for little more than
+// one: the span's halves exchange first, so that the lower half ends with the
+// sum of a and the upper half (`upper`) with that of b.
+__device__ __forceinline__ double span_sum_pair(double a, double b, int n, bool upper) {
+    double v = upper ? b : a;
+    const double o = upper ? a : b;
+    if (n > 8) {
+        v += dpp_d<kMirror>(o);
+        v += dpp_d<kHalfMirror>(v);
+    } else if (n > 4) {
+        v += dpp_d<kHalfMirror>(o);
+    } else if (n > 2) {
+        v += dpp_d<kSwap2>(o);
+    } else {
+        v += dpp_d<kSwap1>(o);
+    }
+    if (n > 4) v += dpp_d<kSwap2>(v);
+    if (n > 2) v += dpp_d<kSwap1>(v);
+    return v;
+}
+
 __device__ __forceinline__ int span_sum_i(int v, int n) {
     if (n > 1) v += dpp_i<kSwap1>(v);
     if (n > 2) v += dpp_i<kSwap2>(v);
@@ -173,10 +194,20 @@ struct Lane {
     bool active; // owns a real electron of a valid walker
 };
 
+// The lane's index, formed anew where it stands.  A value kept across the
+// adjoint's divergent blocks may be moved to the accumulation registers at the
+// end of one, before the masked lanes are back, and is then undefined in them;
+// indexes that idle lanes load with are taken from here instead.
+__device__ __forceinline__ int lane_now() {
+    int z = 0;
+    asm volatile("" : "+s"(z));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, z));
+}
+
 __device__ __forceinline__ Lane make_lane(const DevSystem &S, int64_t wave_first_walker, int64_t W,
-                                          int64_t *walker) {
+                                          int64_t *walker, int lane = threadIdx.x) {
     Lane L;
-    L.lane = threadIdx.x;
+    L.lane = lane;
     L.wloc = L.lane / S.LW;
     L.lw = L.lane % S.LW;
     L.grp = L.lw / S.G;
@@ -911,12 +942,13 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     // ---- S = sum_n d_n det T_up[H,P] det T_dn[H,P] ----------------------
     // records are loaded kRecBatch at a time so their latencies overlap
     const double *Tup = sT, *Tdn = sT + tstride;
+    const int lw = FULLT ? lane_now() & (S.LW - 1) : L.lw;
     double Sp = 0.0;
     for (int i0 = 0; i0 < S.det_rows; i0 += kRecBatch) {
         uint4v rb[kRecBatch];
 #pragma unroll
         for (int u = 0; u < kRecBatch; ++u)
-            rb[u] = i0 + u < S.det_rows ? const_tab((const uint4v *)S.det_recs)[(i0 + u) * S.LW + L.lw] : uint4v{0, 0, 0, 0};
+            rb[u] = i0 + u < S.det_rows ? const_tab((const uint4v *)S.det_recs)[(i0 + u) * S.LW + lw] : uint4v{0, 0, 0, 0};
 #pragma unroll
         for (int u = 0; u < kRecBatch; ++u) {
             const uint4v r = rb[u];
@@ -945,7 +977,7 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
             uint4v rb[kRecBatch];
 #pragma unroll
             for (int u = 0; u < kRecBatch; ++u)
-                rb[u] = i0 + u < S.cof_rows ? const_tab((const uint4v *)S.cof_recs)[(i0 + u) * S.LW + L.lw] : uint4v{0, 0, 0, 0};
+                rb[u] = i0 + u < S.cof_rows ? const_tab((const uint4v *)S.cof_recs)[(i0 + u) * S.LW + lw] : uint4v{0, 0, 0, 0};
 #pragma unroll
             for (int u = 0; u < kRecBatch; ++u) {
                 const uint4v r = rb[u];  // an all-zero padding record adds 0 and never flushes
