@@ -284,7 +284,9 @@ __device__ __forceinline__ double radial_energy(double f1, double f2, double ri,
 // term; the partner's b and nuclear derivative replace p by dp (dg/db = -g^2,
 // dp/dR = -p' t_j), b3 replaces s, and the own factor's b and nuclear
 // derivative only need the sums A, B, D of jastrow_terms.  A forward-mode
-// pass per direction ran the pair loop 48 times for CO with 5 terms.
+// pass per direction ran the pair loop 48 times for CO with 5 terms; a pass per
+// nucleus formed each pair's part twice (134 k cycles of a wave, now 112 k;
+// 4099 walkers 284 -> 264 us).
 __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L, double x0, double x1, double x2,
                                                const double (&h)[3], const double *sPos, const double *sF,
                                                const double *sG, const GradOut &G, const WalkerOut &out) {
@@ -353,106 +355,140 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
         const double kc = c * a1 * a2 * a3;
         // this term with unit coefficients, and the b1, b2, b3 directions
         double l0 = 0.0, e0 = 0.0, lb1 = 0.0, eb1 = 0.0, lb2 = 0.0, eb2 = 0.0, lb3 = 0.0, eb3 = 0.0;
-        for (int a = 0; a < S.n_atoms; ++a) {
-            double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
-            if (L.active) {
-                const double *g = sG + (L.lw * S.n_atoms + a) * kEenGeo;
-                const double u = g[0], ui = g[4], tv[3] = {g[1], g[2], g[3]};
-                const double ht = h[0] * tv[0] + h[1] * tv[1] + h[2] * tv[2];
-                // own factor's functional in each role (0: electron i, factor 1)
-                const Pade q[2] = {pade(b1, u), pade(b2, u)};
-                double al[2], be[2][3], ga[2];
+        // NR factors of an own electron: one when f1 = f2 (both roles then share
+        // its functional), and two nuclei at a time, which share the pair's part
+        auto term = [&](auto roles) {
+            constexpr int NR = decltype(roles)::value, NA = NR == 1 ? 2 : 1;
+            for (int a0 = 0; a0 < S.n_atoms; a0 += NA) {
+                double lr[NA][3] = {}, er[NA][3] = {};
+                if (L.active) {
+                    double ui[NA], tv[NA][3], ht[NA], al[NA][NR], be[NA][NR][3], ga[NA][NR];
+                    Pade q[NA][NR];
+                    const double *fj[NA];  // partner 0's table entries of the nucleus
+                    bool on[NA];
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    al[r] = radial_energy(q[r].g1, q[r].g2, ui, ht);
-                    ga[r] = -0.5 * q[r].g;
+                    for (int n = 0; n < NA; ++n) {
+                        on[n] = a0 + n < S.n_atoms;
+                        const int a = on[n] ? a0 + n : a0;
+                        const double *g = sG + (L.lw * S.n_atoms + a) * kEenGeo;
+                        ui[n] = g[4];
+                        for (int k = 0; k < 3; ++k) tv[n][k] = g[1 + k];
+                        ht[n] = h[0] * tv[n][0] + h[1] * tv[n][1] + h[2] * tv[n][2];
+                        // own factor's functional in each role (0: electron i, factor 1)
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) be[r][k] = -(q[r].g1 * tv[k] + q[r].g * h[k]);
+                        for (int r = 0; r < NR; ++r) {
+                            const Pade p = pade(r == 0 ? b1 : b2, g[0]);
+                            q[n][r] = p;
+                            al[n][r] = radial_energy(p.g1, p.g2, ui[n], ht[n]);
+                            ga[n][r] = -0.5 * p.g;
+                            for (int k = 0; k < 3; ++k) be[n][r][k] = -(p.g1 * tv[n][k] + p.g * h[k]);
+                        }
+                        fj[n] = sF + (a * S.een_n + m) * 2;
+                    }
+                    // sums over the partners by role; pl, pe the partner's b
+                    double A[NA][2] = {}, B[NA][2][3] = {}, D[NA][2] = {};
+                    double pl = 0.0, pe[2] = {0.0, 0.0};
+                    for (int t = 1; t < S.ne; ++t) {
+                        int lj;
+                        const int j = partner(S, L.e, t, &lj);
+                        const bool first = L.e > j;
+                        const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
+                        const Sep s = separation(d0, d1, d2);
+                        const Pade p3 = pade(b3, s.r);
+                        const double w0 = d0 * s.ri, w1 = d1 * s.ri, w2 = d2 * s.ri;
+                        const double lap = p3.g2 + 2.0 * p3.g1 * s.ri;
+                        // the pair factor along b3: ds = -s^2, ds' = -2 s s', ds'' = q^3 (6 b s - 2)
+                        const double s3 = -p3.g * p3.g, s31 = -2.0 * p3.g * p3.g1;
+                        const double lap3 = p3.q * p3.g1 * (6.0 * b3 * p3.g - 2.0) + 2.0 * s31 * s.ri;
+                        const double v0 = p3.g1 * w0, v1 = p3.g1 * w1, v2 = p3.g1 * w2;
+#pragma unroll
+                        for (int n = 0; n < NA; ++n) {
+                            // partner's factor p, p' = (p / r_aj)^2, dp/db = -p^2
+                            const double *gj = sG + (lj * S.n_atoms + (on[n] ? a0 + n : a0)) * kEenGeo;
+                            const double pt = fj[n][lj * S.n_atoms * S.een_n * 2 + (first ? 1 : 0)];
+                            const double p = on[n] ? pt : 0.0;
+                            const double pq = p * gj[4], pd = pq * pq;
+                            const int r1 = NR - 1;
+                            const double o = first ? q[n][0].g : q[n][r1].g;
+                            const double bw = (first ? be[n][0][0] : be[n][r1][0]) * w0 +
+                                              (first ? be[n][0][1] : be[n][r1][1]) * w1 +
+                                              (first ? be[n][0][2] : be[n][r1][2]) * w2;
+                            const double alr = first ? al[n][0] : al[n][r1], gar = first ? ga[n][0] : ga[n][r1];
+                            // functional of o s, and of o ds/db3
+                            const double es = alr * p3.g + bw * p3.g1 + gar * lap;
+                            eb3 += p * (alr * s3 + bw * s31 + gar * lap3);
+                            const double op = first ? o * p : 0.0;  // the pair's value is counted at i
+                            lb3 += op * s3;
+                            const double jv = first ? o * p3.g : 0.0;
+                            pl -= p * p * jv;
+                            const double pp = p * p * es;
+#pragma unroll
+                            for (int r = 0; r < 2; ++r) {
+                                const double pr = first == (r == 0) ? p : 0.0;
+                                A[n][r] += pr * p3.g;
+                                B[n][r][0] += pr * v0;
+                                B[n][r][1] += pr * v1;
+                                B[n][r][2] += pr * v2;
+                                D[n][r] += pr * lap;
+                                pe[r] -= first == (r == 0) ? pp : 0.0;
+                            }
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) {
+                                const double dp = -pd * gj[1 + k];
+                                lr[n][k] += dp * jv;
+                                er[n][k] += dp * es;
+                            }
+                        }
+                    }
+                    // role 0's partners hold factor 2, role 1's factor 1
+                    lb2 += pl;
+                    eb2 += pe[0];
+                    eb1 += pe[1];
+#pragma unroll
+                    for (int n = 0; n < NA; ++n) {
+                        l0 += q[n][0].g * A[n][0];
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            const int v = r < NR ? r : 0;
+                            const Pade &o = q[n][v];
+                            const double *Br = B[n][r], *br = be[n][v];
+                            const double bB = br[0] * Br[0] + br[1] * Br[1] + br[2] * Br[2];
+                            e0 += al[n][v] * A[n][r] + bB + ga[n][v] * D[n][r];
+                            // own b: o -> do = -g^2, do' = -2 g g', do'' = q^3 (6 b g - 2)
+                            const double bo = r == 0 ? b1 : b2;
+                            const double og = -o.g * o.g, og1 = -2.0 * o.g * o.g1;
+                            const double og2 = o.q * o.g1 * (6.0 * bo * o.g - 2.0);
+                            const double hB = h[0] * Br[0] + h[1] * Br[1] + h[2] * Br[2];
+                            const double tB = tv[n][0] * Br[0] + tv[n][1] * Br[1] + tv[n][2] * Br[2];
+                            const double eo = radial_energy(og1, og2, ui[n], ht[n]) * A[n][r] - (og1 * tB + og * hB) -
+                                              0.5 * og * D[n][r];
+                            if (r == 0) {
+                                lb1 += og * A[n][0];
+                                eb1 += eo;
+                            } else {
+                                eb2 += eo;
+                            }
+                            // own factor's nuclear derivative: du = -t_x, dt = -(e_x - t_x t) / u
+                            const double o3 = 6.0 * bo * bo * o.q * o.q * o.g1;
+                            const double o1u = o.g1 * ui[n], c2 = o.g2 - o1u;
+                            const double ct = (0.5 * (o3 + 2.0 * ui[n] * c2) + c2 * ht[n]) * A[n][r] + c2 * tB +
+                                              o.g1 * hB + 0.5 * o.g1 * D[n][r];
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) {
+                                if (r == 0) lr[n][k] -= o.g1 * tv[n][k] * A[n][r];
+                                er[n][k] += ct * tv[n][k] + o1u * (A[n][r] * h[k] + Br[k]);
+                            }
+                        }
+                    }
                 }
-                // sums over the partners by role; pl, pe the partner's b
-                double A[2] = {0.0, 0.0}, B[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, D[2] = {0.0, 0.0};
-                double pl = 0.0, pe[2] = {0.0, 0.0};
-                for (int t = 1; t < S.ne; ++t) {
-                    int lj;
-                    const int j = partner(S, L.e, t, &lj);
-                    const bool first = L.e > j;
-                    const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
-                    const Sep s = separation(d0, d1, d2);
-                    const Pade p3 = pade(b3, s.r);
-                    const double w0 = d0 * s.ri, w1 = d1 * s.ri, w2 = d2 * s.ri;
-                    const double lap = p3.g2 + 2.0 * p3.g1 * s.ri;
-                    // partner's factor p, p' = (p / r_aj)^2, dp/db = -p^2
-                    const double *gj = sG + (lj * S.n_atoms + a) * kEenGeo;
-                    const double p = sF[((lj * S.n_atoms + a) * S.een_n + m) * 2 + (first ? 1 : 0)];
-                    const double pq = p * gj[4], pd = pq * pq;
-                    const double o = first ? q[0].g : q[1].g;
-                    const double bw = (first ? be[0][0] : be[1][0]) * w0 + (first ? be[0][1] : be[1][1]) * w1 +
-                                      (first ? be[0][2] : be[1][2]) * w2;
-                    const double alr = first ? al[0] : al[1], gar = first ? ga[0] : ga[1];
-                    // functional of o s, and of o ds/db3 (ds = -s^2, ds' = -2 s s',
-                    // ds'' = q^3 (6 b s - 2))
-                    const double es = alr * p3.g + bw * p3.g1 + gar * lap;
-                    const double s3 = -p3.g * p3.g, s31 = -2.0 * p3.g * p3.g1;
-                    const double s32 = p3.q * p3.g1 * (6.0 * b3 * p3.g - 2.0);
-                    eb3 += p * (alr * s3 + bw * s31 + gar * (s32 + 2.0 * s31 * s.ri));
-                    const double op = first ? o * p : 0.0;  // the pair's value is counted at i
-                    lb3 += op * s3;
-                    const double jv = first ? o * p3.g : 0.0;
-                    pl -= p * p * jv;
+                if (need_R)
 #pragma unroll
-                    for (int r = 0; r < 2; ++r) {
-                        const double pr = first == (r == 0) ? p : 0.0;
-                        A[r] += pr * p3.g;
-                        B[r][0] += pr * p3.g1 * w0;
-                        B[r][1] += pr * p3.g1 * w1;
-                        B[r][2] += pr * p3.g1 * w2;
-                        D[r] += pr * lap;
-                        pe[r] -= pr * p * es;
-                    }
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        const double dp = -pd * gj[1 + k];
-                        lr[k] += dp * jv;
-                        er[k] += dp * es;
-                    }
-                }
-                // role 0's partners hold factor 2, role 1's factor 1
-                lb2 += pl;
-                eb2 += pe[0];
-                eb1 += pe[1];
-                l0 += q[0].g * A[0];
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    const double bB = be[r][0] * B[r][0] + be[r][1] * B[r][1] + be[r][2] * B[r][2];
-                    e0 += al[r] * A[r] + bB + ga[r] * D[r];
-                    // own b: o -> do = -g^2, do' = -2 g g', do'' = q^3 (6 b g - 2)
-                    const double bo = r == 0 ? b1 : b2;
-                    const double og = -q[r].g * q[r].g, og1 = -2.0 * q[r].g * q[r].g1;
-                    const double og2 = q[r].q * q[r].g1 * (6.0 * bo * q[r].g - 2.0);
-                    const double hB = h[0] * B[r][0] + h[1] * B[r][1] + h[2] * B[r][2];
-                    const double tB = tv[0] * B[r][0] + tv[1] * B[r][1] + tv[2] * B[r][2];
-                    const double eo = radial_energy(og1, og2, ui, ht) * A[r] - (og1 * tB + og * hB) - 0.5 * og * D[r];
-                    if (r == 0) {
-                        lb1 += og * A[0];
-                        eb1 += eo;
-                    } else {
-                        eb2 += eo;
-                    }
-                    // own factor's nuclear derivative: du = -t_x, dt = -(e_x - t_x t) / u
-                    const double o1 = q[r].g1, o2 = q[r].g2;
-                    const double o3 = 6.0 * bo * bo * q[r].q * q[r].q * o1;
-                    const double o1u = o1 * ui, c2 = o2 - o1u;
-                    const double ct = (0.5 * (o3 + 2.0 * ui * c2) + c2 * ht) * A[r] + c2 * tB + o1 * hB +
-                                      0.5 * o1 * D[r];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        if (r == 0) lr[k] -= o1 * tv[k] * A[r];
-                        er[k] += ct * tv[k] + o1u * (A[r] * h[k] + B[r][k]);
-                    }
-                }
+                    for (int n = 0; n < NA; ++n)
+                        if (a0 + n < S.n_atoms) out.add_atom(a0 + n, lr[n], er[n], kc);
             }
-            if (need_R) out.add_atom(a, lr, er, kc);
-        }
+        };
+        if (a1 == a2 && b1 == b2) term(std::integral_constant<int, 1>());
+        else term(std::integral_constant<int, 2>());
         const int at = p_een + 7 * m;
         out.put(at + 0, a1 * a2 * a3 * l0, a1 * a2 * a3 * e0);
         out.put(at + 1, c * a2 * a3 * l0, c * a2 * a3 * e0);
@@ -479,7 +515,7 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
 // them.  All outputs, as first written with LDS rows per electron, then with
 // the contractions here, then with these two and one reduction per pair of
 // results: Li2, 32 768 walkers 542 -> 254 -> 209 us (175 MB written); CO, 8192
-// walkers 564 -> 217 -> 161 us; many-body CO, 4099 walkers 2523 -> 349 -> 288 us.
+// walkers 564 -> 217 -> 161 us; many-body CO, 4099 walkers 2523 -> 349 -> 264 us.
 template <int NMO, typename RT>
 __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__restrict__ X, int64_t W,
                                                 GradOut G) {
