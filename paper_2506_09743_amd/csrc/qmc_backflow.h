@@ -36,7 +36,7 @@
 // per configuration of its spin, its g_i and, per configuration of the
 // other spin, v_i = sum over its cross partners i' of Y_ii' g_i', so the
 // cross term of a determinant is the sum of g_i . v_i over all lanes.
-// CO, 81 determinants, 8192 walkers, a Metropolis step: 278 -> 207 us (MO
+// CO, 27 determinants, 8192 walkers, a Metropolis step: 278 -> 207 us (MO
 // channels on the matrix cores, J blocks from a table).  What bounds it now:
 // one wave per SIMD at 512 registers, FP64 work, and moves between vector and
 // accumulation registers where the Y blocks are used.
@@ -250,15 +250,19 @@ struct MoChannels<kFewMO, NC> {
     }
 };
 
-// All five channels are contracted in one pass over the shells while their
-// accumulators (10 NMO registers) fit beside the Y blocks; wider tables take
-// value and psi, then the gradient.
-template <int NMO>
-constexpr int bf_channels() { return NMO <= 20 ? 5 : 3; }
+// The low-rank kernels contract all five channels in one pass over the shells
+// while their accumulators (10 NMO registers) fit beside the Y blocks; wider
+// tables, and the kernels that factorise every configuration, whose loop spills
+// what the accumulators displace, take value and psi, then the gradient.  CO, a
+// step, one pass against two: low-rank, 27 determinants, 8192 walkers 214 / 228
+// us; every configuration factorised, 100 determinants, 65 536 walkers 11.1 /
+// 10.1 ms.
+template <int NMO, bool LR>
+constexpr int bf_channels() { return LR && NMO <= 20 ? 5 : 3; }
 
-template <int NMO>
+template <int NMO, bool LR>
 constexpr size_t bf_orbital_lds_bytes() {
-    return (size_t)bf_channels<NMO>() * MoChannels<NMO, 1>::kRows * kWave * sizeof(double);
+    return (size_t)bf_channels<NMO, LR>() * MoChannels<NMO, 1>::kRows * kWave * sizeof(double);
 }
 
 // Channels C0 .. C0 + NC - 1 of the lane's MO table at q in one pass over
@@ -497,7 +501,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
             q0 = q1 = q2 = 100.0;  // a far point keeps idle lanes finite
         }
         wave_sync();  // every lane has read the J blocks
-        if constexpr (bf_channels<NMO>() == 5) {
+        if constexpr (bf_channels<NMO, LR>() == 5) {
             mo_channels_bf<NMO, 0, 5>(S, L.lane, buf, q0, q1, q2, Yii, k0, k1, k2, tab);
         } else {
             mo_channels_bf<NMO, 0, 2>(S, L.lane, buf, q0, q1, q2, Yii, k0, k1, k2, tab);
@@ -594,9 +598,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
 
     // ---- every configuration of each spin --------------------------------
     // per-configuration rows of this lane (CAP >= the system's configurations per spin)
-    // of the up and of the down spin: g for the lane's own spin, v for the other
-    double tabs[2][CAP * 3];
-    double *gtab = tabs[L.grp], *vtab = tabs[1 - L.grp];
+    double gtab[CAP * 3], vtab[CAP * 3];
     for (int q = 0; q < ncmax; ++q) {
         const bool live = q < ncfg_g;
         double t1 = 0.0, clog = -INFINITY, csgn = 0.0;
@@ -836,26 +838,19 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     double cr = 0.0, gb0 = 0.0, gb1 = 0.0, gb2 = 0.0;
     if (L.active && !zero) {
         // cross term: every lane adds g_i . v_i over its share of the pairs
-        // for each determinant, in the same order on every lane.  The up
-        // configuration's vector is read once per run of determinants that
-        // share it; four determinants' loads are in flight at once.
+        // for each determinant.  The loop runs over the determinants in the
+        // same order on every lane, unrolled so that several determinants'
+        // loads are in flight at once.
         const double *scu = sCfg + 4, *scd = sCfg + 5 * S.n_cfg_max + 4;
         const auto *det_cfg = const_tab((const int *)S.det_cfg);  // (up, down) configuration pairs
         const auto *ci_x = const_tab(S.ci_x);
-        int last = -1;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, su = 0.0;
 #pragma unroll 4
         for (int n = 0; n < S.n_det_x; ++n) {
             const int cu = det_cfg[2 * n], cd = det_cfg[2 * n + 1];
-            if (cu != last) {
-                last = cu;
-                a0 = tabs[0][3 * cu];
-                a1 = tabs[0][3 * cu + 1];
-                a2 = tabs[0][3 * cu + 2];
-                su = scu[5 * cu];
-            }
-            const double w = ci_x[n] * su * scd[5 * cd];
-            const double gv = a0 * tabs[1][3 * cd] + a1 * tabs[1][3 * cd + 1] + a2 * tabs[1][3 * cd + 2];
+            const double w = ci_x[n] * scu[5 * cu] * scd[5 * cd];
+            const int own = L.grp ? cd : cu, oth = L.grp ? cu : cd;
+            const double gv = gtab[3 * own] * vtab[3 * oth] + gtab[3 * own + 1] * vtab[3 * oth + 1] +
+                              gtab[3 * own + 2] * vtab[3 * oth + 2];
             cr += w != 0.0 ? w * gv : 0.0;  // a vanishing weight drops the term whatever g is
         }
         cr *= Sinv;

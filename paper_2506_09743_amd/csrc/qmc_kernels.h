@@ -543,7 +543,7 @@ static hipError_t launch_t(bool mc, const DevSystem &S, double *X, double *LP, d
     constexpr bool kMixed = sizeof(RT) != sizeof(double);
     const int64_t blocks = (W + S.WPW - 1) / S.WPW;
     size_t lds = (size_t)S.WPW * lds_per_walker<NMO, RT, EXPL, BF>(S) * sizeof(double);
-    const size_t rows = BF ? bf_orbital_lds_bytes<NMO>() : orbital_lds_bytes<NMO>();
+    const size_t rows = BF ? bf_orbital_lds_bytes<NMO, !EXPL>() : orbital_lds_bytes<NMO>();
     if (lds < rows) lds = rows;
     if (MF > 0 && lds < (size_t)kStageBytes) lds = kStageBytes;
     const hipStream_t st = cs.st;
