@@ -62,8 +62,8 @@ def mixed_peak(form: str) -> dict:
             "bf16_flop": f_val if form.startswith("bf16") else 0.0}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "co_metropolis_traffic.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2506_09743_amd", "csrc", f)
-                  for f in ("qmc_kernels.h", "qmc_form_fp64.hip", "qmc_walker.h", "qmc_backflow.h",
-                            "qmc_device.h", "qmc_api.hip")]
+                  for f in ("qmc_kernels.h", "qmc_form_fp64.hip", "qmc_walker.h", "qmc_orbitals.h", "qmc_exp.h",
+                            "qmc_backflow.h", "qmc_device.h", "qmc_api.hip")]
 
 
 def flops_per_walker_step(sysd) -> dict:
