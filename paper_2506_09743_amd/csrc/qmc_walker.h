@@ -505,7 +505,11 @@ __host__ __device__ inline int walker_lds(const DevSystem &S) {
 // Separation of two points: r, 1 / r.  The hardware reciprocal root with one
 // third-order step, and r corrected by its residual: the root within half an
 // ulp or so, its reciprocal within an ulp, without the scaling and division
-// of the full-range functions.
+// of the full-range functions.  The refinement forms 0 * inf at r = 0 (an
+// electron on a nucleus, or on another one, where every Jastrow term is finite)
+// and at an infinite r; the division fix-up puts in the values of r2 / 1 and
+// 1 / r2 there, 0 and inf.  (Many-body CO block of 16 384 walkers, 10 steps:
+// 1105 us without it, 1113 so, 1156 by a comparison and selects.)
 struct Sep {
     double r, ri;
 };
@@ -515,8 +519,9 @@ __device__ __forceinline__ Sep separation(double d0, double d1, double d2) {
     double y = __builtin_amdgcn_rsq(r2);
     const double e = __builtin_fma(-(r2 * y), y, 1.0);
     y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
-    const double r = r2 * y;
-    return {__builtin_fma(__builtin_fma(-r, r, r2), 0.5 * y, r), y};
+    double r = r2 * y;
+    r = __builtin_fma(__builtin_fma(-r, r, r2), 0.5 * y, r);
+    return {__builtin_amdgcn_div_fixup(r, 1.0, r2), __builtin_amdgcn_div_fixup(y, r2, 1.0)};
 }
 
 // Partner t = 1 .. N_e - 1 of electron e, cyclic, and its lane in the walker:
