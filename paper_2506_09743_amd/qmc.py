@@ -299,7 +299,8 @@ class System:
         g_logpsi and g_eloc [W] applied to the outputs of grad()."""
         import torch
         W, P, A = g_logpsi.shape[0], self.param_count, self.n_atoms
-        dl, de, dlR, deR = jac
+        # a lazily negated tensor's memory holds the opposite sign
+        g_logpsi, g_eloc, dl, de, dlR, deR = (t.resolve_neg() for t in (g_logpsi, g_eloc, *jac))
         out = torch.empty(P + 3 * A, dtype=torch.float64, device=dl.device)
         work = torch.empty(lib().qmc_vjp_work_bytes(self.handle, W) // 8, dtype=torch.float64, device=dl.device)
         _check(lib().qmc_vjp(self.handle, _dev_ptr(g_logpsi, "g_logpsi", (W,)), _dev_ptr(g_eloc, "g_eloc", (W,)),
