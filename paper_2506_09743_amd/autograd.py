@@ -105,9 +105,12 @@ class Wavefunction:
 
 
 def _readable(t) -> bool:
-    """Whether t's memory can be passed to a kernel (not under vmap and the like)."""
+    """Whether t's memory can be passed to a kernel: not under vmap and the
+    like, nor a subclass or a zero tensor that holds its values elsewhere."""
+    if type(t) is not torch.Tensor:
+        return False
     try:
-        return t.data_ptr() is not None
+        return t.data_ptr() != 0 or t.numel() == 0
     except RuntimeError:
         return False
 

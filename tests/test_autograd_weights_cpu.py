@@ -102,3 +102,46 @@ def test_vjp_resolves_every_operand(host_lib, which):
     args[which] = torch._neg_view(-args[which])
     got = s.vjp(args[0], args[1], args[2:])
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+class _Held(torch.Tensor):
+    """A tensor that keeps its values in another one and has no memory itself."""
+
+    @staticmethod
+    def __new__(cls, t):
+        return torch.Tensor._make_wrapper_subclass(cls, t.shape, dtype=t.dtype, device=t.device)
+
+    def __init__(self, t):
+        self.t = t
+
+    @classmethod
+    def __torch_dispatch__(cls, f, types, args=(), kw=None):
+        def plain(t):
+            return t.t if isinstance(t, _Held) else t
+        out = f(*torch.utils._pytree.tree_map(plain, args), **torch.utils._pytree.tree_map(plain, kw or {}))
+        return torch.utils._pytree.tree_map(lambda t: _Held(t) if isinstance(t, torch.Tensor) else t, out)
+
+
+def _values(t):
+    return t.t if isinstance(t, _Held) else t
+
+
+@pytest.mark.parametrize("kind", ["subclass", "zero", "plain", "none"])
+def test_weights_without_memory(host_lib, kind):
+    """Weights that a kernel cannot read (a wrapper subclass, torch's zero
+    tensors without storage) take the torch products, the others the kernel."""
+    s, jac, lib = host_lib
+    from paper_2506_09743_amd import autograd as ag
+    wf = _Wf(s)
+    n = 0 if kind == "none" else W
+    lp, _, el = ag.psi_eloc(wf, torch.zeros(n, 2, 3, dtype=torch.float64))
+    v = _weights(n, False)
+    g = {"subclass": _Held(v), "zero": torch._efficientzerotensor((n,), dtype=torch.float64)}.get(kind, v)
+    assert kind in ("plain", "none") or g.data_ptr() == 0
+    lib.calls = 0
+    got = torch.autograd.grad((lp, el), (wf.theta, wf.R), (g, g))
+    assert lib.calls == (1 if kind in ("plain", "none") else 0)
+    v = torch.zeros(n, dtype=torch.float64) if kind == "zero" else v
+    want = (v @ (jac[0] + jac[1])[:n], torch.einsum("w,wak->ak", v, (jac[2] + jac[3])[:n]))
+    for a, b in zip(got, want):
+        assert torch.allclose(_values(a), b, rtol=1e-14, atol=1e-14)
