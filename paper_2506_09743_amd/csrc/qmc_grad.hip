@@ -233,15 +233,17 @@ __device__ __forceinline__ void put_mo_gradient(const DevSystem &S, int lane, in
 
 // Sums over a walker's electrons of a derivative of log|Psi| and of E_L.  The
 // walker's first lane keeps the first, the first lane of its upper half the
-// second (span_sum_pair).
+// second (span_sum_pair).  Idle lanes add zeros, whatever they bring (NaN with a
+// nucleus at their far point).
 struct WalkerOut {
     double *param;  // this lane's row of the parameter output, or NULL
     double *atom;   // this lane's column of the walker's nuclear sums in LDS, or NULL
     int LW;
-    bool upper;
+    bool upper, active;
 
     __device__ __forceinline__ WalkerOut(const GradOut &G, const Lane &L, int LW_, int64_t w, double *sAtom) {
         LW = LW_;
+        active = L.active;
         upper = L.lw >= LW / 2;
         param = atom = nullptr;
         if (L.wvalid && (L.lw == 0 || L.lw == LW / 2)) {
@@ -251,13 +253,13 @@ struct WalkerOut {
         }
     }
     __device__ __forceinline__ void put(int at, double l, double e) const {
-        const double v = span_sum_pair(l, e, LW, upper);
+        const double v = span_sum_pair(active ? l : 0.0, active ? e : 0.0, LW, upper);
         if (param) param[at] = v;
     }
     __device__ __forceinline__ void add_atom(int a, const double (&l)[3], const double (&e)[3], double f = 1.0) const {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const double v = span_sum_pair(f * l[k], f * e[k], LW, upper);
+            const double v = span_sum_pair(active ? f * l[k] : 0.0, active ? f * e[k] : 0.0, LW, upper);
             if (atom) atom[6 * a + k] += v;
         }
     }
@@ -813,9 +815,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
             }
             const double qg = qv[0] * gJ[0] + qv[1] * gJ[1] + qv[2] * gJ[2];
             // one pass over the primitives: radial sums and exponent derivatives
-            // (idle lanes: zero sums, so their shares vanish)
-            const double on = L.active ? 1.0 : 0.0;
-            const ExpoSums z = {on * q, on * (qd + qL + 2.0 * qg), on * (2.0 * gd * q)};
+            const ExpoSums z = {q, qd + qL + 2.0 * qg, 2.0 * gd * q};
             const double rk = S.basis == 0 ? power(r, si.z) : 1.0;
             Radial R = {0.0, 0.0, 0.0, 0.0, 0.0};
             for (int i = 0; i < si.w; ++i) {
