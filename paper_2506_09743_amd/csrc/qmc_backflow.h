@@ -793,28 +793,29 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
     }
 
     // ---- Sigma, configuration weights ------------------------------------
+    const int lw = lane_now() & (LW - 1);
     double mu = -INFINITY, md = -INFINITY;
-    for (int q = L.lw; q < S.n_cfg_up; q += LW) mu = fmax(mu, sCfg[5 * q]);
-    for (int q = L.lw; q < S.n_cfg_dn; q += LW) md = fmax(md, sCfg[5 * (S.n_cfg_max + q)]);
+    for (int q = lw; q < S.n_cfg_up; q += LW) mu = fmax(mu, sCfg[5 * q]);
+    for (int q = lw; q < S.n_cfg_dn; q += LW) md = fmax(md, sCfg[5 * (S.n_cfg_max + q)]);
     mu = walker_max(mu, LW);
     md = walker_max(md, LW);
     const bool none = mu == -INFINITY || md == -INFINITY;
     // scaled determinant values sign * exp(log|D| - shift)
-    for (int q = L.lw; q < S.n_cfg_up + S.n_cfg_dn; q += LW) {
+    for (int q = lw; q < S.n_cfg_up + S.n_cfg_dn; q += LW) {
         const int sp = q < S.n_cfg_up ? 0 : 1;
         double *own = sCfg + 5 * (sp * S.n_cfg_max + (sp ? q - S.n_cfg_up : q));
         own[4] = none ? 0.0 : own[1] * exp(own[0] - (sp ? md : mu));
     }
     wave_sync();
     double Sp = 0.0;
-    for (int n = L.lw; n < S.n_det_x; n += LW) {
+    for (int n = lw; n < S.n_det_x; n += LW) {
         const int2 dc = S.det_cfg[n];
         Sp += S.ci_x[n] * sCfg[5 * dc.x + 4] * sCfg[5 * (S.n_cfg_max + dc.y) + 4];
     }
     const double Ssum = walker_sum(Sp, LW);
     const bool zero = none || Ssum == 0.0 || !isfinite(Ssum);
     const double Sinv = zero ? 0.0 : 1.0 / Ssum;
-    for (int q = L.lw; q < S.n_cfg_up + S.n_cfg_dn; q += LW) {
+    for (int q = lw; q < S.n_cfg_up + S.n_cfg_dn; q += LW) {
         const int sp = q < S.n_cfg_up ? 0 : 1;
         const int cq = sp ? q - S.n_cfg_up : q;
         double *own = sCfg + 5 * (sp * S.n_cfg_max + cq);
@@ -830,7 +831,7 @@ __device__ __forceinline__ void backflow_dets(const DevSystem &S, const Lane &L,
 
     // ---- sum_c W_c L_c, cross term, weighted g ----------------------------
     double lp = 0.0;
-    for (int q = L.lw; q < S.n_cfg_up + S.n_cfg_dn; q += LW) {
+    for (int q = lw; q < S.n_cfg_up + S.n_cfg_dn; q += LW) {
         const int sp = q < S.n_cfg_up ? 0 : 1;
         const double *own = sCfg + 5 * (sp * S.n_cfg_max + (sp ? q - S.n_cfg_up : q));
         if (own[2] != 0.0) lp += own[2] * own[3];

@@ -295,16 +295,17 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
     const bool need_R = G.dlogpsi_dR || G.deloc_dR;
     const int p_b = S.n_prim + S.n_ao * S.n_mo;  // output index of b
     const int p_en = p_b + 1, p_een = p_en + (S.jas_en ? 3 * S.n_atoms : 0);
+    const int e_ = L.active ? L.e : 0;  // idle lanes take electron 0's partners
     // ---- Pade b: K = a g, dK/db = -a g^2 ------------------------------------
     double dl = 0.0, de = 0.0;
-    if (L.active) {
+    {
 #pragma unroll 2
         for (int t = 1; t < S.ne; ++t) {
             int lj;
-            const int j = partner(S, L.e, t, &lj);
+            const int j = partner(S, e_, t, &lj);
             const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
             const Sep s = separation(d0, d1, d2);
-            const double a = (j < S.n_up) == (L.e < S.n_up) ? S.a_par : S.a_anti;
+            const double a = (j < S.n_up) == (e_ < S.n_up) ? S.a_par : S.a_anti;
             const Pade p = pade(S.b, s.r);
             const double hw = (h[0] * d0 + h[1] * d1 + h[2] * d2) * s.ri;
             dl -= 0.5 * a * p.g * p.g;
@@ -317,7 +318,7 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
         for (int a = 0; a < S.n_atoms; ++a) {
             double l3[3] = {0.0, 0.0, 0.0}, e3[3] = {0.0, 0.0, 0.0};
             double lr[3] = {0.0, 0.0, 0.0}, er[3] = {0.0, 0.0, 0.0};
-            if (L.active) {
+            {
                 const auto *R = const_tab(S.atoms) + 4 * a;
                 const auto *wn = const_tab(S.jas_en) + 3 * a;
                 const double d[3] = {x0 - R[0], x1 - R[1], x2 - R[2]};
@@ -367,7 +368,7 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
             constexpr int NR = decltype(roles)::value, NA = NR == 1 ? 2 : 1;
             for (int a0 = 0; a0 < S.n_atoms; a0 += NA) {
                 double lr[NA][3] = {}, er[NA][3] = {};
-                if (L.active) {
+                {
                     double ui[NA], tv[NA][3], ht[NA], al[NA][NR], be[NA][NR][3], ga[NA][NR];
                     Pade q[NA][NR];
                     const double *fj[NA];  // partner 0's table entries of the nucleus
@@ -396,8 +397,8 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
                     double pl = 0.0, pe[2] = {0.0, 0.0};
                     for (int t = 1; t < S.ne; ++t) {
                         int lj;
-                        const int j = partner(S, L.e, t, &lj);
-                        const bool first = L.e > j;
+                        const int j = partner(S, e_, t, &lj);
+                        const bool first = e_ > j;
                         const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
                         const Sep s = separation(d0, d1, d2);
                         const Pade p3 = pade(b3, s.r);
@@ -825,7 +826,7 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
                 out.put(p + i, gl, ge);
             }
             p += si.w;
-            if (L.active) {
+            {
                 const double d[3] = {a.dx, a.dy, a.dz};
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
@@ -862,14 +863,12 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
     }
     // e-n attraction
     for (int a = 0; a < S.n_atoms; ++a) {
-        double er[3] = {0.0, 0.0, 0.0};
-        if (L.active) {
-            const auto *A = const_tab(S.atoms) + 4 * a;
-            const double d[3] = {x0 - A[0], x1 - A[1], x2 - A[2]};
-            const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-            const double f = -A[3] / (rr * rr * rr);
-            for (int k = 0; k < 3; ++k) er[k] = f * d[k];
-        }
+        double er[3];
+        const auto *A = const_tab(S.atoms) + 4 * a;
+        const double d[3] = {x0 - A[0], x1 - A[1], x2 - A[2]};
+        const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        const double f = -A[3] / (rr * rr * rr);
+        for (int k = 0; k < 3; ++k) er[k] = f * d[k];
         const double none[3] = {0.0, 0.0, 0.0};
         out.add_atom(a, none, er);
     }
@@ -877,8 +876,9 @@ __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__res
     // ---- Jastrow parameters and the Jastrow part of the nuclear gradients ---
     wave_sync();  // the rings and rows are no longer read
     {
-        double *sP = wsm;                                   // [LW][3]
-        double *sF = wsm + 3 * S.LW;                        // [LW][n_atoms][2 een_n]
+        L = make_lane(S, wave_first, W, &w, lane_now());
+        double *sP = smem + L.wloc * grad_walker<NMO>(S);   // [LW][3]
+        double *sF = sP + 3 * S.LW;                         // [LW][n_atoms][2 een_n]
         double *sG = sF + S.LW * S.n_atoms * 2 * S.een_n;   // [LW][n_atoms][kEenGeo]
         sP[3 * L.lw + 0] = x0;
         sP[3 * L.lw + 1] = x1;

@@ -44,7 +44,7 @@ __device__ __forceinline__ WalkerResult eval_walker(const DevSystem &S, const La
         gS2 = c.bgS2;
         lapS = c.blap;
     } else {
-        sigma_derivs<NMO, RT, VK>(S, L.lane, (double *)stage, x0, x1, x2, c.av, gS0, gS1, gS2, lapS);
+        sigma_derivs<NMO, RT, VK>(S, lane_now(), (double *)stage, x0, x1, x2, c.av, gS0, gS1, gS2, lapS);
     }
 
     // ---- local energy and log|Psi| ------------------------------------------

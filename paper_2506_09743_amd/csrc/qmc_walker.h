@@ -194,10 +194,12 @@ struct Lane {
     bool active; // owns a real electron of a valid walker
 };
 
-// The lane's index, formed anew where it stands.  A value kept across the
-// adjoint's divergent blocks may be moved to the accumulation registers at the
-// end of one, before the masked lanes are back, and is then undefined in them;
-// indexes that idle lanes load with are taken from here instead.
+// The lane's index, formed anew where it stands.  The compiler has moved a value
+// kept across a divergent block to the accumulation registers at the block's
+// end, before the masked lanes were back, which leaves it undefined in them.
+// So indexes that idle lanes load global tables with are taken from here, idle
+// lanes run the pair loops with the others instead of being masked, and
+// what they hold is dropped by selects.
 __device__ __forceinline__ int lane_now() {
     int z = 0;
     asm volatile("" : "+s"(z));
@@ -552,7 +554,7 @@ __device__ __forceinline__ Pade pade(double b, double r) {
 template <bool GEO>
 __device__ __forceinline__ void een_table_fill(const DevSystem &S, const Lane &L, double x0, double x1, double x2,
                                                double *sF, double *sG) {
-    if (S.een_n == 0 || !L.active) return;
+    if (S.een_n == 0) return;
     for (int a = 0; a < S.n_atoms; ++a) {
         const auto *R = const_tab(S.atoms) + 4 * a;
         const double e0 = x0 - R[0], e1 = x1 - R[1], e2 = x2 - R[2];
@@ -583,16 +585,17 @@ struct JasTerms {
 // e-e-n kernels of the many-body appendix) of the lane's electron: its share
 // of J, grad_e J and lap_e J, and its Coulomb terms (eq. Hmol: half of each
 // e-e pair, the e-n attraction).  sPos holds the walker's positions, sF the
-// e-e-n factors of een_table_fill.
+// e-e-n factors of een_table_fill.  Idle lanes take electron 0's partners and
+// return zeros.
 __device__ __forceinline__ JasTerms jastrow_terms(const DevSystem &S, const Lane &L, double x0, double x1, double x2,
                                                   const double *sPos, const double *sF) {
     JasTerms o = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (!L.active) return o;
-    const bool up = L.e < S.n_up;
+    const int e = L.active ? L.e : 0;
+    const bool up = e < S.n_up;
 #pragma unroll 2
     for (int t = 1; t < S.ne; ++t) {
         int lj;
-        const int j = partner(S, L.e, t, &lj);
+        const int j = partner(S, e, t, &lj);
         const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
         const Sep s = separation(d0, d1, d2);
         const double a = (j < S.n_up) == up ? S.a_par : S.a_anti;
@@ -654,8 +657,8 @@ __device__ __forceinline__ JasTerms jastrow_terms(const DevSystem &S, const Lane
 #pragma unroll 2
                 for (int t = 1; t < S.ne; ++t) {
                     int lj;
-                    const int j = partner(S, L.e, t, &lj);
-                    const bool first = L.e > j;
+                    const int j = partner(S, e, t, &lj);
+                    const bool first = e > j;
                     const double d0 = x0 - sPos[3 * lj], d1 = x1 - sPos[3 * lj + 1], d2 = x2 - sPos[3 * lj + 2];
                     const Sep s = separation(d0, d1, d2);
                     const Pade p = pade(b3, s.r);
@@ -699,7 +702,8 @@ __device__ __forceinline__ JasTerms jastrow_terms(const DevSystem &S, const Lane
         if (tm[1] == tm[3] && tm[2] == tm[4]) term(std::integral_constant<int, 1>());
         else term(std::integral_constant<int, 2>());
     }
-    return o;
+    auto own = [&](double v) { return L.active ? v : 0.0; };
+    return {own(o.J), own(o.g0), own(o.g1), own(o.g2), own(o.lap), own(o.vpot)};
 }
 
 // Per-lane results of the stages every evaluation shares.
@@ -947,7 +951,7 @@ __device__ __forceinline__ void core_stages(const DevSystem &S, const Lane &L, d
     // ---- S = sum_n d_n det T_up[H,P] det T_dn[H,P] ----------------------
     // records are loaded kRecBatch at a time so their latencies overlap
     const double *Tup = sT, *Tdn = sT + tstride;
-    const int lw = FULLT ? lane_now() & (S.LW - 1) : L.lw;
+    const int lw = lane_now() & (S.LW - 1);
     double Sp = 0.0;
     for (int i0 = 0; i0 < S.det_rows; i0 += kRecBatch) {
         uint4v rb[kRecBatch];
@@ -1201,15 +1205,16 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
     wave_sync();
 
     // common shifts, Sigma / (e^mu e^md)
+    const int lw = lane_now() & (S.LW - 1);
     double mu = -INFINITY, md = -INFINITY;
-    for (int q = L.lw; q < S.n_cfg_up; q += S.LW) mu = fmax(mu, sCfg[3 * q]);
-    for (int q = L.lw; q < S.n_cfg_dn; q += S.LW) md = fmax(md, sCfg[3 * (S.n_cfg_max + q)]);
+    for (int q = lw; q < S.n_cfg_up; q += S.LW) mu = fmax(mu, sCfg[3 * q]);
+    for (int q = lw; q < S.n_cfg_dn; q += S.LW) md = fmax(md, sCfg[3 * (S.n_cfg_max + q)]);
     mu = walker_max(mu, S.LW);
     md = walker_max(md, S.LW);
     const bool none = mu == -INFINITY || md == -INFINITY;
     double Sp = 0.0;
     if (!none)
-        for (int n = L.lw; n < S.n_det_x; n += S.LW) {
+        for (int n = lw; n < S.n_det_x; n += S.LW) {
             const int2 dc = S.det_cfg[n];
             const double *u = sCfg + 3 * dc.x, *v = sCfg + 3 * (S.n_cfg_max + dc.y);
             Sp += S.ci_x[n] * u[1] * v[1] * exp((u[0] - mu) + (v[0] - md));
@@ -1218,7 +1223,7 @@ __device__ __forceinline__ void explicit_dets(const DevSystem &S, const Lane &L,
     const bool zero = none || Ssum == 0.0 || !isfinite(Ssum);
 
     // weights W_c (the lanes split both spins' configurations)
-    for (int q = L.lw; q < S.n_cfg_up + S.n_cfg_dn; q += S.LW) {
+    for (int q = lw; q < S.n_cfg_up + S.n_cfg_dn; q += S.LW) {
         const int sp = q < S.n_cfg_up ? 0 : 1;
         const int cq = sp ? q - S.n_cfg_up : q;
         double *own = sCfg + 3 * (sp * S.n_cfg_max + cq);
