@@ -308,8 +308,21 @@ __device__ __forceinline__ void metropolis_wave(const DevSystem &S0, const Lane 
     }
 }
 
+// Waves per SIMD that the FP64 evaluation is compiled for: at one the compiler
+// holds the contractions' accumulators in registers of their own, 148 for 12 MOs
+// and 184 for 20, a wave fewer per SIMD than with 124 and 144, and a grid of that
+// many waves then takes one more round.  (LiH, 4096 waves 37.8 -> 31.1 us; CO,
+// 2502 waves 79.5 -> 63.8 us.)  16 MOs keep three waves either way; wider tables
+// are faster at two (24 MOs, 4096 waves: 89 us, at three 99).
 template <int NMO, typename RT, int MF, bool EXPL, int BF>
-__global__ __launch_bounds__(kWave, (MF > 0 ? 2 : 1)) void k_eval(DevSystem S, const double *__restrict__ X, int64_t W,
+constexpr int eval_waves() {
+    if (EXPL || BF) return 1;
+    if (sizeof(RT) == sizeof(float)) return MF > 0 ? 2 : 1;
+    return NMO <= 12 ? 4 : NMO == 20 ? 3 : 1;
+}
+
+template <int NMO, typename RT, int MF, bool EXPL, int BF>
+__global__ __launch_bounds__(kWave, (eval_waves<NMO, RT, MF, EXPL, BF>())) void k_eval(DevSystem S, const double *__restrict__ X, int64_t W,
                                                  double *__restrict__ LP, double *__restrict__ SG,
                                                  double *__restrict__ EL) {
     extern __shared__ double smem[];
@@ -449,8 +462,11 @@ __global__ __launch_bounds__(kWave, 3) void k_refine(DevSystem S, double *__rest
 // coordinates (Psi only: no cofactor tables, no derivative passes), then
 // lap Psi / Psi = sum_c (Psi(x + h e_c) - 2 Psi(x) + Psi(x - h e_c)) / (h^2 Psi(x)).
 // The potential is taken at x.  FP64, low-rank determinants.
+// Compiled for three waves per SIMD up to 12 MOs and two above, for the reason at
+// eval_waves (208 and 328 registers at 12 and 32 MOs otherwise; LiH, 2560 waves
+// 417 -> 295 us; 24 MOs, 4096 waves 5.56 -> 3.63 ms).
 template <int NMO>
-__global__ __launch_bounds__(kWave, 1) void k_eval_fd(DevSystem S, const double *__restrict__ X, int64_t W, double h,
+__global__ __launch_bounds__(kWave, (NMO <= 12 ? 3 : 2)) void k_eval_fd(DevSystem S, const double *__restrict__ X, int64_t W, double h,
                                                       double *__restrict__ LP, double *__restrict__ EL) {
     extern __shared__ double smem[];
     int64_t w;

@@ -8,33 +8,19 @@ destination is written nowhere else in the kernel.  Nothing in the source rules
 it out, so every build is searched for it."""
 import re
 import shutil
-import struct
 import subprocess
 from concurrent.futures import ProcessPoolExecutor
 
 import pytest
 
-OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
+from built_code import code_objects, llvm_tool
+
+OBJDUMP = llvm_tool("llvm-objdump")
 # instructions whose first operand is not a vector register that they write
 NO_DST = ("global_store", "ds_write", "scratch_store", "flat_store", "buffer_store", "s_", "v_cmp", "v_readlane",
           "v_readfirstlane")
 LINE = re.compile(r"\t(\S+)\s*([^/]*?)\s*//\s*([0-9A-F]+):")
 REG = re.compile(r"([va])(?:(\d+)|\[(\d+):(\d+)\])$")
-
-
-def code_objects(lib):
-    """The gfx950 code objects bundled in a library built here."""
-    data = open(lib, "rb").read()
-    at, out = 0, []
-    while (at := data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
-        (n,), p = struct.unpack_from("<Q", data, at + 24), at + 32
-        for _ in range(n):
-            off, size, length = struct.unpack_from("<QQQ", data, p)
-            if b"gfx950" in data[p + 24:p + 24 + length] and size:
-                out.append(data[at + off:at + off + size])
-            p += 24 + length
-        at += 24
-    return out
 
 
 def registers(operand):
