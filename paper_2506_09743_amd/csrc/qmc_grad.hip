@@ -324,12 +324,14 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
                 const double d[3] = {x0 - R[0], x1 - R[1], x2 - R[2]};
                 const Sep s = separation(d[0], d[1], d[2]);
                 const double r = s.r, w0 = wn[0], w1 = wn[1], w2 = wn[2];
-                const Pade p = pade(w2, r);
+                // (the full division as in the value; w2 q first, 2 w2 may overflow)
+                const double q = 1.0 / (1.0 + w2 * r), wq = w2 * q;
+                const Pade p = {q, r * q, q * q, -2.0 * wq * q * q};
                 const double u[3] = {d[0] * s.ri, d[1] * s.ri, d[2] * s.ri};
                 const double hu = h[0] * u[0] + h[1] * u[1] + h[2] * u[2];
                 // K = (w0 r + w1 r^2) q and its derivatives in r
                 const double K = (w0 + w1 * r) * p.g, K1 = (w0 + 2.0 * w1 * r - K * w2) * p.q;
-                const double K2 = (2.0 * w1 - 2.0 * K1 * w2) * p.q, K3 = -3.0 * w2 * K2 * p.q;
+                const double K2 = (2.0 * w1 - 2.0 * K1 * w2) * p.q, K3 = -3.0 * wq * K2;
                 // dK/dw0 = g, dK/dw1 = r g, dK/dw2 = -K g
                 l3[0] = p.g;
                 e3[0] = radial_energy(p.g1, p.g2, s.ri, hu);

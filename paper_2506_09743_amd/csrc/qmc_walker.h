@@ -615,9 +615,10 @@ __device__ __forceinline__ JasTerms jastrow_terms(const DevSystem &S, const Lane
         o.vpot -= R[3] * s.ri;
         if (S.jas_en) {
             // e-n kernel K = N / D, N = w0 r + w1 r^2, D = 1 + w2 r:
-            // K' = (N' - K D') / D and K'' = (N'' - 2 K' D') / D
+            // K' = (N' - K D') / D and K'' = (N'' - 2 K' D') / D.  One division
+            // per nucleus, so the full one: D may be past the largest double.
             const auto *w = const_tab(S.jas_en) + 3 * a;
-            const double q = rcp_ge1(1.0 + w[2] * s.r);
+            const double q = 1.0 / (1.0 + w[2] * s.r);
             const double K = (w[0] + w[1] * s.r) * s.r * q;
             const double K1 = (w[0] + 2.0 * w[1] * s.r - K * w[2]) * q;
             const double K2 = (2.0 * w[1] - 2.0 * K1 * w[2]) * q;

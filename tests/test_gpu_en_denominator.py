@@ -1,0 +1,32 @@
+"""The e-n kernel K(r) = (w0 r + w1 r^2) / (1 + w2 r) over the range of w2 that a
+system may have: a denominator past the largest double ends the kernel.  From
+w2 = 1e300 on K and its derivatives are below 1e-299, so the reference is the
+oracle without the numerators (its own derivatives square w2 and overflow)."""
+import numpy as np
+import pytest
+
+from paper_2506_09743_amd import synth
+from parity_helpers import _compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("w2", [0.0, 1e3, 1e150, 1e307, 1e308, 1.7e308])
+def test_en_denominator(torch_cuda, qmc, oracle_mod, w2):
+    torch = torch_cuda
+    sysd = synth.with_many_body_jastrow(synth.make_system("LiH"), synth.MBJ_SEED["LiH"])
+    sysd["jas_en"] = np.array(sysd["jas_en"])
+    sysd["jas_en"][:, 2] = w2
+    X = synth.init_walkers(sysd, 33, 7)
+    s = qmc.System(sysd, device=0)
+    tX = torch.from_numpy(X).cuda()
+    lp, sg, el = [t.cpu().numpy() for t in s.eval(tX)]
+    ref = dict(sysd, jas_en=np.array(sysd["jas_en"]))
+    if w2 >= 1e300:
+        ref["jas_en"][:] = 0.0
+    _compare(oracle_mod.OracleSystem(ref), ref, X, lp, sg, el, f"e-n w2={w2:g}")
+    assert np.isfinite(lp).all() and np.isfinite(el).all()
+    flp, fel = [t.cpu().numpy() for t in s.eval_fd(tX)]
+    assert np.isfinite(flp).all() and np.isfinite(fel).all()
+    assert all(np.isfinite(g.cpu().numpy()).all() for g in s.grad(tX))
+    s.close()
