@@ -568,7 +568,9 @@ qmc_status qmc_system_create(const qmc_system_desc *d, int32_t device, qmc_syste
     S.n_prim = (int)prims.size();
     S.a_par = d->jas_a_par;
     S.a_anti = d->jas_a_anti;
-    S.b = d->jas_b;
+    // The kernel is zero to every digit of log|Psi| from far smaller values on, and
+    // 1 + b r must stay a number whose reciprocal is.
+    S.b = std::min(d->jas_b, 1e300);
     S.vnn = vnn;
     S.atoms = (const double *)(base + o_atoms);
     S.shells = (const int4 *)(base + o_shells);

@@ -30,3 +30,19 @@ def test_en_denominator(torch_cuda, qmc, oracle_mod, w2):
     assert np.isfinite(flp).all() and np.isfinite(fel).all()
     assert all(np.isfinite(g.cpu().numpy()).all() for g in s.grad(tX))
     s.close()
+
+
+@pytest.mark.parametrize("b", [0.0, 1e3, 1e150, 1e307, 1e308, 1.7e308])
+def test_pade_denominator(torch_cuda, qmc, oracle_mod, b):
+    """The same for the e-e kernel a r / (1 + b r)."""
+    torch = torch_cuda
+    sysd = dict(synth.make_system("LiH"), jas_b=b)
+    X = synth.init_walkers(sysd, 33, 7)
+    s = qmc.System(sysd, device=0)
+    tX = torch.from_numpy(X).cuda()
+    lp, sg, el = [t.cpu().numpy() for t in s.eval(tX)]
+    ref = dict(sysd, jas_a_par=0.0, jas_a_anti=0.0) if b >= 1e300 else sysd
+    _compare(oracle_mod.OracleSystem(ref), ref, X, lp, sg, el, f"e-e b={b:g}")
+    assert np.isfinite(lp).all() and np.isfinite(el).all()
+    assert all(np.isfinite(g.cpu().numpy()).all() for g in s.grad(tX))
+    s.close()
