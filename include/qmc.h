@@ -96,7 +96,9 @@ typedef enum {
    with QMC_FP64 to rounding; a walker whose reference matrix is singular but
    whose CI sum is not gets finite values here.  It returns QMC_EUNSUPPORTED
    when the per-walker tables (growing with the number of distinct
-   configurations) exceed the 160 KiB of LDS of a compute unit.
+   configurations, and with e-e-n terms 2 jas_een_n + 5 doubles per lane and
+   nucleus) exceed the 160 KiB of LDS of a compute unit; so do both methods
+   with backflow.
    With backflow (bf_omega != 0) only FP64 exists and the mixed forms return
    QMC_EUNSUPPORTED.  QMC_FP64 factorises the reference matrices only and
    updates every configuration from them by the rank <= 2 identity of
@@ -237,9 +239,11 @@ qmc_status qmc_eval_eloc_fd(qmc_system *sys, const double *d_X, int64_t W, doubl
    and the MO value contraction of the forward evaluation in FP32, as in
    qmc_eval_psi_eloc's mixed form without its FP64 re-evaluation; every
    derivative pass FP64); the other forms return QMC_EUNSUPPORTED, a value
-   outside qmc_precision QMC_EINVAL.  Returns QMC_EUNSUPPORTED when the
-   walker tables do not fit the 160 KiB of LDS of a compute unit and for
-   systems with backflow. */
+   outside qmc_precision QMC_EINVAL.  Returns QMC_EUNSUPPORTED for systems
+   with backflow and when the walker tables do not fit the 160 KiB of LDS of
+   a compute unit.  These are the kernel's, and at least, per lane, the larger
+   of 2 (n_ao + n_mo, rounded up to a table width) and 3 + 2 n_atoms
+   (2 jas_een_n + 5) doubles, and 6 n_atoms per walker. */
 qmc_status qmc_grad(qmc_system *sys, int32_t precision, const double *d_X, int64_t W, double *d_dlogpsi,
                     double *d_deloc_dtheta, double *d_dlogpsi_dR, double *d_deloc_dR, void *stream);
 

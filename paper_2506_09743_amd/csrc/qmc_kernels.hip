@@ -142,6 +142,8 @@ size_t explicit_lds_bytes(const DevSystem &S) {
         QMC_CASE(4) QMC_CASE(8) QMC_CASE(12) QMC_CASE(16) QMC_CASE(20) QMC_CASE(24) QMC_CASE(32)
 #undef QMC_CASE
     }
+    const int admit = walker::een_admit(S);
+    if (per < admit) per = admit;
     return (size_t)S.WPW * per * sizeof(double);
 }
 

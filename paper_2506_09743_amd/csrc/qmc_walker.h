@@ -472,6 +472,14 @@ __host__ __device__ inline int een_table(const DevSystem &S) {
     return S.LW * S.n_atoms * 2 * S.een_n;
 }
 
+// Doubles of the e-e-n tables by which the explicit and backflow methods admit a
+// system: the factors and every lane's geometry.  The tables no longer hold the
+// geometry here; it stays in the limit so that the systems a caller sees refused
+// do not depend on the kernels' layout.
+inline int een_admit(const DevSystem &S) {
+    return S.een_n > 0 ? S.LW * S.n_atoms * (2 * S.een_n + kEenGeo) + 3 * S.LW : 0;
+}
+
 template <int NMO, bool FULL = true>
 __host__ __device__ inline int tab_c0(const DevSystem &S) {
     return FULL ? 0 : (S.n_up < S.n_dn ? S.n_up : S.n_dn) & ~1;
