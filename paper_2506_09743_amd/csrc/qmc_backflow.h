@@ -196,7 +196,7 @@ struct MoChannels {
 #pragma unroll
         for (int m = 0; m < MB; ++m) A[m] = Ap[m];
     }
-    __device__ __forceinline__ void flush() {  // at the end of each shell
+    __device__ __forceinline__ void flush(int) {  // at the end of each shell, of nc rows
         while (pending >= 4) contract();
     }
     __device__ __forceinline__ void finish(double *out) {  // out[c * NMO + m]
@@ -221,14 +221,15 @@ struct MoChannels {
     }
 };
 
-// The same on the vector unit (kFewMO).
+// The same on the vector unit (kFewMO; the row of C moves by flush, as there).
 template <int NC>
 struct MoChannels<kFewMO, NC> {
     static constexpr int kRows = 0;
     const __attribute__((address_space(4))) double *row;
+    int comp;  // component within the shell
     double acc[NC][kFewMO];
 
-    __device__ __forceinline__ MoChannels(const DevSystem &S, int, double *) : row(const_tab(S.mo)) {
+    __device__ __forceinline__ MoChannels(const DevSystem &S, int, double *) : row(const_tab(S.mo)), comp(0) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -238,10 +239,13 @@ struct MoChannels<kFewMO, NC> {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int m = 0; m < kFewMO; ++m) acc[c][m] += v[c] * row[m];
-        row += kFewMO;
+            for (int m = 0; m < kFewMO; ++m) acc[c][m] += v[c] * row[comp * kFewMO + m];
+        ++comp;
     }
-    __device__ __forceinline__ void flush() {}
+    __device__ __forceinline__ void flush(int nc) {
+        row += nc * kFewMO;
+        comp = 0;
+    }
     __device__ __forceinline__ void finish(double *out) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -344,7 +348,7 @@ __device__ __forceinline__ void mo_channels_bf(const DevSystem &S, int lane, dou
                     put(P * R, R2 * Y[yi] + (d[j] * u[i] + d[i] * u[j]) + P * w1, g[0], g[1], g[2]);
                 }
         }
-        rows.flush();
+        rows.flush((si.y + 1) * (si.y + 2) / 2);
     }
     rows.finish(out);
 }

@@ -101,8 +101,8 @@ struct MoRows {
 #pragma unroll
         for (int m = 0; m < MB; ++m) A[m] = Ap[m];
     }
-    // at the end of each shell
-    __device__ __forceinline__ void flush() {
+    // at the end of each shell, of nc rows
+    __device__ __forceinline__ void flush(int) {
         while (mu - done >= 4) contract();
     }
     __device__ __forceinline__ void finish(double (&out)[NMO]) {
@@ -121,22 +121,30 @@ struct MoRows {
     }
 };
 
-// The same on the vector unit (kFewMO).
+// The same on the vector unit (kFewMO).  The shell's first row of C moves once
+// per shell, by flush, and not by the pushes: a pointer that the branches over s,
+// p and d shells advance by different amounts was compiled without its step in the
+// d branch, and the next shell read C at a stale address (qmc_grad faulted for
+// any system of at most 4 MOs with a shell behind a d shell).
 template <>
 struct MoRows<kFewMO> {
     const __attribute__((address_space(4))) double *row;
+    int c;  // component within the shell
     double acc[kFewMO];
 
-    __device__ __forceinline__ MoRows(const DevSystem &S, int, double *) : row(const_tab(S.mo)) {
+    __device__ __forceinline__ MoRows(const DevSystem &S, int, double *) : row(const_tab(S.mo)), c(0) {
 #pragma unroll
         for (int m = 0; m < kFewMO; ++m) acc[m] = 0.0;
     }
     __device__ __forceinline__ void push(double v) {
 #pragma unroll
-        for (int m = 0; m < kFewMO; ++m) acc[m] += v * row[m];
-        row += kFewMO;
+        for (int m = 0; m < kFewMO; ++m) acc[m] += v * row[c * kFewMO + m];
+        ++c;
     }
-    __device__ __forceinline__ void flush() {}
+    __device__ __forceinline__ void flush(int nc) {
+        row += nc * kFewMO;
+        c = 0;
+    }
     __device__ __forceinline__ void finish(double (&out)[kFewMO]) {
 #pragma unroll
         for (int m = 0; m < kFewMO; ++m) out[m] = acc[m];
@@ -176,7 +184,7 @@ __device__ __forceinline__ void mo_values_f64(const DevSystem &S, int lane, doub
             rows.push(a.dy * a.dz * R);
             rows.push(a.dz * a.dz * R);
         }
-        rows.flush();
+        rows.flush((si.y + 1) * (si.y + 2) / 2);
     }
     rows.finish(phi);
 }
@@ -263,8 +271,9 @@ __device__ __forceinline__ void mo_values_direction(const DevSystem &S, int lane
             beta.push(a.dy * a.dz * X + R2 * (a.dz * gJ[1] + a.dy * gJ[2]));
             beta.push(a.dz * a.dz * X + R2 * (1.0 + 2.0 * a.dz * gJ[2]));
         }
-        chi.flush();
-        beta.flush();
+        const int nc = (si.y + 1) * (si.y + 2) / 2;
+        chi.flush(nc);
+        beta.flush(nc);
     }
     chi.finish(phi);
     beta.finish(bvec);
