@@ -36,7 +36,7 @@
 // per configuration of its spin, its g_i and, per configuration of the
 // other spin, v_i = sum over its cross partners i' of Y_ii' g_i', so the
 // cross term of a determinant is the sum of g_i . v_i over all lanes.
-// CO, 27 determinants, 8192 walkers, a Metropolis step: 278 -> 207 us (MO
+// CO, 27 determinants, 8192 walkers, a Metropolis step: 278 -> 209 us (MO
 // channels on the matrix cores, J blocks from a table).  What bounds it now:
 // one wave per SIMD at 512 registers, FP64 work, and moves between vector and
 // accumulation registers where the Y blocks are used.
@@ -148,8 +148,8 @@ __device__ __forceinline__ void shell_radial_h(const DevSystem &S, int p, int np
 }
 
 // NC channels of AO rows contracted with the MO coefficients, the way MoRows
-// does one: out[c][m] = sum_mu C[mu][m] row_mu[c].  buf: mo_channel_lds<NMO, NC>
-// bytes of LDS, a ring of kRows rows per channel (at most 3 + 6 are pending).
+// does one: out[c][m] = sum_mu C[mu][m] row_mu[c].  buf: NC rings of kRows rows
+// of kWave doubles in LDS (bf_orbital_lds_bytes; at most 3 + 6 are pending).
 template <int NMO, int NC>
 struct MoChannels {
     static constexpr int MB = NMO / 4, kRows = 12;
@@ -255,12 +255,14 @@ struct MoChannels<kFewMO, NC> {
 };
 
 // The low-rank kernels contract all five channels in one pass over the shells
-// while their accumulators (10 NMO registers) fit beside the Y blocks; wider
-// tables, and the kernels that factorise every configuration, whose loop spills
-// what the accumulators displace, take value and psi, then the gradient.  CO, a
-// step, one pass against two: low-rank, 27 determinants, 8192 walkers 214 / 228
-// us; every configuration factorised, 100 determinants, 65 536 walkers 11.1 /
-// 10.1 ms.
+// up to 20 MOs; wider tables, whose accumulators (10 NMO registers) displace
+// more, and the kernels that factorise every configuration, whose loop spills
+// what the accumulators displace, take value and psi, then the gradient.  At 20
+// MOs the Y blocks and the accumulators together fill all 512 registers: the
+// step kernel spills 31 of them, the evaluation 8 (16 MOs: 493 and 480, none).
+// The second pass costs more than these spills.  CO, a step, one pass against
+// two: low-rank, 27 determinants, 8192 walkers 214 / 228 us; every configuration
+// factorised, 100 determinants, 65 536 walkers 11.1 / 10.1 ms.
 template <int NMO, bool LR>
 constexpr int bf_channels() { return LR && NMO <= 20 ? 5 : 3; }
 

@@ -525,6 +525,7 @@ __device__ __forceinline__ void jastrow_derivs(const DevSystem &S, const Lane &L
 // the contractions here, then with these two and one reduction per pair of
 // results: Li2, 32 768 walkers 542 -> 254 -> 209 us (175 MB written); CO, 8192
 // walkers 564 -> 217 -> 161 us; many-body CO, 4099 walkers 2523 -> 349 -> 264 us.
+// Idle lanes run unmasked and selects drop their shares: 211, 163 and 266 us.
 template <int NMO, typename RT>
 __global__ __launch_bounds__(kWave) void k_grad(DevSystem S, const double *__restrict__ X, int64_t W,
                                                 GradOut G) {

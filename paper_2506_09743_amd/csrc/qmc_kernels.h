@@ -383,8 +383,10 @@ __global__ __launch_bounds__(kWave, 1) void k_metropolis_loop(DevSystem S, doubl
 // scans walkers [b span, (b + 1) span) 64 at a time and gathers the ones it
 // takes into its wave's walker slots, WPW at a time, so a few hundred
 // work-groups cover any W and each usually evaluates once or twice.  Every
-// work-group leaves the loop once its range is scanned.  Few waves run at
-// once, so the kernel takes the registers it wants (one wave per SIMD).
+// work-group leaves the loop once its range is scanned.  The bound of three
+// waves per SIMD (168 registers, the rest in scratch) lets its waves run
+// beside the step kernel's; with the registers it would take at one wave it
+// waited for whole SIMDs to drain and ran after the step kernel.
 constexpr int kRefineGroups = 1024;
 
 template <int NMO, typename RT, int MF, bool MC>

@@ -41,8 +41,8 @@ constexpr size_t orbital_lds_bytes() {
 
 // Up to this many MOs (H2-sized systems) the vector unit contracts directly:
 // a row is one scalar load of 32 bytes and 4 multiply-adds, less than the
-// exchange through LDS costs a lone wave (1024 H2 walkers, 200 steps: 1.41 ms
-// through the matrix cores).
+// exchange through LDS costs a lone wave (1024 H2 walkers, 200 steps: 1.30 ms
+// so, 1.41 ms through the matrix cores).
 constexpr int kFewMO = 4;
 
 // Displacement from the current atom, in the arithmetic of the AO values
