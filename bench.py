@@ -202,12 +202,13 @@ def grad_flops_per_walker(sysd) -> dict:
     return f
 
 
-def hbm_bytes_per_launch(sysd, W: int, steps: int) -> int:
+def hbm_bytes_per_launch(sysd, W: int, steps: int, acceptance: float) -> int:
     """Walker state read and written once per step (the FP64 block takes one
-    kernel per step): X, log|Psi|, sign, E_L and four accumulators, FP64."""
+    kernel per step): X, log|Psi|, sign, E_L and four accumulators, FP64; the
+    positions of a rejected move are not written."""
     from paper_2506_09743_amd import synth
-    per = (3 * synth.n_elec(sysd) + 7) * 8
-    return 2 * per * W * steps
+    per = 2 * 7 * 8 + (1 + acceptance) * 3 * synth.n_elec(sysd) * 8
+    return round(per * W * steps)
 
 
 def kernel_sha() -> str:
@@ -805,7 +806,8 @@ def main():
                            "per step and half of the walkers, the halves on two streams"),
                 "flops_per_walker_step": per_unit, "flops_per_walker_step_recount": fl["total"],
                 "walker_steps_per_launch": W * args.chunk,
-                "hbm_bytes_per_launch_algorithmic": hbm_bytes_per_launch(sysd, W, args.chunk),
+                "hbm_bytes_per_launch_algorithmic": hbm_bytes_per_launch(sysd, W, args.chunk,
+                                                                         main_form["acceptance"]),
                 "launch_ms_mean": main_form["launch_ms_mean"]}
     for form in results:
         if form == "fp64":
