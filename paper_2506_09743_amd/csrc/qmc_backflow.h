@@ -262,9 +262,10 @@ struct MoChannels<kFewMO, NC> {
 // step kernel spills 31 of them, the evaluation 8 (16 MOs: 493 and 480, none).
 // The second pass costs more than these spills.  CO, a step, one pass against
 // two: low-rank, 27 determinants, 8192 walkers 214 / 228 us; every configuration
-// factorised, 100 determinants, 65 536 walkers 11.1 / 10.1 ms.
+// factorised, 100 determinants, 65 536 walkers 11.1 / 10.1 ms.  Up to kFewMO
+// MOs both kinds have the registers for one pass.
 template <int NMO, bool LR>
-constexpr int bf_channels() { return LR && NMO <= 20 ? 5 : 3; }
+constexpr int bf_channels() { return NMO <= (LR ? 20 : kFewMO) ? 5 : 3; }
 
 template <int NMO, bool LR>
 constexpr size_t bf_orbital_lds_bytes() {
